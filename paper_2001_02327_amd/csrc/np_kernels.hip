@@ -179,8 +179,17 @@ __device__ __forceinline__ unsigned long long wave_max_u64(unsigned long long v)
     return v;
 }
 
-// Atomic maximum of v over a block of NW wavefronts into *out.
-template <int NW>
+// Maximum of v over a block of NW wavefronts into *out.  Atomics on one address
+// are served one after another, ~12 ns each: the 4096 blocks of a 1024^2 force
+// test spent ~45 of its 52 us there.  So a block first reads *out (~6 ns each,
+// 27 us for that test) and issues its atomic only when it would raise the
+// maximum, which never falls during a kernel (a stale read costs a superfluous
+// atomic at most); and the kernels that have little work per block run at most
+// kReduceBlocks blocks in grid-stride loops (19 us for that test).  CHECK is off
+// in the z-march passes, whose blocks end far enough apart (residual norm of a
+// 258^3 level: 33.8 us without the read, 36.9 with it).
+constexpr int kReduceBlocks = 512;
+template <int NW, bool CHECK = true>
 __device__ __forceinline__ void block_max_to_w(unsigned long long v, unsigned long long* out)
 {
     __shared__ unsigned long long red[NW];
@@ -191,13 +200,14 @@ __device__ __forceinline__ void block_max_to_w(unsigned long long v, unsigned lo
     if (threadIdx.x == 0) {
         unsigned long long m = red[0];
         for (int w = 1; w < NW; w++) m = red[w] > m ? red[w] : m;
-        atomicMax(out, m);
+        if (!CHECK || m > __hip_atomic_load(out, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(out, m);
     }
 }
 
+template <bool CHECK = true>
 __device__ __forceinline__ void block_max_to(unsigned long long v, unsigned long long* out)
 {
-    block_max_to_w<kBlock / 64>(v, out);
+    block_max_to_w<kBlock / 64, CHECK>(v, out);
 }
 
 __device__ __forceinline__ unsigned long long abs_bits(double a)
@@ -218,7 +228,9 @@ __device__ __forceinline__ double resid(double f, double s, double u, double two
 // right-hand side = 4 pi G rho on Gamma^0 (caller gives Omega^0 plus its inner
 // layer, (n+2)^d points).
 // Also reduces max |f| into *fmax (grid-stride loop, one atomic per block).
-constexpr int kInitBlocks = 16384;
+// 2048 blocks fill the chip (8 per CU); 16384 spent ~200 us of their 200-us
+// launch at 256^3 in the atomic
+constexpr int kInitBlocks = 2048;
 template <int D>
 __global__ void __launch_bounds__(kBlock) k_level0_init(SGrid g, const double* __restrict__ rho0,
                                                         const double* __restrict__ phi_outer, double fourpiG,
@@ -303,11 +315,11 @@ __global__ void __launch_bounds__(kBlock) k_interface_fill(SGrid gc, const doubl
                                                            double fourpiG, double* __restrict__ phif,
                                                            double* __restrict__ ff, unsigned long long* fmax)
 {
-    long t = xcd_block() * kBlock + threadIdx.x;
-    long total = (long)gf.nx * gf.ny * gf.nz;
+    const long total = (long)gf.nx * gf.ny * gf.nz;
+    const long stride = (long)gridDim.x * kBlock;
     const int nfx = gf.nx - 4, nfy = gf.ny - 4, nfz = gf.nz - 4;
     unsigned long long best = 0;
-    if (t < total) {
+    for (long t = xcd_block() * kBlock + threadIdx.x; t < total; t += stride) {
     int pi = (int)(t % gf.nx);
     long r = t / gf.nx;
     int pj = (int)(r % gf.ny);
@@ -330,7 +342,8 @@ __global__ void __launch_bounds__(kBlock) k_interface_fill(SGrid gc, const doubl
         v = interp_tensor<D>(fc, gc, qi, qj, qk, si, sj, sk);
     }
     ff[p] = v;
-    best = abs_bits(v);
+    const unsigned long long b = abs_bits(v);
+    best = b > best ? b : best;
     }
     if (fmax) block_max_to(best, fmax);
 }
@@ -732,7 +745,7 @@ __global__ void __launch_bounds__(kForceBlock) k_forces3_zm(SGrid g, double m12d
             }
         }
     }
-    if (DELTA) block_max_to_w<kForceBlock / 64>(best, maxbits);
+    if (DELTA) block_max_to_w<kForceBlock / 64, false>(best, maxbits);
 }
 
 // Forces into F (d arrays of n^d) and the maximum change against the values
@@ -742,10 +755,10 @@ __global__ void __launch_bounds__(kBlock) k_force_delta(SGrid g, double m12dx, c
                                                         double* __restrict__ F, unsigned long long* maxbits)
 {
     const int nx = g.nx - 4, ny = g.ny - 4, nz = D == 3 ? g.nz - 4 : 1;
-    long t = xcd_block() * kBlock + threadIdx.x;
-    long total = (long)nx * ny * nz;
+    const long total = (long)nx * ny * nz;
+    const long stride = (long)gridDim.x * kBlock;
     unsigned long long m = 0;
-    if (t < total) {
+    for (long t = xcd_block() * kBlock + threadIdx.x; t < total; t += stride) {
         int i = (int)(t % nx);
         long r = t / nx;
         int j = (int)(r % ny);
@@ -892,7 +905,7 @@ __global__ void __launch_bounds__(kBlock) k_resid_norm3(SGrid g, const double* _
             }
         }
     }
-    block_max_to(best, maxbits);
+    block_max_to<false>(best, maxbits);
 }
 
 // Max norm of the residual's mean over boxes of 4^3 active points of a 3-D
@@ -1623,7 +1636,7 @@ __global__ void __launch_bounds__(kFsBlock) k_full_sweep3(const T* __restrict__ 
         load(k, L);
         step(k, L);
     }
-    if (MODE) block_max_to(best, maxbits);
+    if (MODE) block_max_to<false>(best, maxbits);
 }
 
 // Paired form of k_full_sweep3 (even row length hx): a lane owns the compact
@@ -1834,7 +1847,7 @@ __global__ void __launch_bounds__(kFsBlock) k_full_sweep3_pair(const T* __restri
             b1[i] = ba[i];
         }
     }
-    if (MODE) block_max_to(best, maxbits);
+    if (MODE) block_max_to<false>(best, maxbits);
 }
 
 // Coarse right-hand side and correction of one coarse point.  With seed_h2 > 0
@@ -3347,7 +3360,7 @@ __global__ void __launch_bounds__(kBlock) k_dc_outer3(SGrid g, DcIn<TL, UPD> in,
             }
         }
     }
-    block_max_to(best, maxbits);
+    block_max_to<false>(best, maxbits);
 }
 
 // Paired form of k_dc_outer3 (row length hx even): a thread owns the compact
@@ -3540,7 +3553,7 @@ __global__ void __launch_bounds__(kBlock) k_dc_outer3_pair(SGrid g, DcIn<TL, UPD
             step(pk, d);
         }
     }
-    block_max_to(best, maxbits);
+    block_max_to<false>(best, maxbits);
 }
 
 // Copy of the ghost layer (the points outside the active box) of a nested-level
@@ -3626,7 +3639,9 @@ void launch_interface_fill(int dim, hipStream_t st, SGrid gc, const double* phic
                            fc, gf, offx, offy, offz, rho, fourpiG, phif, ff, pblocks, fmax);
         return;
     }
-    NP_DISPATCH(dim, k_interface_fill, dim3(ceil_div(npoints(gf), kBlock)), dim3(kBlock), st, gc, phic, fc, gf,
+    int blocks = ceil_div(npoints(gf), kBlock);
+    if (blocks > kReduceBlocks) blocks = kReduceBlocks;
+    NP_DISPATCH(dim, k_interface_fill, dim3(blocks), dim3(kBlock), st, gc, phic, fc, gf,
                 offx, offy, offz, rho, fourpiG, phif, ff, fmax);
 }
 
@@ -3660,7 +3675,9 @@ void launch_force_delta(int dim, hipStream_t st, SGrid g, double dx, const doubl
                            m12dx, phi, F, F + total, F + 2 * total, pblocks, maxbits);
         return;
     }
-    NP_DISPATCH(dim, k_force_delta, dim3(ceil_div(total, kBlock)), dim3(kBlock), st, g, m12dx, phi, F, maxbits);
+    int blocks = ceil_div(total, kBlock);
+    if (blocks > kReduceBlocks) blocks = kReduceBlocks;
+    NP_DISPATCH(dim, k_force_delta, dim3(blocks), dim3(kBlock), st, g, m12dx, phi, F, maxbits);
 }
 
 void launch_export(int dim, hipStream_t st, SGrid g, const double* a, double* out)
@@ -3689,7 +3706,7 @@ void launch_norm(int dim, hipStream_t st, SGrid g, const double* u, const double
         return;
     }
     int blocks = ceil_div(ncompact_active(dim, g), kBlock);
-    if (blocks > 2048) blocks = 2048;
+    if (blocks > kReduceBlocks) blocks = kReduceBlocks;
     NP_DISPATCH(dim, k_norm, dim3(blocks, g.nb), dim3(kBlock), st, g, u, f, inv_h2, mode, maxbits);
 }
 
