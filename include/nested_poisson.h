@@ -346,6 +346,11 @@ size_t np_net_workspace_bytes(int cin, int cout, long nvox);
  * weights, FP32 accumulation; 1 <= cin, cout <= 16. */
 int np_net_conv3d_fwd(const float* in, int cin, const unsigned short* w_bf16, const float* bias, int cout, int relu,
                       int batch, int nz, int ny, int nx, float* out, void* stream);
+/* np_net_conv3d_fwd with ReLU followed by np_net_round_bf16 of the output, in
+ * one pass for the network's layer shapes: a hidden layer of the training
+ * forward pass.  Same results as the two calls. */
+int np_net_conv3d_fwd_round(const float* in, int cin, const unsigned short* w_bf16, const float* bias, int cout, int batch,
+                            int nz, int ny, int nx, float* out, void* stream);
 /* A layer of the network on the matrix cores (the inference path), for
  * (cin, cout) = (2, 16), (16, 16) or (16, 1): bfloat16 activations in,
  * bfloat16 out (cout 16) or FP32 out (cout 1), FP32 accumulation
@@ -356,6 +361,11 @@ int np_net_conv3d_fwd_mfma(const unsigned short* in_bf16, int cin, const unsigne
 /* gin = d loss / d in given gout = d loss / d out. */
 int np_net_conv3d_bwd_data(const float* gout, int cout, const unsigned short* w_bf16, int cin, int batch, int nz,
                            int ny, int nx, float* gin, void* stream);
+/* np_net_conv3d_bwd_data followed by np_net_relu_bwd(act, gin), in one pass for
+ * the network's layer shapes; act: the activations that are the layer's input
+ * (gin's shape).  Same results as the two calls. */
+int np_net_conv3d_bwd_data_relu(const float* gout, int cout, const unsigned short* w_bf16, int cin, int batch, int nz,
+                                int ny, int nx, const float* act, float* gin, void* stream);
 /* gw [27][cout][cin] and gb [cout] (FP32), summed in a fixed order (deterministic). */
 int np_net_conv3d_bwd_weight(const float* in, int cin, const float* gout, int cout, int batch, int nz, int ny, int nx,
                              float* gw, float* gb, float* workspace, size_t workspace_bytes, void* stream);

@@ -123,6 +123,10 @@ SIGNATURES = {
                                               ctypes.c_int, ctypes.c_int, ctypes.c_int, _vp, _vp]),
     "np_net_conv3d_bwd_data": (ctypes.c_int, [_vp, ctypes.c_int, _vp, ctypes.c_int, ctypes.c_int, ctypes.c_int,
                                               ctypes.c_int, ctypes.c_int, _vp, _vp]),
+    "np_net_conv3d_fwd_round": (ctypes.c_int, [_vp, ctypes.c_int, _vp, _vp, ctypes.c_int, ctypes.c_int, ctypes.c_int,
+                                               ctypes.c_int, ctypes.c_int, _vp, _vp]),
+    "np_net_conv3d_bwd_data_relu": (ctypes.c_int, [_vp, ctypes.c_int, _vp, ctypes.c_int, ctypes.c_int, ctypes.c_int,
+                                                   ctypes.c_int, ctypes.c_int, _vp, _vp, _vp]),
     "np_net_conv3d_bwd_weight": (ctypes.c_int, [_vp, ctypes.c_int, _vp, ctypes.c_int, ctypes.c_int, ctypes.c_int,
                                                 ctypes.c_int, ctypes.c_int, _vp, _vp, _vp, ctypes.c_size_t, _vp]),
     "np_net_relu_bwd": (ctypes.c_int, [_vp, _vp, ctypes.c_long, _vp]),

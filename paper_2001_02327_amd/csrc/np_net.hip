@@ -13,6 +13,7 @@
 #include <cstdint>
 #include <cstdio>
 #include <mutex>
+#include <type_traits>
 
 #include "../../include/nested_poisson.h"
 #include "np_internal.h"
@@ -290,18 +291,6 @@ __global__ void __launch_bounds__(kNB) k_conv_bwd_weight_part(const float* __res
     for (int e = threadIdx.x; e < ne; e += kNB, q++) part[(long)blockIdx.x * ne + e] = acc[q];
 }
 
-// Second stage: gw/gb = sum over the partials, in a fixed order.
-__global__ void k_sum_parts(const float* __restrict__ part, int nparts, int ne, int nw, float* __restrict__ gw,
-                            float* __restrict__ gb)
-{
-    const int e = blockIdx.x * kNB + threadIdx.x;
-    if (e >= ne) return;
-    float s = 0.0f;
-    for (int p = 0; p < nparts; p++) s += part[(long)p * ne + e];
-    if (e < nw) gw[e] = s;
-    else gb[e - nw] = s;
-}
-
 __global__ void k_relu_bwd(const float* __restrict__ act, float* __restrict__ g, long n)
 {
     const long i = (long)blockIdx.x * kNB + threadIdx.x;
@@ -331,13 +320,26 @@ __global__ void k_mse(const float* __restrict__ pred, const float* __restrict__ 
     if (threadIdx.x == 0) part[blockIdx.x] = red[0];
 }
 
-__global__ void k_sum(const float* __restrict__ part, int n, float scale, float* __restrict__ out)
+// out = scale * (part[0] + part[1] + ...), added one after another in that
+// order by one wavefront: 64 partials at a time are loaded together and passed
+// to the running sum lane by lane (a thread that loaded and added took 346 us
+// for the 8583 partials of a 130^3 sample, all of it load latency).
+__global__ void __launch_bounds__(64) k_sum(const float* __restrict__ part, int n, float scale, float* __restrict__ out)
 {
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        float s = 0.0f;
-        for (int i = 0; i < n; i++) s += part[i];
-        out[0] = s * scale;
+    const int lane = threadIdx.x;
+    float s = 0.0f, next = lane < n ? part[lane] : 0.0f;
+    for (int i0 = 0; i0 < n; i0 += 64) {
+        const float v = next;
+        if (i0 + 64 + lane < n) next = part[i0 + 64 + lane];
+        const int m = n - i0 < 64 ? n - i0 : 64;
+        if (m == 64) {
+#pragma unroll
+            for (int e = 0; e < 64; e++) s += __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), e));
+        } else {
+            for (int e = 0; e < m; e++) s += __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), e));
+        }
     }
+    if (lane == 0) out[0] = s * scale;
 }
 
 // Adam (Kingma & Ba) with bias correction on FP32 master weights; the
@@ -544,6 +546,584 @@ __global__ void __launch_bounds__(256) k_conv_mfma_lds(const uint16_t* __restric
     }
 }
 
+// ------------------------------------------------------------------ training on the FP32 matrix cores
+// The convolutions of a training step with FP32 activations and gradients, for
+// the network's own channel counts.  v_mfma_f32_16x16x4_f32 is a chain of four
+// FP32 fused multiply-adds in the order of k (checked bit for bit against
+// fmaf), so a forward output formed tap by tap and channel by channel has the
+// bits of k_conv_fwd_t's: the activations that are rounded to bfloat16 next
+// keep their values.  FP32 matrix products run at twice the rate of the vector
+// unit (153 TFLOP/s measured), and one LDS read feeds 16 of them.
+//
+// Operand layout: lane l = 16 q + r supplies A[row r][k q] and B[k q][col r]
+// and receives D[rows 4q .. 4q+3][col r].  Rows are output channels and columns
+// 16 voxels along x, so a lane ends with four neighbouring channels of a voxel.
+//
+// A workgroup produces blocks of 16 (x) x 4 (y) x 4 (z) voxels, 4 rows of 16
+// per wavefront, from a block of 18 x 6 x 6 voxels in LDS (zero outside the volume).
+// Taps outside the volume are products with zero instead of being skipped; with a
+// non-finite weight that would make NaN, so then the block is formed voxel by
+// voxel as in k_conv_fwd_t (conv_voxel).
+constexpr int kTSX = 18, kTSY = 6, kTSZ = 6, kTNV = kTSX * kTSY * kTSZ;
+constexpr long kTrainBlocks = 768;  // three workgroups per CU (52 KB of LDS each) for 16 channels
+
+struct ConvTile {
+    int b, x0, y0, z0;
+};
+
+__device__ __forceinline__ ConvTile conv_tile(long id, int Z, int Y, int X)
+{
+    const int ntx = (X + 15) >> 4, nty = (Y + 3) >> 2, ntz = (Z + 3) >> 2;
+    const int bx = (int)(id % ntx);
+    id /= ntx;
+    const int by = (int)(id % nty);
+    id /= nty;
+    return ConvTile{(int)(id / ntz), bx * 16, by * 4, (int)(id % ntz) * 4};
+}
+
+__host__ __device__ inline long conv_tiles(int B, int Z, int Y, int X)
+{
+    return (long)B * ((Z + 3) / 4) * ((Y + 3) / 4) * ((X + 15) / 16);
+}
+
+// element index of voxel lv (0 .. kTNV-1) of a block's input region, or -1 outside the volume
+__device__ __forceinline__ long region_voxel(const ConvTile& T, int lv, int Z, int Y, int X)
+{
+    const int lx = lv % kTSX, ly = (lv / kTSX) % kTSY, lz = lv / (kTSX * kTSY);
+    const int x = T.x0 - 1 + lx, y = T.y0 - 1 + ly, z = T.z0 - 1 + lz;
+    if (x < 0 || x >= X || y < 0 || y >= Y || z < 0 || z >= Z) return -1;
+    return (((long)T.b * Z + z) * Y + y) * X + x;
+}
+
+// Weight of output channel o from input channel i at the tap that reads the
+// input at offset t (dz, dy, dx): the layer's own (forward), or for the data
+// gradient, whose input is gout (channel i of it) and output gin (channel o),
+// the mirrored tap of the transposed weights.
+template <int CI, int CO, bool BWD>
+__device__ __forceinline__ float tap_weight(const uint16_t* __restrict__ w, int t, int o, int i)
+{
+    return bf16_to_f32(BWD ? w[((26 - t) * CI + i) * CO + o] : w[(t * CO + o) * CI + i]);
+}
+
+// One channel of one output voxel by scalar arithmetic, taps outside the volume skipped.
+template <int CI, int CO, bool BWD>
+__device__ __forceinline__ float conv_voxel(const float* __restrict__ in, const uint16_t* __restrict__ w,
+                                            const float* __restrict__ bias, int Z, int Y, int X, int b, int z, int y,
+                                            int x, int o)
+{
+    float acc = BWD ? 0.0f : bias[o];
+#pragma unroll 1
+    for (int t = 0; t < 27; t++) {
+        const int zz = z + t / 9 - 1, yy = y + t / 3 % 3 - 1, xx = x + t % 3 - 1;
+        if (zz < 0 || zz >= Z || yy < 0 || yy >= Y || xx < 0 || xx >= X) continue;
+        const float* src = in + ((((long)b * Z + zz) * Y + yy) * X + xx) * CI;
+#pragma unroll 1
+        for (int i = 0; i < CI; i++) acc = fmaf(tap_weight<CI, CO, BWD>(w, t, o, i), src[i], acc);
+    }
+    return acc;
+}
+
+// What follows the sums of a training convolution: forward, ReLU and the
+// rounding to bfloat16 (kept in FP32) of a hidden layer; data gradient, the mask
+// of the ReLU that produced the layer's input (act, may be null).
+struct ConvPost {
+    int relu, round;
+    const float* act;
+};
+
+__device__ __forceinline__ float conv_post(float v, const ConvPost& P, float act)
+{
+    if (P.relu) v = fmaxf(v, 0.0f);
+    if (P.round) v = bf16_to_f32(f32_to_bf16(v));
+    if (P.act && !(act > 0.0f)) v = 0.0f;
+    return v;
+}
+
+// the block voxel by voxel (a thread each): only with non-finite weights
+template <int CI, int CO, bool BWD>
+__device__ __forceinline__ void conv_block_scalar(const ConvTile& T, const float* __restrict__ in,
+                                                  const uint16_t* __restrict__ w, const float* __restrict__ bias,
+                                                  int Z, int Y, int X, const ConvPost& P, float* __restrict__ out)
+{
+    const int x = T.x0 + (int)(threadIdx.x & 15), y = T.y0 + (int)(threadIdx.x >> 4 & 3), z = T.z0 + (int)(threadIdx.x >> 6);
+    if (x >= X || y >= Y || z >= Z) return;
+    const long base = ((((long)T.b * Z + z) * Y + y) * X + x) * CO;
+#pragma unroll 1
+    for (int o = 0; o < CO; o++)
+        out[base + o] = conv_post(conv_voxel<CI, CO, BWD>(in, w, bias, Z, Y, X, T.b, z, y, x, o), P,
+                                  P.act ? P.act[base + o] : 0.0f);
+}
+
+__device__ __forceinline__ void store_row16(const ConvTile& T, int rid, int q, int r, int Z, int Y, int X, const v4f& acc,
+                                            const ConvPost& P, float* __restrict__ out)
+{
+    const int x = T.x0 + r, y = T.y0 + (rid & 3), z = T.z0 + (rid >> 2);
+    if (x >= X || y >= Y || z >= Z) return;
+    const long base = ((((long)T.b * Z + z) * Y + y) * X + x) * 16 + 4 * q;
+    float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (P.act) a = *(const float4*)(P.act + base);
+    *(float4*)(out + base) = make_float4(conv_post(acc[0], P, a.x), conv_post(acc[1], P, a.y), conv_post(acc[2], P, a.z),
+                                         conv_post(acc[3], P, a.w));
+}
+
+// 16 -> 16 channels: the layer's forward pass, or its data gradient (BWD).  The
+// 27 x 16 x 16 weights stay in registers (108 per lane) over the blocks a
+// workgroup runs; a voxel's channels lie in LDS in the order 4 q + s for
+// channel 4 s + q, so that one 16-byte read gives a lane its operands of four
+// products.  Bound by the matrix cores (108 products of 32 cycles per row of 16
+// voxels: 0.22 ms at 130^3 with the padding of its rows to 16): forward 592 ->
+// 301 us, data gradient 2690 -> 288 us there, launch included.
+constexpr int kTVS = 20;  // LDS floats per voxel: 16 channels, padded so that 8 voxels in a row meet different banks
+
+template <bool BWD>
+__global__ void __launch_bounds__(256, 3) k_conv16_mfma_f32(const float* __restrict__ in, const uint16_t* __restrict__ w,
+                                                            const float* __restrict__ bias, int B, int Z, int Y, int X,
+                                                            ConvPost P, float* __restrict__ out, long per_block)
+{
+    __shared__ __align__(16) float tile[kTNV * kTVS];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, q = lane >> 4, r = lane & 15;
+    float aw[27][4];
+    bool bad = false;
+    // the weights pass through LDS (read directly, a lane's 108 two-byte loads are strided)
+    uint16_t* const wl = (uint16_t*)tile;
+    for (int e = threadIdx.x; e < 27 * 256; e += 256) wl[e] = w[e];
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < 27; t++)
+#pragma unroll
+        for (int s = 0; s < 4; s++) {
+            aw[t][s] = tap_weight<16, 16, BWD>(wl, t, r, 4 * s + q);
+            bad = bad || !(fabsf(aw[t][s]) < INFINITY);
+        }
+    const bool scalar = __any(bad);  // the same in every wavefront
+    v4f b0 = {0.f, 0.f, 0.f, 0.f};
+    if (!BWD) b0 = v4f{bias[4 * q], bias[4 * q + 1], bias[4 * q + 2], bias[4 * q + 3]};
+    const long ntiles = conv_tiles(B, Z, Y, X);
+    const long first = (long)blockIdx.x * per_block;
+    const long last = first + per_block < ntiles ? first + per_block : ntiles;
+    for (long id = first; id < last; id++) {
+        const ConvTile T = conv_tile(id, Z, Y, X);
+        if (scalar) {
+            conv_block_scalar<16, 16, BWD>(T, in, w, bias, Z, Y, X, P, out);
+            continue;
+        }
+        __syncthreads();  // the previous block's operands have been read
+        for (int v = threadIdx.x; v < kTNV; v += 256) {
+            const long g = region_voxel(T, v, Z, Y, X);
+            float4 c0 = make_float4(0.f, 0.f, 0.f, 0.f), c1 = c0, c2 = c0, c3 = c0;
+            if (g >= 0) {
+                const float4* src = (const float4*)(in + g * 16);
+                c0 = src[0];
+                c1 = src[1];
+                c2 = src[2];
+                c3 = src[3];
+            }
+            float4* dst = (float4*)(tile + v * kTVS);
+            dst[0] = make_float4(c0.x, c1.x, c2.x, c3.x);
+            dst[1] = make_float4(c0.y, c1.y, c2.y, c3.y);
+            dst[2] = make_float4(c0.z, c1.z, c2.z, c3.z);
+            dst[3] = make_float4(c0.w, c1.w, c2.w, c3.w);
+        }
+        __syncthreads();
+        // the wavefront's four rows (y = 0 .. 3 of plane `wave`), two at a time
+#pragma unroll 1
+        for (int p = 0; p < 4; p += 2) {
+            const float* t0 = tile + ((wave * kTSY + p) * kTSX + r) * kTVS + 4 * q;
+            v4f acc0 = b0, acc1 = b0;
+#pragma unroll
+            for (int t = 0; t < 27; t++) {
+                const int off = ((t / 9 * kTSY + t / 3 % 3) * kTSX + t % 3) * kTVS;
+                const v4f u0 = *(const v4f*)(t0 + off), u1 = *(const v4f*)(t0 + off + kTSX * kTVS);
+#pragma unroll
+                for (int s = 0; s < 4; s++) {
+                    acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(aw[t][s], u0[s], acc0, 0, 0, 0);
+                    acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(aw[t][s], u1[s], acc1, 0, 0, 0);
+                }
+            }
+            store_row16(T, wave * 4 + p, q, r, Z, Y, X, acc0, P, out);
+            store_row16(T, wave * 4 + p + 1, q, r, Z, Y, X, acc1, P, out);
+        }
+    }
+}
+
+// 1 or 2 -> 16 channels: forward of the first layer (CI = 2), data gradient of
+// the last (CI = 1).  K is (tap, channel), four per product: 14 or 7 products per
+// row of 16 voxels; a lane's tap differs by q, so it keeps the LDS offset of
+// each of its products.  Bound by the 16-channel output (141 MB at 130^3): forward 99 ->
+// 76 us, data gradient 249 -> 44 us.
+template <int CI, bool BWD>
+__global__ void __launch_bounds__(256) k_conv_few_to16_mfma_f32(const float* __restrict__ in, const uint16_t* __restrict__ w,
+                                                                const float* __restrict__ bias, int B, int Z, int Y, int X,
+                                                                ConvPost P, float* __restrict__ out, long per_block)
+{
+    constexpr int NK = (27 * CI + 3) / 4;
+    __shared__ float tile[kTNV * CI];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, q = lane >> 4, r = lane & 15;
+    float aw[NK];
+    int off[NK];
+    bool bad = false;
+#pragma unroll
+    for (int s = 0; s < NK; s++) {
+        const int k = 4 * s + q, t = k / CI, i = k % CI;
+        // past the last tap: zero times zero
+        aw[s] = t < 27 ? tap_weight<CI, 16, BWD>(w, t, r, i) : 0.0f;
+        off[s] = t < 27 ? ((t / 9 * kTSY + t / 3 % 3) * kTSX + t % 3) * CI + i : 0;
+        bad = bad || !(fabsf(aw[s]) < INFINITY);
+    }
+    const bool scalar = __any(bad);
+    v4f b0 = {0.f, 0.f, 0.f, 0.f};
+    if (!BWD) b0 = v4f{bias[4 * q], bias[4 * q + 1], bias[4 * q + 2], bias[4 * q + 3]};
+    const long ntiles = conv_tiles(B, Z, Y, X);
+    const long first = (long)blockIdx.x * per_block;
+    const long last = first + per_block < ntiles ? first + per_block : ntiles;
+    for (long id = first; id < last; id++) {
+        const ConvTile T = conv_tile(id, Z, Y, X);
+        if (scalar) {
+            conv_block_scalar<CI, 16, BWD>(T, in, w, bias, Z, Y, X, P, out);
+            continue;
+        }
+        __syncthreads();
+        for (int v = threadIdx.x; v < kTNV; v += 256) {
+            const long g = region_voxel(T, v, Z, Y, X);
+#pragma unroll
+            for (int i = 0; i < CI; i++) tile[v * CI + i] = g >= 0 ? in[g * CI + i] : 0.0f;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int p = 0; p < 4; p++) {
+            const float* t0 = tile + ((wave * kTSY + p) * kTSX + r) * CI;
+            v4f acc = b0;
+#pragma unroll
+            for (int s = 0; s < NK; s++) {
+                const float h = 4 * s + q < 27 * CI ? t0[off[s]] : 0.0f;
+                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(aw[s], h, acc, 0, 0, 0);
+            }
+            store_row16(T, wave * 4 + p, q, r, Z, Y, X, acc, P, out);
+        }
+    }
+}
+
+// 16 -> 1 or 2 channels: forward of the last layer (CO = 1), data gradient of the
+// first (CO = 2).  Too few output channels for a matrix product (15 of 16 rows
+// would be padding), so a thread owns one (x, y) column of a 32 x 8 block and
+// marches along z: each input plane is staged in LDS once and its 3 x 3
+// neighbourhood feeds the sums of three output planes, which sit in registers.
+// A voxel's sum runs over its taps in order, channel by channel, as in
+// k_conv_fwd_t.  The weights come as scalar loads of bfloat16 pairs (w is 4-byte
+// aligned) unpacked on the scalar unit: read from LDS they were three quarters of
+// the LDS traffic.  Forward 213 -> 97 us at 130^3, data gradient 1872 -> 189 us.
+// zch: output planes of a workgroup
+constexpr int kFewX = 32, kFewY = 8;
+static_assert(kFewX * kFewY == 256, "a thread per column");
+
+template <int CO, bool BWD>
+__global__ void __launch_bounds__(256) k_conv16_to_few_f32(const float* __restrict__ in, const uint16_t* __restrict__ w,
+                                                           const float* __restrict__ bias, int B, int Z, int Y, int X,
+                                                           ConvPost P, float* __restrict__ out, int zch)
+{
+    constexpr int SX = kFewX + 2, SY = kFewY + 2, NV = SX * SY;
+    __shared__ __align__(16) float tile[NV * kTVS];
+    bool bad = false;
+    for (int e = threadIdx.x; e < 27 * CO * 16; e += 256) bad = bad || !(fabsf(bf16_to_f32(w[e])) < INFINITY);
+    const bool scalar = __syncthreads_or(bad);
+    const int nbx = (X + kFewX - 1) / kFewX, nby = (Y + kFewY - 1) / kFewY, nbz = (Z + zch - 1) / zch;
+    int id = blockIdx.x;
+    const int bx = id % nbx;
+    id /= nbx;
+    const int by = id % nby;
+    id /= nby;
+    const int z0 = (id % nbz) * zch, b = id / nbz;
+    const int lx = threadIdx.x & (kFewX - 1), ly = threadIdx.x / kFewX;
+    const int x = bx * kFewX + lx, y = by * kFewY + ly;
+    const bool live = x < X && y < Y;
+    const int z1 = z0 + zch < Z ? z0 + zch : Z;
+    const auto store = [&](int z, float (&a)[CO]) {
+        const long base = ((((long)b * Z + z) * Y + y) * X + x) * CO;
+#pragma unroll
+        for (int o = 0; o < CO; o++) out[base + o] = conv_post(a[o], P, P.act ? P.act[base + o] : 0.0f);
+    };
+    if (scalar) {
+        if (live)
+            for (int z = z0; z < z1; z++) {
+                float a[CO];
+#pragma unroll
+                for (int o = 0; o < CO; o++) a[o] = conv_voxel<16, CO, BWD>(in, w, bias, Z, Y, X, b, z, y, x, o);
+                store(z, a);
+            }
+        return;
+    }
+    // acc[d]: the sums of output plane zi + 1 - d, which input plane zi enters as its tap plane d
+    float acc[3][CO] = {};
+    for (int zi = z0 - 1; zi <= z1; zi++) {
+        __syncthreads();
+        for (int v = threadIdx.x; v < NV; v += 256) {
+            const int gx = bx * kFewX - 1 + v % SX, gy = by * kFewY - 1 + v / SX;
+            const bool inside = zi >= 0 && zi < Z && gx >= 0 && gx < X && gy >= 0 && gy < Y;
+            const float4* src = (const float4*)(in + ((((long)b * Z + zi) * Y + gy) * X + gx) * 16);
+            float4* dst = (float4*)(tile + v * kTVS);
+#pragma unroll
+            for (int s = 0; s < 4; s++) dst[s] = inside ? src[s] : make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+        __syncthreads();
+        // output plane zi + 1 starts here (its tap row dz = -1)
+#pragma unroll
+        for (int o = 0; o < CO; o++) {
+            acc[2][o] = acc[1][o];
+            acc[1][o] = acc[0][o];
+            acc[0][o] = BWD ? 0.0f : bias[o];
+        }
+        // (a plane outside the volume adds products with zero; unrolled whole, the
+        // loop would hold every weight at once)
+#pragma unroll 1
+        for (int t2 = 0; t2 < 9; t2++) {
+            const float4* src = (const float4*)(tile + ((ly + t2 / 3) * SX + lx + t2 % 3) * kTVS);
+            float a[16];
+#pragma unroll
+            for (int s = 0; s < 4; s++) {
+                const float4 c = src[s];
+                a[4 * s] = c.x;
+                a[4 * s + 1] = c.y;
+                a[4 * s + 2] = c.z;
+                a[4 * s + 3] = c.w;
+            }
+#pragma unroll
+            for (int d = 0; d < 3; d++) {
+                // the tap's 16 CO weights, pairs in scalar registers: CO = 1 two channels, CO = 2 two outputs
+                const uint32_t* wt = (const uint32_t*)w + (BWD ? 26 - (9 * d + t2) : 9 * d + t2) * 8 * CO;
+#pragma unroll
+                for (int e = 0; e < 8 * CO; e++) {
+                    const uint32_t u = wt[e];
+                    const float lo = __uint_as_float(u << 16), hi = __uint_as_float(u & 0xffff0000u);
+                    if constexpr (CO == 1) {
+                        acc[d][0] = fmaf(lo, a[2 * e], acc[d][0]);
+                        acc[d][0] = fmaf(hi, a[2 * e + 1], acc[d][0]);
+                    } else {
+                        acc[d][0] = fmaf(lo, a[e], acc[d][0]);
+                        acc[d][1] = fmaf(hi, a[e], acc[d][1]);
+                    }
+                }
+            }
+        }
+        if (live && zi - 1 >= z0) store(zi - 1, acc[2]);
+    }
+}
+
+// Weight and bias gradients on the FP32 matrix cores, first stage: a workgroup
+// sums over its range of 16 x 4 x 4 blocks of voxels and writes one partial
+// (27 * CO * CI weights, then CO biases).  The voxels are the K dimension, four
+// along x per product.
+//   16 -> 16: rows output channels (gout), columns input channels, one product
+//             per tap: 27 accumulators per lane set, bound by the matrix cores;
+//   2 -> 16:  rows output channels, columns (tap, input channel) pairs, 4 products;
+//   16 -> 1:  rows taps (gout at the voxel minus the tap), columns input channels, 2
+//             products.  Here the voxels are those of the input, and a gout outside
+//             the volume enters as zero; an input that is not finite is left out
+//             of the products and its pairs are added one by one.
+// The four wavefronts' sums meet in LDS in a fixed order.  At 130^3 with the
+// second stage: 5136 -> 449, 1341 -> 108 and 1885 -> 90 us.
+constexpr int kWgBlocks = 512;
+
+template <int CI, int CO>
+__global__ void __launch_bounds__(256, 2) k_conv_bwd_weight_mfma(const float* __restrict__ in, const float* __restrict__ gout,
+                                                                 int B, int Z, int Y, int X, float* __restrict__ part,
+                                                                 long per_block)
+{
+    constexpr bool LAST = CO == 1;                            // the roles of halo and block swap
+    constexpr int NA = CI == 2 ? 4 : (LAST ? 2 : 27);         // accumulators (products per four voxels)
+    constexpr int HC = LAST ? 1 : CI, BC = LAST ? CI : CO;    // channels of the halo and of the block array
+    constexpr int NE = 27 * CI * CO + CO;
+    constexpr int NL = kTNV * HC + 256 * BC > NE ? kTNV * HC + 256 * BC : NE;
+    __shared__ __align__(16) float lds[NL];
+    __shared__ float extra[LAST ? 27 * 16 : 1];
+    float* const halo = lds;
+    float* const blk = lds + kTNV * HC;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, q = lane >> 4, r = lane & 15;
+    v4f acc[NA];
+#pragma unroll
+    for (int a = 0; a < NA; a++) acc[a] = v4f{0.f, 0.f, 0.f, 0.f};
+    float accb = 0.0f;
+    // halo offset of the lane's row or column in each product
+    int hoff[LAST || CI == 2 ? NA : 1];
+    bool hlive[LAST || CI == 2 ? NA : 1];
+    if constexpr (LAST || CI == 2) {
+#pragma unroll
+        for (int a = 0; a < NA; a++) {
+            const int e = 16 * a + r, t = LAST ? e : e >> 1;
+            hlive[a] = t < 27;
+            const int tt = LAST ? 26 - t : t;  // LAST: gout at the voxel minus the tap
+            hoff[a] = hlive[a] ? ((tt / 9 * kTSY + tt / 3 % 3) * kTSX + tt % 3) * HC + (LAST ? 0 : e & 1) : 0;
+        }
+    }
+    if constexpr (LAST)
+        for (int e = threadIdx.x; e < 27 * 16; e += 256) extra[e] = 0.0f;  // (a barrier follows in the loop)
+    const float* const hsrc = LAST ? gout : in;
+    const float* const bsrc = LAST ? in : gout;
+    const long ntiles = conv_tiles(B, Z, Y, X);
+    const long first = (long)blockIdx.x * per_block;
+    const long last = first + per_block < ntiles ? first + per_block : ntiles;
+    // The next block's values are loaded into registers while the current block is
+    // multiplied (HV + 4 vectors per thread), so its load latency is hidden.
+    constexpr int HV = HC == 16 ? 4 : 1, NR = (kTNV + 255) / 256;
+    constexpr int KU = NA > 4 ? 1 : 4;  // (27 products unrolled four times spill)
+    float4 nh[NR][HV], nc[4];
+    const int cv = threadIdx.x;  // the thread's voxel of the block
+    const auto fetch = [&](const ConvTile& T) {
+#pragma unroll
+        for (int j = 0; j < NR; j++) {
+            const int v = (int)threadIdx.x + 256 * j;
+            const long g = v < kTNV ? region_voxel(T, v, Z, Y, X) : -1;
+#pragma unroll
+            for (int s = 0; s < HV; s++) {
+                nh[j][s] = make_float4(0.f, 0.f, 0.f, 0.f);
+                if (g < 0) continue;
+                if constexpr (HC == 16) {
+                    nh[j][s] = ((const float4*)(hsrc + g * 16))[s];
+                } else {
+                    nh[j][s].x = hsrc[g * HC];
+                    if (HC == 2) nh[j][s].y = hsrc[g * HC + 1];
+                }
+            }
+        }
+        const int x = T.x0 + (cv & 15), y = T.y0 + (cv >> 4 & 3), z = T.z0 + (cv >> 6);
+        const bool inside = x < X && y < Y && z < Z;
+        const float4* src = (const float4*)(bsrc + ((((long)T.b * Z + z) * Y + y) * X + x) * 16);
+#pragma unroll
+        for (int s = 0; s < 4; s++) nc[s] = inside ? src[s] : make_float4(0.f, 0.f, 0.f, 0.f);
+    };
+    if (first < last) fetch(conv_tile(first, Z, Y, X));
+    for (long id = first; id < last; id++) {
+        const ConvTile T = conv_tile(id, Z, Y, X);
+        __syncthreads();  // the previous block's operands have been read
+#pragma unroll
+        for (int j = 0; j < NR; j++) {
+            const int v = (int)threadIdx.x + 256 * j;
+            if (v >= kTNV) break;
+            if constexpr (HC == 16) {
+#pragma unroll
+                for (int s = 0; s < HV; s++) ((float4*)(halo + v * 16))[s] = nh[j][s];
+            } else {
+                halo[v * HC] = nh[j][0].x;
+                if (HC == 2) halo[v * HC + 1] = nh[j][0].y;
+            }
+        }
+        if constexpr (LAST) {
+            const int x = T.x0 + (cv & 15), y = T.y0 + (cv >> 4 & 3), z = T.z0 + (cv >> 6);
+            if (x < X && y < Y && z < Z) {
+                float* const c16 = &nc[0].x;
+                const long g = (((long)T.b * Z + z) * Y + y) * X + x;
+                const float g0 = gout[g];
+                const bool gfin = fabsf(g0) < INFINITY;
+#pragma unroll
+                for (int i = 0; i < 16; i++) {
+                    const float a = c16[i];
+                    const bool fin = fabsf(a) < INFINITY;
+                    if (!fin) c16[i] = 0.0f;
+                    if (fin && gfin) continue;
+                    // (inf and NaN: the order of these additions does not matter)
+#pragma unroll 1
+                    for (int t = 0; t < 27; t++) {
+                        const int dz = t / 9 - 1, dy = t / 3 % 3 - 1, dx = t % 3 - 1;
+                        const auto in_volume = [&](int zz, int yy, int xx) {
+                            return zz >= 0 && zz < Z && yy >= 0 && yy < Y && xx >= 0 && xx < X;
+                        };
+                        if (!fin && in_volume(z - dz, y - dy, x - dx))
+                            atomicAdd(&extra[t * 16 + i],
+                                      a * gout[(((long)T.b * Z + z - dz) * Y + y - dy) * X + x - dx]);
+                        if (!gfin && !in_volume(z + dz, y + dy, x + dx)) atomicAdd(&extra[t * 16 + i], g0 * 0.0f);
+                    }
+                }
+            }
+        }
+#pragma unroll
+        for (int s = 0; s < 4; s++) ((float4*)(blk + cv * 16))[s] = nc[s];
+        __syncthreads();
+        if (id + 1 < last) fetch(conv_tile(id + 1, Z, Y, X));
+        // a voxel past the row's end: gout is zero there, and so is what it multiplies
+#pragma unroll 1
+        for (int p = 0; p < 4; p++) {
+            if (T.z0 + wave >= Z || T.y0 + p >= Y) break;
+            const float* h0 = halo + ((wave * kTSY + p) * kTSX + q) * HC;
+            const float* c0 = blk + ((wave * 4 + p) * 16 + q) * BC + r;
+#pragma unroll KU
+            for (int k4 = 0; k4 < 4; k4++, h0 += 4 * HC, c0 += 4 * BC) {
+                const float g = *c0;
+                const bool vox = T.x0 + 4 * k4 + q < X;
+                if constexpr (!LAST) accb += g;
+#pragma unroll
+                for (int a = 0; a < NA; a++) {
+                    if constexpr (LAST) {
+                        const float h = hlive[a] && vox ? h0[hoff[a]] : 0.0f;
+                        acc[a] = __builtin_amdgcn_mfma_f32_16x16x4f32(h, g, acc[a], 0, 0, 0);
+                        if (a == 0 && r == 13) accb += h;  // the centre tap's row: gout of the voxel itself
+                    } else if constexpr (CI == 2) {
+                        const float h = hlive[a] && vox ? h0[hoff[a]] : 0.0f;
+                        acc[a] = __builtin_amdgcn_mfma_f32_16x16x4f32(g, h, acc[a], 0, 0, 0);
+                    } else {
+                        const float h = h0[((a / 9 * kTSY + a / 3 % 3) * kTSX + a % 3) * 16 + r];
+                        acc[a] = __builtin_amdgcn_mfma_f32_16x16x4f32(g, vox ? h : 0.0f, acc[a], 0, 0, 0);
+                    }
+                }
+            }
+        }
+    }
+    // bias: the four voxel lanes of a channel, then the wavefronts with the weights
+    accb += __shfl_xor(accb, 16, 64);
+    accb += __shfl_xor(accb, 32, 64);
+    for (int wv = 0; wv < 4; wv++) {
+        __syncthreads();
+        if (wave != wv) continue;
+#pragma unroll
+        for (int a = 0; a < NA; a++)
+#pragma unroll
+            for (int e = 0; e < 4; e++) {
+                const int m = 4 * q + e;  // row
+                int at;
+                if constexpr (LAST) at = 16 * a + m < 27 ? (16 * a + m) * 16 + r : -1;
+                else if constexpr (CI == 2) at = 16 * a + r < 54 ? ((16 * a + r) / 2 * 16 + m) * 2 + (r & 1) : -1;
+                else at = (a * 16 + m) * 16 + r;
+                if (at >= 0) lds[at] = wv == 0 ? acc[a][e] : lds[at] + acc[a][e];
+            }
+        const bool mine = LAST ? lane == 13 : lane < 16;
+        if (mine) {
+            const int at = 27 * CI * CO + (LAST ? 0 : lane);
+            lds[at] = wv == 0 ? accb : lds[at] + accb;
+        }
+    }
+    __syncthreads();
+    for (int e = threadIdx.x; e < NE; e += 256) {
+        float v = lds[e];
+        if constexpr (LAST)
+            if (e < 27 * 16) v += extra[e];
+        part[(long)blockIdx.x * NE + e] = v;
+    }
+}
+
+// Second stage: gw/gb = sum over the partials, in a fixed order: 16 groups of
+// partials per weight, then the groups (one thread per weight over all 2048
+// partials took 517 us).
+constexpr int kSumGroups = 16;
+
+__global__ void __launch_bounds__(64 * kSumGroups) k_sum_parts(const float* __restrict__ part, int nparts, int ne, int nw,
+                                                               float* __restrict__ gw, float* __restrict__ gb)
+{
+    __shared__ float red[kSumGroups][64];
+    const int lane = threadIdx.x & 63, grp = threadIdx.x >> 6;
+    const int e = blockIdx.x * 64 + lane;
+    float s = 0.0f;
+    if (e < ne) {
+#pragma unroll 8
+        for (int p = grp; p < nparts; p += kSumGroups) s += part[(long)p * ne + e];
+    }
+    red[grp][lane] = s;
+    __syncthreads();
+    if (grp || e >= ne) return;
+    s = 0.0f;
+#pragma unroll
+    for (int g = 0; g < kSumGroups; g++) s += red[g][lane];
+    if (e < nw) gw[e] = s;
+    else gb[e - nw] = s;
+}
+
 // ------------------------------------------------------------------ solver glue
 // Features of a nested level's Gamma ((n+2)^3 points, channel-last, 2 channels):
 // f / ||f|| and r0 / ||f|| with r0 = f - lap(phi) of the interpolated guess.
@@ -621,10 +1201,50 @@ static bool conv_fwd_fixed(hipStream_t st, const TI* in, int cin, const uint16_t
     return true;
 }
 
+// The FP32 matrix-core kernels move a voxel's 16 channels in 16-byte accesses:
+// they take the network's layer shapes with 16-byte aligned arrays, the other
+// calls go to the thread-per-voxel kernels.
+static bool aligned16(const void* a, const void* b, const void* c)
+{
+    return (((uintptr_t)a | (uintptr_t)b | (uintptr_t)c) & 15) == 0;
+}
+
+// input channels ci, output channels co of the pass (for the data gradient the
+// layer's output and input channels); false: not one of the layers' shapes
+template <bool BWD>
+static bool train_conv(hipStream_t st, const float* in, int ci, const uint16_t* w, const float* bias, int co, ConvPost P,
+                       int B, int Z, int Y, int X, float* out)
+{
+    if (!aligned16(in, out, P.act)) return false;
+    const long tiles = conv_tiles(B, Z, Y, X);
+    const long per = (tiles + kTrainBlocks - 1) / kTrainBlocks;
+    const dim3 grid((unsigned)((tiles + per - 1) / per));
+    // the small-channel kernel holds few weights: more, shorter ranges
+    const long per1 = (tiles + 4 * kTrainBlocks - 1) / (4 * kTrainBlocks);
+    const dim3 grid1((unsigned)((tiles + per1 - 1) / per1));
+    // planes per workgroup of the few-channel kernel: 8 (1.25 times the input read)
+    // where that gives two workgroups per CU, else 2 for shorter chains
+    const long cols = (long)B * cdiv(X, kFewX) * cdiv(Y, kFewY);
+    const int zch = cols * cdiv(Z, 8) >= 512 ? 8 : 2;
+    const long few = cols * cdiv(Z, zch);
+    if (ci == 16 && co == 16)
+        hipLaunchKernelGGL(k_conv16_mfma_f32<BWD>, grid, dim3(256), 0, st, in, w, bias, B, Z, Y, X, P, out, per);
+    else if (ci == (BWD ? 1 : 2) && co == 16)
+        hipLaunchKernelGGL((k_conv_few_to16_mfma_f32<BWD ? 1 : 2, BWD>), grid1, dim3(256), 0, st, in, w, bias, B, Z, Y, X,
+                           P, out, per1);
+    else if (ci == 16 && co == (BWD ? 2 : 1) && few < (1L << 31) && ((uintptr_t)w & 3) == 0)
+        hipLaunchKernelGGL((k_conv16_to_few_f32<BWD ? 2 : 1, BWD>), dim3((unsigned)few), dim3(256), 0, st, in, w, bias, B,
+                           Z, Y, X, P, out, zch);
+    else
+        return false;
+    return true;
+}
+
 void net_conv_fwd_f32(hipStream_t st, const float* in, int cin, const uint16_t* w, const float* bias, int cout, int relu,
                       int B, int Z, int Y, int X, float* out)
 {
     long nv = (long)B * Z * Y * X;
+    if (train_conv<false>(st, in, cin, w, bias, cout, ConvPost{relu, 0, nullptr}, B, Z, Y, X, out)) return;
     if (conv_fwd_fixed(st, in, cin, w, bias, cout, relu, B, Z, Y, X, out)) return;
     hipLaunchKernelGGL((k_conv_fwd<float, float>), dim3(cdiv(nv, kNB)), dim3(kNB), 0, st, in, cin, w, bias, cout, relu, B,
                        Z, Y, X, out);
@@ -670,6 +1290,7 @@ void net_conv_bwd_data(hipStream_t st, const float* gout, int cout, const uint16
                        int X, float* gin)
 {
     long nv = (long)B * Z * Y * X;
+    if (train_conv<true>(st, gout, cout, w, nullptr, cin, ConvPost{0, 0, nullptr}, B, Z, Y, X, gin)) return;
     hipLaunchKernelGGL(k_conv_bwd_data, dim3(cdiv(nv, kNB)), dim3(kNB), 0, st, gout, cout, w, cin, B, Z, Y, X, gin);
 }
 
@@ -678,9 +1299,24 @@ size_t net_bwd_weight_workspace(int cin, int cout) { return (size_t)kNetParts * 
 void net_conv_bwd_weight(hipStream_t st, const float* in, int cin, const float* gout, int cout, int B, int Z, int Y,
                          int X, float* gw, float* gb, float* part)
 {
-    int ne = 27 * cin * cout + cout;
-    hipLaunchKernelGGL(k_conv_bwd_weight_part, dim3(kNetParts), dim3(kNB), 0, st, in, cin, gout, cout, B, Z, Y, X, part);
-    hipLaunchKernelGGL(k_sum_parts, dim3(cdiv(ne, kNB)), dim3(kNB), 0, st, part, kNetParts, ne, 27 * cin * cout, gw, gb);
+    const int ne = 27 * cin * cout + cout;
+    const long tiles = conv_tiles(B, Z, Y, X);
+    const long per = (tiles + kWgBlocks - 1) / kWgBlocks;
+    const dim3 grid((unsigned)((tiles + per - 1) / per));
+    int parts = (int)grid.x;
+    const bool wide = aligned16(cin == 16 ? in : nullptr, cout == 16 ? gout : nullptr, nullptr);
+    if (wide && cin == 16 && cout == 16)
+        hipLaunchKernelGGL((k_conv_bwd_weight_mfma<16, 16>), grid, dim3(256), 0, st, in, gout, B, Z, Y, X, part, per);
+    else if (wide && cin == 2 && cout == 16)
+        hipLaunchKernelGGL((k_conv_bwd_weight_mfma<2, 16>), grid, dim3(256), 0, st, in, gout, B, Z, Y, X, part, per);
+    else if (wide && cin == 16 && cout == 1)
+        hipLaunchKernelGGL((k_conv_bwd_weight_mfma<16, 1>), grid, dim3(256), 0, st, in, gout, B, Z, Y, X, part, per);
+    else {
+        parts = kNetParts;
+        hipLaunchKernelGGL(k_conv_bwd_weight_part, dim3(parts), dim3(kNB), 0, st, in, cin, gout, cout, B, Z, Y, X, part);
+    }
+    hipLaunchKernelGGL(k_sum_parts, dim3(cdiv(ne, 64)), dim3(64 * kSumGroups), 0, st, part, parts, ne, 27 * cin * cout, gw,
+                       gb);
 }
 
 void net_relu_bwd(hipStream_t st, const float* act, float* g, long n)
@@ -695,7 +1331,7 @@ void net_mse(hipStream_t st, const float* pred, const float* target, const float
 {
     int nb = cdiv(n, kNB);
     hipLaunchKernelGGL(k_mse, dim3(nb), dim3(kNB), 0, st, pred, target, mask, n, 1.0f / count, grad, part);
-    hipLaunchKernelGGL(k_sum, dim3(1), dim3(1), 0, st, part, nb, 1.0f / count, loss);
+    hipLaunchKernelGGL(k_sum, dim3(1), dim3(64), 0, st, part, nb, 1.0f / count, loss);
 }
 
 void net_adam(hipStream_t st, float* w, const float* g, float* m, float* v, long n, float lr, float b1, float b2,
@@ -778,6 +1414,31 @@ int np_net_conv3d_bwd_data(const float* gout, int cout, const unsigned short* w,
 {
     if (!gout || !w || !gin || !net_ok(cin, cout) || !dims_ok(batch, nz, ny, nx)) return NP_EINVAL;
     net_conv_bwd_data((hipStream_t)stream, gout, cout, w, cin, batch, nz, ny, nx, gin);
+    return hipGetLastError() == hipSuccess ? NP_OK : NP_EHIP;
+}
+
+int np_net_conv3d_fwd_round(const float* in, int cin, const unsigned short* w, const float* bias, int cout, int batch,
+                            int nz, int ny, int nx, float* out, void* stream)
+{
+    if (!in || !w || !bias || !out || !net_ok(cin, cout) || !dims_ok(batch, nz, ny, nx)) return NP_EINVAL;
+    const hipStream_t st = (hipStream_t)stream;
+    if (!train_conv<false>(st, in, cin, w, bias, cout, ConvPost{1, 1, nullptr}, batch, nz, ny, nx, out)) {
+        const long n = (long)batch * nz * ny * nx * cout;
+        net_conv_fwd_f32(st, in, cin, w, bias, cout, 1, batch, nz, ny, nx, out);
+        hipLaunchKernelGGL(k_round_bf16, dim3(cdiv(n, kNB)), dim3(kNB), 0, st, out, n);
+    }
+    return hipGetLastError() == hipSuccess ? NP_OK : NP_EHIP;
+}
+
+int np_net_conv3d_bwd_data_relu(const float* gout, int cout, const unsigned short* w, int cin, int batch, int nz, int ny,
+                                int nx, const float* act, float* gin, void* stream)
+{
+    if (!gout || !w || !act || !gin || !net_ok(cin, cout) || !dims_ok(batch, nz, ny, nx)) return NP_EINVAL;
+    const hipStream_t st = (hipStream_t)stream;
+    if (!train_conv<true>(st, gout, cout, w, nullptr, cin, ConvPost{0, 0, act}, batch, nz, ny, nx, gin)) {
+        net_conv_bwd_data(st, gout, cout, w, cin, batch, nz, ny, nx, gin);
+        net_relu_bwd(st, act, gin, (long)batch * nz * ny * nx * cin);
+    }
     return hipGetLastError() == hipSuccess ? NP_OK : NP_EHIP;
 }
 

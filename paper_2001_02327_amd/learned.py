@@ -100,16 +100,19 @@ class GuessNet:
         for k, (ci, co) in enumerate(LAYERS):
             w, b = self._w(k)
             out = torch.empty((B, Z, Y, X, co), dtype=torch.float32, device=self.dev)
-            _chk(_lib.lib().np_net_conv3d_fwd(_p(h), ci, _p(w), _p(b), co, int(k < len(LAYERS) - 1), B, Z, Y, X,
-                                              _p(out), ctypes.c_void_p(self.st)), "conv fwd")
             if bf16_acts and k < len(LAYERS) - 1:
-                self._round_bf16(out)
+                _chk(_lib.lib().np_net_conv3d_fwd_round(_p(h), ci, _p(w), _p(b), co, B, Z, Y, X, _p(out),
+                                                        ctypes.c_void_p(self.st)), "conv fwd")
+            else:
+                _chk(_lib.lib().np_net_conv3d_fwd(_p(h), ci, _p(w), _p(b), co, int(k < len(LAYERS) - 1), B, Z, Y, X,
+                                                  _p(out), ctypes.c_void_p(self.st)), "conv fwd")
             acts.append(out)
             h = out
         return acts
 
-    def backward(self, acts, gy):
-        """Accumulates parameter gradients into self.grad (overwrites); returns d loss / d input."""
+    def backward(self, acts, gy, input_grad=True):
+        """Accumulates parameter gradients into self.grad (overwrites); returns d loss / d input
+        (None without input_grad: a training step does not need it)."""
         B, Z, Y, X, _ = acts[0].shape
         g = gy
         for k in range(len(LAYERS) - 1, -1, -1):
@@ -121,13 +124,16 @@ class GuessNet:
             gb = self.grad[sb]
             _chk(_lib.lib().np_net_conv3d_bwd_weight(_p(acts[k]), ci, _p(g), co, B, Z, Y, X, _p(gw), _p(gb), _p(work),
                                                      ws, ctypes.c_void_p(self.st)), "conv bwd weight")
+            if k == 0 and not input_grad:
+                return None
             gin = torch.empty((B, Z, Y, X, ci), dtype=torch.float32, device=self.dev)
             w, _ = self._w(k)
-            _chk(_lib.lib().np_net_conv3d_bwd_data(_p(g), co, _p(w), ci, B, Z, Y, X, _p(gin), ctypes.c_void_p(self.st)),
-                 "conv bwd data")
             if k > 0:
-                _chk(_lib.lib().np_net_relu_bwd(_p(acts[k]), _p(gin), gin.numel(), ctypes.c_void_p(self.st)),
-                     "relu bwd")
+                _chk(_lib.lib().np_net_conv3d_bwd_data_relu(_p(g), co, _p(w), ci, B, Z, Y, X, _p(acts[k]), _p(gin),
+                                                            ctypes.c_void_p(self.st)), "conv bwd data")
+            else:
+                _chk(_lib.lib().np_net_conv3d_bwd_data(_p(g), co, _p(w), ci, B, Z, Y, X, _p(gin),
+                                                       ctypes.c_void_p(self.st)), "conv bwd data")
             g = gin
         return g
 
@@ -151,7 +157,7 @@ class GuessNet:
         """Error objective: mean (y - target)^2."""
         acts = self.forward(x)
         loss, gy = self.loss_grad(acts[-1], target, mask)
-        self.backward(acts, gy)
+        self.backward(acts, gy, input_grad=False)
         self.adam_step(lr)
         return loss
 
@@ -170,7 +176,7 @@ class GuessNet:
         loss, gl = self.loss_grad(ly, r)
         gy = torch.empty_like(gl)
         self._lap7(gl, gy)  # the stencil is its own adjoint
-        self.backward(acts, gy)
+        self.backward(acts, gy, input_grad=False)
         self.adam_step(lr)
         return loss
 
