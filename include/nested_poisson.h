@@ -88,8 +88,15 @@ extern "C" {
                                layer is its Dirichlet data); FP64, interpolated guess and the
                                residual stop rule only */
 
-/* How multigrid level 0 of a 3-D FP64 solve is smoothed (np_config.sweep).
- * NP_SWEEP_FULL: on level grids whose full sweep starts at least 4096
+/* How a 3-D solve runs its V-cycles (np_config.sweep).
+ * NP_SWEEP_FULL: with one or two pre- and post-smoothing sweeps (n_pre, n_post,
+ * coarse_post) as fused legs: one launch takes a multigrid level through its
+ * pre-smoothing sweeps, the residual and its restriction, another through the
+ * prolongation, the post-smoothing sweeps and on multigrid level 0 the stop
+ * test's residual norm.  FP64: every level above the coarse tail, from the
+ * level's potential into a second buffer (the handle's) and back; the defect
+ * correction: the coarse levels of up to 1024 blocks of 8^3 points.  With other
+ * sweep counts, FP64: on level grids whose full sweep starts at least 4096
  * wavefronts (cubic levels from about 420^3 cells; on smaller or thin grids
  * the half sweeps, which occupy the chip better, run), each
  * red-black sweep is one pass from the level's potential
@@ -106,7 +113,7 @@ extern "C" {
  * runs inside the restriction that follows it (Sec. 2.3 steps 2-5 in one pass;
  * needs N^0 = 2 N^1 along every axis and an odd N^1_x, elsewhere they run
  * apart).  On MI355X this pass is slower than the two kernels it replaces, so
- * it is not the default.  The iterates are the same in all four. */
+ * it is not the default.  NP_SWEEP_HALF and NP_SWEEP_FULL_ALL run no fused legs.  The iterates are the same in all four. */
 #define NP_SWEEP_FULL 0
 #define NP_SWEEP_HALF 1
 #define NP_SWEEP_FUSED 2
@@ -255,7 +262,8 @@ int nested_poisson_potential(np_solver* s, int level, double* phi_padded);
 /* Kernel-class timing.  With profiling enabled the handle records a HIP
  * event pair on its stream around each launch (or group of launches) of a
  * class and accumulates the elapsed device time; classes: */
-#define NP_KCLASS_SMOOTH 0   /* red-black half sweeps on the nested-level arrays (multigrid level 0) */
+#define NP_KCLASS_SMOOTH 0   /* red-black half sweeps on the nested-level arrays (multigrid level 0), or
+                              * its fused legs on grids too small for full sweeps */
 #define NP_KCLASS_RESTRICT 1 /* fused residual + restriction out of multigrid level 0 */
 #define NP_KCLASS_PROLONG 2  /* prolongation + correction into multigrid level 0 */
 #define NP_KCLASS_COARSE 3   /* all work on multigrid levels >= 1 (one interval per V-cycle) */
@@ -266,8 +274,9 @@ int nested_poisson_potential(np_solver* s, int level, double* phi_padded);
 #define NP_KCLASS_GUESS 8    /* learned initial guess (features, three convolutions, update) */
 #define NP_KCLASS_SEEDED 9   /* first black half sweep of a defect-correction step, which forms its red
                               * neighbours from the defect (and stores them with one pre-smoothing sweep) */
-#define NP_KCLASS_FULL 10    /* full red-black sweeps of multigrid level 0 (NP_SWEEP_FULL) */
-#define NP_KCLASS_FULL_RES 11 /* the full sweep that also completes the stop test's residual norm */
+#define NP_KCLASS_FULL 10    /* full red-black sweeps of multigrid level 0, or on grids of their size the
+                              * fused leg down */
+#define NP_KCLASS_FULL_RES 11 /* the full sweep or fused leg up that completes the stop test's residual norm */
 #define NP_KCLASS_DC_SCALE 12 /* first scaled defect of a level from its starting residual */
 #define NP_KCLASS_BLACK_RESTRICT 13 /* last pre-smoothing black half sweep of multigrid level 0 fused with
                                      * the residual restriction (NP_SWEEP_FUSED, 2-byte storage) */

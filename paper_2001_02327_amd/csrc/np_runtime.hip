@@ -299,6 +299,9 @@ struct np_solver {
     // multigrid scratch for L >= 1, shared by the levels (sized for the largest)
     double* mg_u[NP_MAX_MG] = {};
     double* mg_f[NP_MAX_MG] = {};
+    // results of the fused up legs on levels L >= 1 (use_legs)
+    double* mg_r[NP_MAX_MG] = {};
+    float* mg_r32[NP_MAX_MG] = {};
     double* force_scratch = nullptr;  // FORCE_DELTA stop rule
     unsigned long long* d_bits = nullptr;  // device reduction slots
     unsigned long long* h_bits = nullptr;  // pinned host copy
@@ -465,12 +468,13 @@ struct MGView {
     int nmg;
     T* u[NP_MAX_MG];
     T* f[NP_MAX_MG];
+    T* r[NP_MAX_MG];  // with fused legs: what the up leg leaves on the level
     SGrid g[NP_MAX_MG];
     double h[NP_MAX_MG];
 };
 
 template <typename T>
-MGView<T> mg_view(const np_solver* s, int l, T* const* mu, T* const* mf)
+MGView<T> mg_view(const np_solver* s, int l, T* const* mu, T* const* mf, T* const* mr)
 {
     MGView<T> v;
     v.nmg = s->plan.nmg[l];
@@ -478,6 +482,7 @@ MGView<T> mg_view(const np_solver* s, int l, T* const* mu, T* const* mf)
     for (int L = 0; L < v.nmg; L++) {
         v.u[L] = L == 0 ? nullptr : mu[L];
         v.f[L] = L == 0 ? nullptr : mf[L];
+        v.r[L] = L == 0 ? nullptr : mr[L];
         v.g[L] = L == 0 ? s->lg[l] : mg_grid(s, l, L);
         v.h[L] = std::ldexp(dx, L);
     }
@@ -511,6 +516,60 @@ int tail_level(const np_solver* s, int l, size_t esz)
     return 0;
 }
 
+// post-smoothing sweeps below multigrid level 0
+int coarse_npost(const np_config& c) { return c.coarse_post >= 0 ? c.coarse_post : c.n_post; }
+
+// Fused legs (one launch down and one up per multigrid level, np_tile.hip and np_stream.hip) hold one or
+// two sweeps; other counts, 2-D and the sweep modes that name another form run the
+// per-pass kernels.
+bool legs_cfg(const np_config& c)
+{
+    return (c.sweep == NP_SWEEP_FULL || c.sweep == NP_SWEEP_FUSED) && level_legs_fit(c.dim, c.n_pre, c.n_post) &&
+           level_legs_fit(c.dim, c.n_pre, coarse_npost(c));
+}
+
+// First multigrid level of nested level l that runs as fused legs, as do the levels
+// from there to the coarse tail; nmg if none does.  FP64: every level (level 0
+// too), the mixed precisions: the coarse levels that the block form serves (their
+// larger levels are as fast or faster per pass, and level 0 is stored in 16 bits).
+int legs_level(const np_solver* s, int l)
+{
+    const int nmg = s->plan.nmg[l];
+    if (!legs_cfg(s->cfg)) return nmg;
+    const bool fp64 = s->cfg.precision == NP_PREC_FP64;
+    const int Lt = tail_level(s, l, fp64 ? sizeof(double) : sizeof(float));
+    if (Lt == 0) return nmg;
+    // (the streamed form addresses a plane of a colour by 31 bits)
+    if (fp64) return s->lg[l].ps * sizeof(double) < (1ULL << 31) ? 0 : nmg;
+    for (int L = 1; L < Lt; L++)
+        if (level_tile(mg_grid(s, l, L))) return L;
+    return nmg;
+}
+
+// Levels 1 to pass_end - 1 run the per-pass kernels, and the restriction into each of
+// them does its first red half sweep.
+int pass_end(const np_solver* s, int l, size_t esz)
+{
+    const int Lt = tail_level(s, l, esz), end = Lt ? Lt : s->plan.nmg[l];
+    return std::min(end, std::max(1, legs_level(s, l)));
+}
+
+bool use_legs(const np_solver* s, int l) { return legs_level(s, l) == 0; }
+
+// where level L >= 1 leaves its result
+template <typename T>
+const T* mg_result(const np_solver* s, int l, const MGView<T>& v, int L)
+{
+    return L >= legs_level(s, l) && L < tail_level(s, l, sizeof(T)) ? v.r[L] : v.u[L];
+}
+
+template <typename T>
+LevelLeg leg_of(const np_solver* s, int l, const MGView<T>& v, int L, int rev)
+{
+    const double h2 = v.h[L] * v.h[L];
+    return LevelLeg{v.g[L], v.g[L + 1], h2, 1.0 / h2, L > 0 ? rule_of(s, l, L) : Rule3{}, rule_of(s, l, L + 1), rev};
+}
+
 // Everything a V-cycle does on levels L >= 1 (Sec. 2.3 steps 6-13 below the
 // finest multigrid level): from the pre-smoothing of level 1 down to the
 // coarsest level and back up to the post-smoothing of level 1, which precedes
@@ -523,7 +582,7 @@ void coarse_part(const np_solver* s, int l, const MGView<T>& v, hipStream_t st)
     const np_config& c = s->cfg;
     const int d = c.dim;
     const int Lt = tail_level(s, l, sizeof(T));
-    const int npost = c.coarse_post >= 0 ? c.coarse_post : c.n_post;  // post-smoothing below level 0
+    const int npost = coarse_npost(c);
     auto tail = [&](int L0) {
         const int nlev = s->plan.nmg[l] - L0;
         double h[kTailMaxLevels];
@@ -539,26 +598,26 @@ void coarse_part(const np_solver* s, int l, const MGView<T>& v, hipStream_t st)
         tail(1);
         return;
     }
-    // the restriction into a level that the tail does not take has already done
-    // that level's first red half sweep (seeded correction)
-    for (int it = 0; it < c.n_pre; it++) coarse_sweep(s, l, v, 1, st, it == 0 ? 1 : 0);
-    int L = 1;
-    while (L + 1 < s->plan.nmg[l]) {
-        const bool seed = c.n_pre > 0 && L + 1 != Lt;
+    // the restriction into a level that neither the tail nor the legs take has already
+    // done that level's first red half sweep (seeded correction)
+    const int Lp = pass_end(s, l, sizeof(T));
+    const int Lend = Lt ? Lt : s->plan.nmg[l] - 1;
+    for (int L = 1; L < Lp; L++) {
+        for (int it = 0; it < c.n_pre; it++) coarse_sweep(s, l, v, L, st, it == 0 ? 1 : 0);
+        if (L == Lend) break;
+        const bool seed = c.n_pre > 0 && L + 1 < Lp;
         launch_resid_restrict<T, T>(d, st, v.g[L], v.u[L], v.f[L], 1.0 / (v.h[L] * v.h[L]), 1.0, v.g[L + 1], v.f[L + 1],
                                     v.u[L + 1], 1, rule_of(s, l, L), seed ? v.h[L + 1] * v.h[L + 1] : 0.0);
-        if (L + 1 == Lt) {
-            tail(Lt);
-            L = Lt;
-            break;
-        }
-        for (int it = 0; it < c.n_pre; it++) coarse_sweep(s, l, v, L + 1, st, it == 0 ? 1 : 0);
-        L++;
     }
-    while (L > 1) {
-        launch_prolong_add<T, T>(d, st, v.g[L], v.u[L], v.g[L - 1], v.u[L - 1], 0, rule_of(s, l, L));
+    for (int L = Lp; L < Lt; L++)
+        launch_level_down<T>(st, leg_of(s, l, v, L, 0), c.n_pre, true, v.u[L], v.f[L], v.u[L], v.f[L + 1]);
+    if (Lt) tail(Lt);
+    for (int L = Lt - 1; L >= Lp; L--)
+        launch_level_up<T>(st, leg_of(s, l, v, L, 0), npost, true, v.u[L], v.u[L], v.f[L], v.r[L],
+                           mg_result(s, l, v, L + 1), nullptr);
+    for (int L = std::min(Lp, Lend); L > 1; L--) {
+        launch_prolong_add<T, T>(d, st, v.g[L], mg_result(s, l, v, L), v.g[L - 1], v.u[L - 1], 0, rule_of(s, l, L));
         for (int it = 0; it < npost; it++) coarse_sweep(s, l, v, L - 1, st);
-        L--;
     }
 }
 
@@ -643,9 +702,9 @@ int vcycle_t(np_solver* s, int l, T0* u0, const T0* f0, double h2_0, double inv_
         if (nsweep) prof_end(s, nsweep);
     };
     smooth0(c.n_pre, fuse);
-    // the restriction does multigrid level 1's first red half sweep unless the
-    // coarse tail starts at level 1 (coarse_part then skips it)
-    const bool seed1 = c.n_pre > 0 && tail_level(s, l, sizeof(TC)) != 1;
+    // the restriction does multigrid level 1's first red half sweep unless the coarse
+    // tail or the fused legs start at level 1 (coarse_part then skips it)
+    const bool seed1 = c.n_pre > 0 && pass_end(s, l, sizeof(TC)) > 1;
     if constexpr (std::is_same<T0, __half>::value && std::is_same<TC, float>::value) {
         if (fuse) {
             prof_begin(s, NP_KCLASS_BLACK_RESTRICT);
@@ -667,36 +726,72 @@ int vcycle_t(np_solver* s, int l, T0* u0, const T0* f0, double h2_0, double inv_
     prof_begin(s, NP_KCLASS_PROLONG);
     // on level 0 (fixed ghost layer) the red corrections are dead when a
     // post-smoothing red half sweep follows: it reads only black points
-    launch_prolong_add<TC, T0>(d, st, v.g[1], v.u[1], v.g[0], u0, c.n_post > 0, rule_of(s, l, 1));
+    launch_prolong_add<TC, T0>(d, st, v.g[1], mg_result(s, l, v, 1), v.g[0], u0, c.n_post > 0, rule_of(s, l, 1));
     prof_end(s);
     smooth0(c.n_post, false);
+    return NP_OK;
+}
+
+// Where full sweeps of multigrid level 0 pay.  A full sweep's thread takes a pair of columns times five rows times a chunk
+// of 16 planes and needs registers for one wave per SIMD, so a launch of fewer
+// than about four waves per SIMD leaves the chip partly idle: the paper's
+// 3 x 128^3 stack took 15.2 ms per solve with full sweeps and 8.6 ms with half
+// sweeps, eight 64^3 patches one after another 46.7 and 27.3 ms, a 512 x 512 x
+// 64 slab (1080 waves) 150 us per full sweep against two half sweeps of 48 us;
+// 2 x 256^3 (952 waves) alike, 512^3 (7128 waves) faster with full sweeps.  The
+// profile counts the fused legs of such levels with the full sweeps, those of
+// smaller ones with the half sweeps.
+constexpr long kFullSweepMinWaves = 4096;
+
+// The FP64 V-cycle as fused legs: u0 to the spare potential buffer and back to u0, whose
+// ghost layer both legs use.  The max norm of the result's residual goes to bits (zeroed
+// here; one slot per batch member).
+int vcycle_legs(np_solver* s, int l, double* u0, const double* f0, const MGView<double>& v, unsigned long long* bits)
+{
+    const np_config& c = s->cfg;
+    hipStream_t st = s->stream;
+    const bool big = full_sweep_waves(v.g[0]) >= kFullSweepMinWaves;
+    prof_begin(s, big ? NP_KCLASS_FULL : NP_KCLASS_SMOOTH);
+    launch_level_down<double>(st, leg_of(s, l, v, 0, 0), c.n_pre, false, u0, f0, s->phi_alt, v.f[1]);
+    prof_end(s);
+    prof_begin(s, NP_KCLASS_COARSE);
+    int rc = run_coarse(s, l, v, s->coarse_exec);
+    prof_end(s);
+    if (rc) return rc;
+    launch_set_u64(st, bits, v.g[0].nb, 0ULL);
+    prof_begin(s, big ? NP_KCLASS_FULL_RES : NP_KCLASS_SMOOTH);
+    launch_level_up<double>(st, leg_of(s, l, v, 0, 1), c.n_post, false, s->phi_alt, u0, f0, u0, mg_result(s, l, v, 1), bits);
+    prof_end(s);
+    return NP_OK;
+}
+
+// One such cycle and the residual norm of its result (host-synchronous).
+int vcycle_legs_sync(np_solver* s, int l, double* out)
+{
+    int rc = vcycle_legs(s, l, s->phi[l], s->f[l], mg_view<double>(s, l, s->mg_u, s->mg_f, s->mg_r), s->d_bits);
+    if (rc) return rc;
+    HIPCHK(s, hipGetLastError());
+    HIPCHK(s, hipMemcpyAsync(s->h_bits, s->d_bits, sizeof(unsigned long long), hipMemcpyDeviceToHost, s->stream));
+    HIPCHK(s, hipStreamSynchronize(s->stream));
+    *out = bits_to_double(s->h_bits[0]);
     return NP_OK;
 }
 
 // Plain FP64 V-cycle on the level's potential.
 int vcycle(np_solver* s, int l)
 {
-    MGView<double> v = mg_view<double>(s, l, s->mg_u, s->mg_f);
+    MGView<double> v = mg_view<double>(s, l, s->mg_u, s->mg_f, s->mg_r);
     double h = v.h[0];
     return vcycle_t<double, double>(s, l, s->phi[l], s->f[l], h * h, 1.0 / (h * h), 1.0, v, s->coarse_exec);
 }
 
 // Whether nested level l (solved on its own) runs full sweeps on multigrid level 0.
-// A full sweep's thread takes a pair of columns times five rows times a chunk
-// of 16 planes and needs registers for one wave per SIMD, so a launch of fewer
-// than about four waves per SIMD leaves the chip partly idle: the paper's
-// 3 x 128^3 stack took 15.2 ms per solve with full sweeps and 8.6 ms with half
-// sweeps, eight 64^3 patches one after another 46.7 and 27.3 ms, a 512 x 512 x
-// 64 slab (1080 waves) 150 us per full sweep against two half sweeps of 48 us;
-// 2 x 256^3 (952 waves) alike, 512^3 (7128 waves) faster with full sweeps.
-constexpr long kFullSweepMinWaves = 4096;
-
 bool full_sweeps(const np_solver* s, int l)
 {
     const np_config& c = s->cfg;
     const SGrid& g = s->lg[l];
     const bool big = full_sweep_waves(g) >= kFullSweepMinWaves;
-    return c.dim == 3 && c.precision == NP_PREC_FP64 && c.sweep != NP_SWEEP_HALF &&
+    return c.dim == 3 && c.precision == NP_PREC_FP64 && c.sweep != NP_SWEEP_HALF && !use_legs(s, l) &&
            (big || c.sweep == NP_SWEEP_FULL_ALL) && s->phi_alt && c.n_pre >= 1 && c.n_post >= 1 &&
            !(l > 0 && c.buffer == NP_BUFFER_INTERP);
 }
@@ -723,7 +818,7 @@ int vcycle_full(np_solver* s, int l, bool first_done)
     const np_config& c = s->cfg;
     const int d = c.dim;
     hipStream_t st = s->stream;
-    MGView<double> v = mg_view<double>(s, l, s->mg_u, s->mg_f);
+    MGView<double> v = mg_view<double>(s, l, s->mg_u, s->mg_f, s->mg_r);
     const double h = v.h[0];
     int it = 0;
     if (first_done) {
@@ -737,7 +832,7 @@ int vcycle_full(np_solver* s, int l, bool first_done)
         for (; it < c.n_pre; it++) full_sweep(s, l, 0);
         prof_end(s, n);
     }
-    const bool seed1 = tail_level(s, l, sizeof(double)) != 1;
+    const bool seed1 = pass_end(s, l, sizeof(double)) > 1;
     prof_begin(s, NP_KCLASS_RESTRICT);
     launch_resid_restrict<double, double>(d, st, v.g[0], s->phi[l], s->f[l], 1.0 / (h * h), 1.0, v.g[1], v.f[1],
                                           v.u[1], 0, Rule3{}, seed1 ? v.h[1] * v.h[1] : 0.0);
@@ -793,7 +888,7 @@ bool dc_seed_black(const np_solver* s, int l)
 template <typename TL>
 int vcycle_lo(np_solver* s, int l, bool red_done)
 {
-    MGView<float> v = mg_view<float>(s, l, s->mg_u32, s->mg_f32);
+    MGView<float> v = mg_view<float>(s, l, s->mg_u32, s->mg_f32, s->mg_r32);
     double h = v.h[0];
     return vcycle_t<TL, float>(s, l, (TL*)s->e_lo, (const TL*)s->r_lo, 1.0, 1.0, 1.0 / (h * h), v, s->coarse_exec32,
                                red_done, red_done && dc_seed_black(s, l));
@@ -1097,15 +1192,19 @@ int solve_batch(np_solver* s, const PatchGroup& G, const double* const* rho, dou
     }
     // the batch's grids: level 0 and the multigrid levels, one row per member
     const double dx = level_dx(&c, m0);
-    MGView<double> v = mg_view<double>(s, m0, s->mg_u, s->mg_f);
+    MGView<double> v = mg_view<double>(s, m0, s->mg_u, s->mg_f, s->mg_r);
     for (int L = 0; L < v.nmg; L++) v.g[L] = batched(v.g[L], n, s->d_act);
     const SGrid g0 = v.g[0];
-    // stop-test norms of the members still iterating into their slots
-    auto norms = [&](bool first) -> int {
-        launch_set_u64(stm, slots, n, 0ULL);
-        prof_begin(s, NP_KCLASS_NORM);
-        launch_norm(d, stm, g0, s->phi[m0], s->f[m0], 1.0 / (dx * dx), 0, slots);
-        prof_end(s);
+    const bool legs = use_legs(s, m0) && s->phi_alt;
+    // stop-test norms of the members still iterating into their slots (with fused
+    // legs the cycle has put them there), to the host
+    auto norms = [&](bool first, bool launch) -> int {
+        if (launch) {
+            launch_set_u64(stm, slots, n, 0ULL);
+            prof_begin(s, NP_KCLASS_NORM);
+            launch_norm(d, stm, g0, s->phi[m0], s->f[m0], 1.0 / (dx * dx), 0, slots);
+            prof_end(s);
+        }
         HIPCHK(s, hipGetLastError());
         HIPCHK(s, hipMemcpyAsync(s->h_bits + kBatchSlot, slots, n * sizeof(unsigned long long), hipMemcpyDeviceToHost,
                                  stm));
@@ -1141,7 +1240,7 @@ int solve_batch(np_solver* s, const PatchGroup& G, const double* const* rho, dou
     };
     for (int b = 0; b < n; b++) s->h_act[b] = 1;
     HIPCHK(s, hipMemcpyAsync(s->d_act, s->h_act, n * sizeof(int), hipMemcpyHostToDevice, stm));
-    int rc = norms(true);
+    int rc = norms(true, true);
     if (rc) return rc;
     for (int b = 0; b < n; b++) {
         r0[b] = r[b];
@@ -1151,12 +1250,15 @@ int solve_batch(np_solver* s, const PatchGroup& G, const double* const* rho, dou
     bool any = update();
     while (any) {
         HIPCHK(s, hipMemcpyAsync(s->d_act, s->h_act, n * sizeof(int), hipMemcpyHostToDevice, stm));
-        rc = vcycle_t<double, double>(s, m0, s->phi[m0], s->f[m0], dx * dx, 1.0 / (dx * dx), 1.0, v,
-                                      s->coarse_exec);
+        if (legs)
+            rc = vcycle_legs(s, m0, s->phi[m0], s->f[m0], v, slots);
+        else
+            rc = vcycle_t<double, double>(s, m0, s->phi[m0], s->f[m0], dx * dx, 1.0 / (dx * dx), 1.0, v,
+                                          s->coarse_exec);
         if (rc) return rc;
         HIPCHK(s, hipGetLastError());
         for (int b = 0; b < n; b++) q[b] += s->h_act[b];
-        rc = norms(false);
+        rc = norms(false, !legs);
         if (rc) return rc;
         for (int b = 0; b < n; b++)
             if (s->h_act[b]) s->hist[G.member[b]].push_back(scale[b] > 0 ? r[b] / scale[b] : r[b]);
@@ -1215,6 +1317,10 @@ void free_all(np_solver* s)
     for (int L = 0; L < NP_MAX_MG; L++) {
         if (s->mg_u[L]) (void)hipFree(s->mg_u[L]);
         if (s->mg_f[L]) (void)hipFree(s->mg_f[L]);
+        if (s->mg_r[L]) (void)hipFree(s->mg_r[L]);
+        if (s->mg_r32[L]) (void)hipFree(s->mg_r32[L]);
+        s->mg_r[L] = nullptr;
+        s->mg_r32[L] = nullptr;
         if (s->mg_u32[L]) (void)hipFree(s->mg_u32[L]);
         if (s->mg_f32[L]) (void)hipFree(s->mg_f32[L]);
         s->mg_u[L] = s->mg_f[L] = nullptr;
@@ -1349,6 +1455,8 @@ int nested_poisson_create(const np_config* cfg, void* hip_stream, np_solver** ou
     // multigrid scratch: per level L the largest grid over the nested levels,
     // FP64 for the plain solve, FP32 for the defect correction's inner cycles
     const bool dc = cfg->precision != NP_PREC_FP64;
+    int legs_min = NP_MAX_MG;  // first level with fused legs
+    for (int gi = 0; gi < s->ngroups; gi++) legs_min = std::min(legs_min, legs_level(s, s->groups[gi].member[0]));
     for (int L = 1; L < NP_MAX_MG && rc == NP_OK; L++) {
         size_t best = 0;
         for (int gi = 0; gi < s->ngroups; gi++) {
@@ -1362,9 +1470,11 @@ int nested_poisson_create(const np_config* cfg, void* hip_stream, np_solver** ou
         if (dc) {
             rc = alloc_dev(s, (void**)&s->mg_u32[L], best * sizeof(float));
             if (rc == NP_OK) rc = alloc_dev(s, (void**)&s->mg_f32[L], best * sizeof(float));
+            if (rc == NP_OK && L >= legs_min) rc = alloc_dev(s, (void**)&s->mg_r32[L], best * sizeof(float));
         } else {
             rc = alloc_dev(s, (void**)&s->mg_u[L], best * sizeof(double));
             if (rc == NP_OK) rc = alloc_dev(s, (void**)&s->mg_f[L], best * sizeof(double));
+            if (rc == NP_OK && L >= legs_min) rc = alloc_dev(s, (void**)&s->mg_r[L], best * sizeof(double));
         }
     }
     if (rc == NP_OK && cfg->buffer == NP_BUFFER_INTERP && cfg->nlevels > 1) {
@@ -1390,10 +1500,10 @@ int nested_poisson_create(const np_config* cfg, void* hip_stream, np_solver** ou
         if (rc == NP_OK) rc = alloc_dev(s, (void**)&s->phi_alt, s->alt_cap);
     }
     if (rc == NP_OK && !dc && d == 3 && cfg->sweep != NP_SWEEP_HALF && cfg->n_pre >= 1 && cfg->n_post >= 1) {
-        // the second potential buffer of the full sweeps
+        // the second potential buffer of the fused legs (a batch's members side by
+        // side) and of the full sweeps
         size_t best = 0;
-        for (int l = 0; l < cfg->nlevels; l++)
-            if (2 * s->lg[l].cs > best) best = 2 * s->lg[l].cs;
+        for (int gi = 0; gi < s->ngroups; gi++) best = std::max(best, s->groups[gi].n * 2 * s->lg[s->groups[gi].member[0]].cs);
         s->alt_cap = best * sizeof(double);
         rc = alloc_dev(s, (void**)&s->phi_alt, s->alt_cap);
     }
@@ -1585,6 +1695,7 @@ int nested_poisson_solve(np_solver* s, const double* const* rho, const double* p
         }
         // full sweeps write the active points of the spare buffer: the same
         const bool fs = !dc && full_sweeps(s, l);
+        const bool legs = !dc && use_legs(s, l) && s->phi_alt;
         bool first_done = false;  // the next cycle's first pre-smoothing sweep has run
         if (fs) launch_copy_ghosts(c.dim, s->stream, s->lg[l], s->phi[l], s->phi_alt);
         for (;;) {
@@ -1620,6 +1731,10 @@ int nested_poisson_solve(np_solver* s, const double* const* rho, const double* p
                     const double m = std::pow(r / rprev, 1.0 / k);
                     rho = m < 0.02 ? 0.02 : (m > 0.95 ? 0.95 : m);
                 }
+            } else if (legs) {
+                rc = vcycle_legs_sync(s, l, &r);
+                if (rc) return rc;
+                q++;
             } else if (fs) {
                 rc = vcycle_full(s, l, first_done);
                 if (rc) return rc;

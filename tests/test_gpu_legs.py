@@ -1,0 +1,84 @@
+"""Fused V-cycle legs (the default sweep mode, 3-D, one or two pre- and
+post-smoothing sweeps) against the per-pass kernels (sweep="half").
+
+One launch takes a multigrid level down or up: blocks of the level in LDS on
+levels of at most 1024 blocks of 8 x 8 x 8 points (batch members included), in
+FP64 columns streamed through it on the larger ones; in the mixed precisions the
+coarse levels that fit the block form.  Every operation and its order are those of
+the per-pass kernels, so potentials, forces, cycle counts and residual histories
+are compared for equality, bit for bit.
+"""
+import numpy as np
+import pytest
+import torch
+
+from paper_2001_02327_amd import workloads as W
+from paper_2001_02327_amd.solver import NestedPoissonSolver
+
+pytestmark = pytest.mark.gpu
+
+
+def _solve(wl, **kw):
+    rho, po = W.make_inputs(wl.geom, wl.prob, device="cuda")
+    s = NestedPoissonSolver(wl.geom, **kw)
+    st = s.solve(rho, po, allow_notconv=True)
+    out = [s.potential(l) for l in range(wl.geom.nlevels)]
+    for l in range(wl.geom.nlevels):
+        out += list(s.forces(l))
+    out = [a.cpu().numpy() for a in out]
+    hist = [s.history(l) for l in range(wl.geom.nlevels)]
+    s.close()
+    return out, hist, list(st["cycles"])
+
+
+def _same(wl, **kw):
+    a, b = _solve(wl, **kw), _solve(wl, sweep="half", **kw)
+    assert a[2] == b[2] and a[1] == b[1]
+    for x, y in zip(a[0], b[0]):
+        assert np.isfinite(x).all()
+        assert np.array_equal(x, y)
+
+
+def _one(*n):
+    g = W.Geometry(dim=3, n=[tuple(n)], off=[(0, 0, 0)], lo0=(0.0, 0.0, 0.0), dx0=1.0 / 32)
+    return W.Workload("one%s" % (n,), g, W.Plummer([(1.0, 0.3, tuple(0.4 * a / 32 for a in n))]))
+
+
+# single levels: a column and block exactly filled, one point more and one less in
+# each direction; flat and long ones; both sides of the limit between the forms
+SIZES = [(8, 8, 8), (10, 8, 14), (16, 18, 20), (40, 38, 36), (72, 68, 34), (80, 80, 80), (88, 88, 72), (108, 102, 90),
+         (110, 104, 92), (106, 100, 110), (120, 114, 80), (122, 116, 82), (118, 112, 78), (200, 200, 12), (24, 200, 180),
+         (40, 44, 400)]
+
+
+@pytest.mark.parametrize("n", SIZES, ids=lambda n: "x".join(map(str, n)))
+@pytest.mark.parametrize("pre,post", [(2, 1), (1, 2)])
+def test_sizes_fp64(n, pre, post):
+    _same(_one(*n), n_pre=pre, n_post=post, max_cycles=8)
+
+
+@pytest.mark.parametrize("kw", [dict(), dict(n_pre=1), dict(n_post=2), dict(n_pre=1, coarse_post=2),
+                                dict(buffer="interp"), dict(stop_rule="force_delta")],
+                         ids=lambda kw: "-".join("%s=%s" % a for a in kw.items()) or "default")
+@pytest.mark.parametrize("wl", [W.c2_plummer(16), W.c3_plummer_offset(96), W.box_plummer_3d(4)], ids=lambda w: w.name)
+def test_nested_fp64(wl, kw):
+    _same(wl, **kw)
+
+
+@pytest.mark.parametrize("n", [16, 32, 64])
+def test_batches(n):
+    # members side by side in one launch: the block form for 16, streamed columns for 64
+    _same(W.many_patches_3d(n, 2, 8, depth2=True))
+
+
+@pytest.mark.parametrize("precision", ["fp32_dc", "fp16s_dc"])
+@pytest.mark.parametrize("kw", [dict(), dict(n_pre=1, coarse_post=2), dict(n_pre=1, n_post=2)],
+                         ids=lambda kw: "-".join("%s=%s" % a for a in kw.items()) or "default")
+@pytest.mark.parametrize("wl", [W.c2_plummer(32), W.c2_plummer(132, 1), W.box_plummer_3d(4)], ids=lambda w: w.name)
+def test_coarse_levels_mixed(wl, kw, precision):
+    _same(wl, precision=precision, inner_cycles="adaptive", **kw)
+
+
+def test_large():
+    # 260^3: streamed legs on the three largest levels, blocks below
+    _same(W.c2_plummer(260, 1))
