@@ -280,6 +280,15 @@ __device__ __forceinline__ void rule_pair(int q, int N, C self, C& lo, C& hi, co
     if (q == N) hi = gr.xn1[ax] ? -lo : gr.coef[ax] * self;
 }
 
+// Barrier that orders LDS only: __syncthreads also waits for every global load in
+// flight.
+__device__ __forceinline__ void lds_barrier()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 // fused multiply-add in the type of its operands
 __device__ __forceinline__ double fma_t(double a, double b, double c) { return __fma_rn(a, b, c); }
 __device__ __forceinline__ float fma_t(float a, float b, float c) { return __fmaf_rn(a, b, c); }

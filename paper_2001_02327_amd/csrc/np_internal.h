@@ -168,7 +168,10 @@ void launch_prolong_add(int dim, hipStream_t st, SGrid gc, const TC* ec, SGrid g
 // (coarse_tail_lds_bytes).
 constexpr int kTailMaxLevels = 8;
 constexpr size_t kTailLdsBytes = 64 * 1024;
+constexpr int kTailThreads = 1024;
 size_t coarse_tail_lds_bytes(int dim, const int (*N)[3], int nlev, size_t esz);
+// a thread each of the tail: both colours' points of a place in a row of a level of N points
+int coarse_tail_slots(int dim, const int* N);
 template <typename T>
 int launch_coarse_tail(int dim, hipStream_t st, int nlev, const int (*N)[3], const double* h, const Rule3* rule,
                        int n_pre, int n_post, SGrid g0, const T* f0, T* u0);

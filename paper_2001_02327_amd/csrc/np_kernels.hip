@@ -2634,264 +2634,6 @@ __global__ void __launch_bounds__(kBlock) k_prolong3_pair(const TC* __restrict__
     }
 }
 
-// ------------------------------------------------------------------ coarse tail
-// The smallest multigrid levels of a V-cycle, from a level Lt whose data and
-// that of every coarser level fit in LDS together, down to the one-point level
-// and back, in one workgroup: as separate launches their cost would be launch
-// latency, not work.  Same operations in the same order and arithmetic as the
-// per-level kernels: n_pre sweeps on Lt; per level down, the restriction
-// (correction cleared) and n_pre sweeps; per level up, the prolongation and
-// n_post sweeps.  Each level lives in LDS in natural order (x fastest) on its
-// box of N_a + 2 points per axis; the ghost slots are never written, the rule
-// supplies their values.
-constexpr int kTailThreads = 1024;
-
-template <typename C>
-struct TailParams {
-    int nlev;                   // levels Lt .. Lt + nlev - 1 (the last has one point along some axis)
-    int N[kTailMaxLevels][3];   // active points per axis
-    int off[kTailMaxLevels];    // LDS element offset of level a's u; its f follows one box later
-    C h2[kTailMaxLevels];       // smoother factor (2^L h)^2
-    C inv_h2[kTailMaxLevels];   // residual factor 1 / (2^L h)^2
-    GRule<C> gr[kTailMaxLevels];
-    float rN[kTailMaxLevels][3];  // 1 / N per axis (index decoding)
-    float rS[kTailMaxLevels];     // 1 / ((N_x + 1) / 2), the slots of one colour per row
-    int n_pre, n_post;
-};
-
-// points of a level's box in LDS ((N_x+2) x (N_y+2) [x (N_z+2)])
-template <int D>
-__device__ __forceinline__ int box_size(const int* N)
-{
-    return D == 3 ? (N[0] + 2) * (N[1] + 2) * (N[2] + 2) : (N[0] + 2) * (N[1] + 2);
-}
-
-template <int D>
-__device__ __forceinline__ int box_active(const int* N)
-{
-    return D == 3 ? N[0] * N[1] * N[2] : N[0] * N[1];
-}
-
-// q = a / N and a % N for 0 <= a < 2^22 through a float reciprocal (rN = 1/N,
-// loop-invariant) corrected by one step, instead of an integer division
-__device__ __forceinline__ int divmod_small(int a, int N, float rN, int& rem)
-{
-    int q = (int)((float)a * rN);
-    int r = a - q * N;
-    if (r < 0) {
-        q--;
-        r += N;
-    } else if (r >= N) {
-        q++;
-        r -= N;
-    }
-    rem = r;
-    return q;
-}
-
-template <int D>
-__device__ __forceinline__ void tail_point(int t, const int* N, const float* rN, int& i, int& j, int& k)
-{
-    int ri;
-    const int r = divmod_small(t, N[0], rN[0], ri);
-    i = 1 + ri;
-    if (D == 3) {
-        int rj;
-        k = 1 + divmod_small(r, N[1], rN[1], rj);
-        j = 1 + rj;
-    } else {
-        j = 1 + r;
-        k = 0;
-    }
-}
-
-// element index of (i, j, k) in a level box with active points N
-__device__ __forceinline__ int box_idx(const int* N, int i, int j, int k)
-{
-    return (k * (N[1] + 2) + j) * (N[0] + 2) + i;
-}
-
-// One half sweep; the threads run over the points of the colour only: row
-// (j, k) holds (N_x + 1) / 2 slots, slot s is i = i0 + 2 s with i0 = 1 or 2
-// by the row's parity (a slot past N_x has no point).
-template <int D, typename C>
-__device__ __forceinline__ void tail_sweep(C* U, const C* F, const int* N, const float* rN, float rS, C h2, C inv2d,
-                                           const GRule<C>& gr, int colour)
-{
-    const int Qx = N[0] + 2, Qxy = Qx * (N[1] + 2);
-    const int hs = (N[0] + 1) >> 1;
-    const int total = hs * N[1] * (D == 3 ? N[2] : 1);
-    for (int t = threadIdx.x; t < total; t += kTailThreads) {
-        int sl;
-        const int row = divmod_small(t, hs, rS, sl);
-        int j, k;
-        if (D == 3) {
-            int rj;
-            k = 1 + divmod_small(row, N[1], rN[1], rj);
-            j = 1 + rj;
-        } else {
-            j = 1 + row;
-            k = 0;
-        }
-        const int i = 1 + ((1 + j + k + D + colour) & 1) + 2 * sl;
-        if (i > N[0]) continue;
-        const int idx = box_idx(N, i, j, k);
-        C xm = U[idx - 1], xp = U[idx + 1], ym = U[idx - Qx], yp = U[idx + Qx], zm = 0, zp = 0;
-        if (D == 3) {
-            zm = U[idx - Qxy];
-            zp = U[idx + Qxy];
-        }
-        const C me = U[idx];
-        rule_pair(i, N[0], me, xm, xp, gr, 0);
-        rule_pair(j, N[1], me, ym, yp, gr, 1);
-        if (D == 3) rule_pair(k, N[2], me, zm, zp, gr, 2);
-        C s = xm + xp;
-        s = s + ym;
-        s = s + yp;
-        if (D == 3) {
-            s = s + zm;
-            s = s + zp;
-        }
-        U[idx] = (s - h2 * F[idx]) * inv2d;
-    }
-}
-
-template <int D, typename C>
-__device__ __forceinline__ void tail_restrict(const C* U, const C* F, const int* Nf, C inv_h2, const GRule<C>& gr,
-                                              C* Uc, C* Fc, const int* Nc, const float* rNc)
-{
-    const int Qx = Nf[0] + 2, Qxy = Qx * (Nf[1] + 2), total = box_active<D>(Nc);
-    for (int t = threadIdx.x; t < total; t += kTailThreads) {
-        int I, J, K;
-        tail_point<D>(t, Nc, rNc, I, J, K);
-        C sum = 0;
-        const int k0 = D == 3 ? 2 * K - 1 : 0, k1 = D == 3 ? 2 * K : 0;
-        for (int k = k0; k <= k1; k++)
-            for (int j = 2 * J - 1; j <= 2 * J; j++)
-                for (int i = 2 * I - 1; i <= 2 * I; i++) {
-                    if (i > Nf[0] || j > Nf[1] || (D == 3 && k > Nf[2])) continue;
-                    const int idx = box_idx(Nf, i, j, k);
-                    C xm = U[idx - 1], xp = U[idx + 1], ym = U[idx - Qx], yp = U[idx + Qx], zm = 0, zp = 0;
-                    if (D == 3) {
-                        zm = U[idx - Qxy];
-                        zp = U[idx + Qxy];
-                    }
-                    const C uc = U[idx];
-                    rule_pair(i, Nf[0], uc, xm, xp, gr, 0);
-                    rule_pair(j, Nf[1], uc, ym, yp, gr, 1);
-                    if (D == 3) rule_pair(k, Nf[2], uc, zm, zp, gr, 2);
-                    C s = xm + xp;
-                    s = s + ym;
-                    s = s + yp;
-                    if (D == 3) {
-                        s = s + zm;
-                        s = s + zp;
-                    }
-                    sum += F[idx] - (s - (C)(2 * D) * uc) * inv_h2;
-                }
-        const int pc = box_idx(Nc, I, J, K);
-        Fc[pc] = sum * ((C)(D == 3 ? 0.125 : 0.25) * (C)1);
-        Uc[pc] = (C)0;
-    }
-}
-
-template <int D, typename C>
-__device__ __forceinline__ void tail_prolong(const C* Ue, const int* Nc, const GRule<C>& gr, C* U, const int* Nf,
-                                             const float* rNf)
-{
-    const int total = box_active<D>(Nf);
-    const AxisNb<C> none{0, (C)1, false};
-    for (int t = threadIdx.x; t < total; t += kTailThreads) {
-        int i, j, k;
-        tail_point<D>(t, Nf, rNf, i, j, k);
-        const int qi = (i + 1) >> 1, si = (i & 1) ? -1 : 1;
-        const int qj = (j + 1) >> 1, sj = (j & 1) ? -1 : 1;
-        const int qk = D == 3 ? (k + 1) >> 1 : 0, sk = (k & 1) ? -1 : 1;
-        const AxisNb<C> pi_ = axis_nb(qi, Nc[0], gr, 0), ni = axis_nb(qi + si, Nc[0], gr, 0);
-        const AxisNb<C> pj_ = axis_nb(qj, Nc[1], gr, 1), nj = axis_nb(qj + sj, Nc[1], gr, 1);
-        const AxisNb<C> pk_ = D == 3 ? axis_nb(qk, Nc[2], gr, 2) : none;
-        const AxisNb<C> nk = D == 3 ? axis_nb(qk + sk, Nc[2], gr, 2) : none;
-        auto E = [&](bool bx, bool by, bool bz) -> C {
-            const AxisNb<C>& ax = bx ? ni : pi_;
-            const AxisNb<C>& ay = by ? nj : pj_;
-            const AxisNb<C>& az = bz ? nk : pk_;
-            C v = Ue[box_idx(Nc, ax.q, ay.q, az.q)];
-            if (ax.ghost) v = ax.fac * v;
-            if (ay.ghost) v = ay.fac * v;
-            if (az.ghost) v = az.fac * v;
-            return v;
-        };
-        C y0 = prolong34(E(false, false, false), E(true, false, false));
-        C y1 = prolong34(E(false, true, false), E(true, true, false));
-        C v = prolong34(y0, y1);
-        if (D == 3) {
-            C y2 = prolong34(E(false, false, true), E(true, false, true));
-            C y3 = prolong34(E(false, true, true), E(true, true, true));
-            v = prolong34(v, prolong34(y2, y3));
-        }
-        const int idx = box_idx(Nf, i, j, k);
-        U[idx] = U[idx] + v;
-    }
-}
-
-template <int D, typename C>
-__global__ void __launch_bounds__(kTailThreads) k_coarse_tail(TailParams<C> P, SGrid g0, const C* __restrict__ fg,
-                                                              C* __restrict__ ug)
-{
-    extern __shared__ __align__(16) unsigned char tail_lds[];
-    if (batch_idle(g0)) return;
-    fg = batch_at(fg, g0);
-    ug = batch_at(ug, g0);
-    C* const lds = reinterpret_cast<C*>(tail_lds);
-    const C inv2d = (C)(1.0 / (2.0 * D));
-    auto U = [&](int a) { return lds + P.off[a]; };
-    auto F = [&](int a) { return lds + P.off[a] + box_size<D>(P.N[a]); };
-    auto sweep = [&](int a) {
-        for (int colour = 0; colour < 2; colour++) {
-            tail_sweep<D, C>(U(a), F(a), P.N[a], P.rN[a], P.rS[a], P.h2[a], inv2d, P.gr[a], colour);
-            __syncthreads();
-        }
-    };
-    {
-        const int* N = P.N[0];
-        const int total = box_active<D>(N);
-        C* u = U(0);
-        C* f = F(0);
-        for (int t = threadIdx.x; t < total; t += kTailThreads) {
-            int i, j, k;
-            tail_point<D>(t, N, P.rN[0], i, j, k);
-            const int idx = box_idx(N, i, j, k);
-            f[idx] = fg[pos<D, C>(g0, i, j, k)];
-            u[idx] = (C)0;
-        }
-        __syncthreads();
-    }
-    for (int it = 0; it < P.n_pre; it++) sweep(0);
-    int a = 0;
-    while (a + 1 < P.nlev) {
-        tail_restrict<D, C>(U(a), F(a), P.N[a], P.inv_h2[a], P.gr[a], U(a + 1), F(a + 1), P.N[a + 1], P.rN[a + 1]);
-        __syncthreads();
-        for (int it = 0; it < P.n_pre; it++) sweep(a + 1);
-        a++;
-    }
-    while (a > 0) {
-        tail_prolong<D, C>(U(a), P.N[a], P.gr[a], U(a - 1), P.N[a - 1], P.rN[a - 1]);
-        __syncthreads();
-        for (int it = 0; it < P.n_post; it++) sweep(a - 1);
-        a--;
-    }
-    {
-        const int* N = P.N[0];
-        const int total = box_active<D>(N);
-        const C* u = U(0);
-        for (int t = threadIdx.x; t < total; t += kTailThreads) {
-            int i, j, k;
-            tail_point<D>(t, N, P.rN[0], i, j, k);
-            ug[pos<D, C>(g0, i, j, k)] = u[box_idx(N, i, j, k)];
-        }
-    }
-}
-
 // ------------------------------------------------------------------ defect correction
 // Outer FP64 pass of the mixed-precision solve, fused into one sweep over the
 // level-0 active points:
@@ -3633,48 +3375,6 @@ void launch_prolong_add(int dim, hipStream_t st, SGrid gc, const TC* ec, SGrid g
         hipLaunchKernelGGL((k_prolong_add<2, TC, TF>), grid, dim3(kBlock), 0, st, ec, gc, u, gf, black_only, gr);
 }
 
-static size_t tail_box(int dim, const int* N)
-{
-    const size_t qx = (size_t)N[0] + 2, qy = (size_t)N[1] + 2, qz = (size_t)N[2] + 2;
-    return dim == 3 ? qx * qy * qz : qx * qy;
-}
-
-size_t coarse_tail_lds_bytes(int dim, const int (*N)[3], int nlev, size_t esz)
-{
-    size_t e = 0;
-    for (int a = 0; a < nlev; a++) e += 2 * tail_box(dim, N[a]);
-    return e * esz;
-}
-
-template <typename T>
-int launch_coarse_tail(int dim, hipStream_t st, int nlev, const int (*N)[3], const double* h, const Rule3* rule,
-                       int n_pre, int n_post, SGrid g0, const T* f0, T* u0)
-{
-    if (nlev < 1 || nlev > kTailMaxLevels) return -1;
-    const size_t bytes = coarse_tail_lds_bytes(dim, N, nlev, sizeof(T));
-    if (bytes > kTailLdsBytes) return -1;
-    TailParams<T> P{};
-    P.nlev = nlev;
-    P.n_pre = n_pre;
-    P.n_post = n_post;
-    int off = 0;
-    for (int a = 0; a < nlev; a++) {
-        for (int ax = 0; ax < 3; ax++) P.N[a][ax] = ax < dim ? N[a][ax] : 0;
-        P.off[a] = off;
-        off += 2 * (int)tail_box(dim, N[a]);
-        P.h2[a] = (T)(h[a] * h[a]);
-        P.inv_h2[a] = (T)(1.0 / (h[a] * h[a]));
-        P.gr[a] = grule<T>(rule[a]);
-        for (int ax = 0; ax < 3; ax++) P.rN[a][ax] = ax < dim ? 1.0f / (float)N[a][ax] : 0.0f;
-        P.rS[a] = 1.0f / (float)((N[a][0] + 1) / 2);
-    }
-    if (dim == 3)
-        hipLaunchKernelGGL((k_coarse_tail<3, T>), dim3(1, g0.nb), dim3(kTailThreads), bytes, st, P, g0, f0, u0);
-    else
-        hipLaunchKernelGGL((k_coarse_tail<2, T>), dim3(1, g0.nb), dim3(kTailThreads), bytes, st, P, g0, f0, u0);
-    return 0;
-}
-
 template <typename TL>
 void launch_dc_outer(int dim, hipStream_t st, SGrid g, const double* phi_in, const TL* e_in, double factor,
                      double* phi_out, const double* f, double inv_h2, double rscale, TL* r, TL* e_out, int first_red,
@@ -3826,10 +3526,6 @@ template void launch_prolong_add<double, double>(int, hipStream_t, SGrid, const 
 template void launch_prolong_add<float, float>(int, hipStream_t, SGrid, const float*, SGrid, float*, int, const Rule3&);
 template void launch_prolong_add<float, __half>(int, hipStream_t, SGrid, const float*, SGrid, __half*, int,
                                                 const Rule3&);
-template int launch_coarse_tail<float>(int, hipStream_t, int, const int (*)[3], const double*, const Rule3*, int, int,
-                                       SGrid, const float*, float*);
-template int launch_coarse_tail<double>(int, hipStream_t, int, const int (*)[3], const double*, const Rule3*, int,
-                                        int, SGrid, const double*, double*);
 template void launch_dc_outer<float>(int, hipStream_t, SGrid, const double*, const float*, double, double*,
                                      const double*, double, double, float*, float*, int, unsigned long long*);
 template void launch_dc_outer<__half>(int, hipStream_t, SGrid, const double*, const __half*, double, double*,

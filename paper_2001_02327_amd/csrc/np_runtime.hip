@@ -501,21 +501,6 @@ void coarse_sweep(const np_solver* s, int l, const MGView<T>& v, int L, hipStrea
         launch_half_sweep<T>(d, st, v.g[L], v.u[L], v.f[L], colour, v.h[L] * v.h[L], 0, rule);
 }
 
-// First multigrid level of the coarse tail of nested level l (the levels from
-// there to the coarsest level fit in LDS together, elements of esz bytes),
-// or 0 if none does.
-int tail_level(const np_solver* s, int l, size_t esz)
-{
-    const int nmg = s->plan.nmg[l];
-    for (int L = 1; L < nmg; L++) {
-        const int nlev = nmg - L;
-        if (nlev <= kTailMaxLevels &&
-            coarse_tail_lds_bytes(s->cfg.dim, &s->plan.N[l][L], nlev, esz) <= kTailLdsBytes)
-            return L;
-    }
-    return 0;
-}
-
 // post-smoothing sweeps below multigrid level 0
 int coarse_npost(const np_config& c) { return c.coarse_post >= 0 ? c.coarse_post : c.n_post; }
 
@@ -526,6 +511,25 @@ bool legs_cfg(const np_config& c)
 {
     return (c.sweep == NP_SWEEP_FULL || c.sweep == NP_SWEEP_FUSED) && level_legs_fit(c.dim, c.n_pre, c.n_post) &&
            level_legs_fit(c.dim, c.n_pre, coarse_npost(c));
+}
+
+// First multigrid level of the coarse tail of nested level l (the levels from
+// there to the coarsest level fit in LDS together, elements of esz bytes),
+// or 0 if none does.  With fused legs the tail takes only levels whose points a
+// thread each holds: 17^3 points in FP32 cost 20 us more in the tail, two kernels of 6
+// and 8 us as legs, eight of 4 us in per-pass kernels.
+int tail_level(const np_solver* s, int l, size_t esz)
+{
+    const int nmg = s->plan.nmg[l];
+    const bool legs = legs_cfg(s->cfg);
+    for (int L = 1; L < nmg; L++) {
+        const int nlev = nmg - L;
+        if (nlev <= kTailMaxLevels &&
+            coarse_tail_lds_bytes(s->cfg.dim, &s->plan.N[l][L], nlev, esz) <= kTailLdsBytes &&
+            (!legs || coarse_tail_slots(s->cfg.dim, s->plan.N[l][L]) <= kTailThreads))
+            return L;
+    }
+    return 0;
 }
 
 // First multigrid level of nested level l that runs as fused legs, as do the levels

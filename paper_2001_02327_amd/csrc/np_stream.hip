@@ -78,15 +78,6 @@ struct LegArgs {
     unsigned long long* maxbits;
 };
 
-// Barrier that orders LDS only: __syncthreads also waits for every global load in
-// flight, which are the next planes' (each step then took a memory round trip, 2 us).
-__device__ __forceinline__ void lds_barrier()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
 // One plane of an array as a buffer: accesses past its `bytes` (inactive lanes get such an
 // offset, planes without work no bytes at all) read zero and write nothing, so a step
 // issues the same loads and stores whatever it does and they can stay in flight for
