@@ -88,15 +88,15 @@ extern "C" {
                                layer is its Dirichlet data); FP64, interpolated guess and the
                                residual stop rule only */
 
-/* How a 3-D solve runs its V-cycles (np_config.sweep).
+/* How a solve runs its V-cycles (np_config.sweep).
  * NP_SWEEP_FULL: with one or two pre- and post-smoothing sweeps (n_pre, n_post,
  * coarse_post) as fused legs: one launch takes a multigrid level through its
  * pre-smoothing sweeps, the residual and its restriction, another through the
  * prolongation, the post-smoothing sweeps and on multigrid level 0 the stop
  * test's residual norm.  FP64: every level above the coarse tail, from the
  * level's potential into a second buffer (the handle's) and back; the defect
- * correction: the coarse levels of up to 1024 blocks of 8^3 points.  With other
- * sweep counts, FP64: on level grids whose full sweep starts at least 4096
+ * correction: the coarse levels, 3-D those of up to 1024 blocks of 8^3 points.
+ * With other sweep counts, 3-D FP64: on level grids whose full sweep starts at least 4096
  * wavefronts (cubic levels from about 420^3 cells; on smaller or thin grids
  * the half sweeps, which occupy the chip better, run), each
  * red-black sweep is one pass from the level's potential

@@ -1,5 +1,5 @@
 // Device helpers shared by the kernels of the nested-grid multigrid solver
-// (np_kernels.hip, np_tile.hip, np_stream.hip): work numbering, lane shifts, colour-split
+// (np_kernels.hip, np_tile.hip, np_tile2.hip, np_stream.hip, np_tail.hip): work numbering, lane shifts, colour-split
 // indexing, maximum reductions, the ghost rule of the coarse levels.
 #pragma once
 

@@ -200,19 +200,21 @@ void launch_copy_ghosts(int dim, hipStream_t st, SGrid g, const double* src, dou
 void launch_copy_box(int dim, hipStream_t st, SGrid gs, const double* src, SGrid gd, double* dst, int lo,
                      const int* hi, int shift);
 
-// Fused legs of one 3-D multigrid level, for one or two pre- and post-smoothing sweeps
-// (level_legs_fit): blocks of a level in LDS (np_tile.hip), or, in FP64 on the levels
-// that level_tile leaves, columns streamed through it (np_stream.hip).  g: the level,
+// Fused legs of one multigrid level, for one or two pre- and post-smoothing sweeps
+// (level_legs_fit): blocks of a level in LDS (3-D: np_tile.hip, 2-D: np_tile2.hip), or, in
+// 3-D FP64 on the levels that level_tile leaves, columns streamed through it
+// (np_stream.hip).  g: the level,
 // gc: the next coarser one; rule / coarse_rule: their ghost rules; rev: order of the
 // blocks (cache reuse only).
 struct LevelLeg {
+    int dim;
     SGrid g, gc;
     double h2, inv_h2;
     Rule3 rule, coarse_rule;
     int rev;
 };
-bool level_legs_fit(int dim, int n_pre, int n_post);
-bool level_tile(const SGrid& g);
+bool level_legs_fit(int n_pre, int n_post);
+bool level_tile(int dim, const SGrid& g);
 // n_pre sweeps, then the residual's restriction into fc.  rule: a coarse level, from zero,
 // ghost values by its rule; otherwise (FP64) multigrid level 0 from u_in, ghost layer
 // in memory.  The smoothed values go to u_out: the black ones, with rule both
@@ -221,6 +223,8 @@ template <typename T>
 void launch_level_down(hipStream_t st, const LevelLeg& a, int n_pre, bool rule, const T* u_in, const T* f, T* u_out, T* fc);
 void launch_stream_down(hipStream_t st, const LevelLeg& a, int n_pre, bool rule, const double* u_in, const double* f,
                         double* u_out, double* fc);
+template <typename T>
+void launch_tile2_down(hipStream_t st, const LevelLeg& a, int n_pre, bool rule, const T* u_in, const T* f, T* u_out, T* fc);
 // u_in (as launch_level_down left it) plus the prolonged ec, n_post sweeps, into u_out
 // (both colours; not u_in).  Without rule the ghost layer is read from ring (which may
 // be u_out) and the max norm of the result's residual goes into maxbits (zeroed by
@@ -230,6 +234,9 @@ void launch_level_up(hipStream_t st, const LevelLeg& a, int n_post, bool rule, c
                      T* u_out, const T* ec, unsigned long long* maxbits);
 void launch_stream_up(hipStream_t st, const LevelLeg& a, int n_post, bool rule, const double* u_in, const double* ring,
                       const double* f, double* u_out, const double* ec, unsigned long long* maxbits);
+template <typename T>
+void launch_tile2_up(hipStream_t st, const LevelLeg& a, int n_post, bool rule, const T* u_in, const T* ring, const T* f,
+                     T* u_out, const T* ec, unsigned long long* maxbits);
 
 // learned initial guess network (np_net.hip); activations channel-last,
 // weights bfloat16 [27][cout][cin]

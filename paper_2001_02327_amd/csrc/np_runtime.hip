@@ -504,13 +504,13 @@ void coarse_sweep(const np_solver* s, int l, const MGView<T>& v, int L, hipStrea
 // post-smoothing sweeps below multigrid level 0
 int coarse_npost(const np_config& c) { return c.coarse_post >= 0 ? c.coarse_post : c.n_post; }
 
-// Fused legs (one launch down and one up per multigrid level, np_tile.hip and np_stream.hip) hold one or
-// two sweeps; other counts, 2-D and the sweep modes that name another form run the
+// Fused legs (one launch down and one up per multigrid level, np_tile.hip, np_tile2.hip and np_stream.hip) hold one or
+// two sweeps; other counts and the sweep modes that name another form run the
 // per-pass kernels.
 bool legs_cfg(const np_config& c)
 {
-    return (c.sweep == NP_SWEEP_FULL || c.sweep == NP_SWEEP_FUSED) && level_legs_fit(c.dim, c.n_pre, c.n_post) &&
-           level_legs_fit(c.dim, c.n_pre, coarse_npost(c));
+    return (c.sweep == NP_SWEEP_FULL || c.sweep == NP_SWEEP_FUSED) && level_legs_fit(c.n_pre, c.n_post) &&
+           level_legs_fit(c.n_pre, coarse_npost(c));
 }
 
 // First multigrid level of the coarse tail of nested level l (the levels from
@@ -544,9 +544,9 @@ int legs_level(const np_solver* s, int l)
     const int Lt = tail_level(s, l, fp64 ? sizeof(double) : sizeof(float));
     if (Lt == 0) return nmg;
     // (the streamed form addresses a plane of a colour by 31 bits)
-    if (fp64) return s->lg[l].ps * sizeof(double) < (1ULL << 31) ? 0 : nmg;
+    if (fp64) return s->cfg.dim == 2 || s->lg[l].ps * sizeof(double) < (1ULL << 31) ? 0 : nmg;
     for (int L = 1; L < Lt; L++)
-        if (level_tile(mg_grid(s, l, L))) return L;
+        if (level_tile(s->cfg.dim, mg_grid(s, l, L))) return L;
     return nmg;
 }
 
@@ -571,7 +571,7 @@ template <typename T>
 LevelLeg leg_of(const np_solver* s, int l, const MGView<T>& v, int L, int rev)
 {
     const double h2 = v.h[L] * v.h[L];
-    return LevelLeg{v.g[L], v.g[L + 1], h2, 1.0 / h2, L > 0 ? rule_of(s, l, L) : Rule3{}, rule_of(s, l, L + 1), rev};
+    return LevelLeg{s->cfg.dim, v.g[L], v.g[L + 1], h2, 1.0 / h2, L > 0 ? rule_of(s, l, L) : Rule3{}, rule_of(s, l, L + 1), rev};
 }
 
 // Everything a V-cycle does on levels L >= 1 (Sec. 2.3 steps 6-13 below the
@@ -1503,7 +1503,8 @@ int nested_poisson_create(const np_config* cfg, void* hip_stream, np_solver** ou
         s->alt_cap = best * sizeof(double);
         if (rc == NP_OK) rc = alloc_dev(s, (void**)&s->phi_alt, s->alt_cap);
     }
-    if (rc == NP_OK && !dc && d == 3 && cfg->sweep != NP_SWEEP_HALF && cfg->n_pre >= 1 && cfg->n_post >= 1) {
+    if (rc == NP_OK && !dc &&
+        (legs_min == 0 || (d == 3 && cfg->sweep != NP_SWEEP_HALF && cfg->n_pre >= 1 && cfg->n_post >= 1))) {
         // the second potential buffer of the fused legs (a batch's members side by
         // side) and of the full sweeps
         size_t best = 0;

@@ -501,7 +501,7 @@ k_tile_up3(const T* __restrict__ u_in, const T* ring, const T* __restrict__ f, S
             if ((j & 1) ? ra : rb) u_out[g.cs + (size_t)pk * g.ps + base] = B[at];
         }
     }
-    if constexpr (NORM) block_max_to_w<S::NT / 64, false>(best, maxbits);
+    if constexpr (NORM) block_max_to_w<S::NT / 64, true>(best, maxbits);
 }
 
 }  // namespace
@@ -517,9 +517,9 @@ static dim3 tl_grid(const SGrid& g)
     return dim3((unsigned)((long)ceil_div(g.nx - 2, 8) * ceil_div(g.ny - 2, 8) * ceil_div(g.nz - 2, 8)), g.nb);
 }
 
-bool level_legs_fit(int dim, int n_pre, int n_post)
+bool level_legs_fit(int n_pre, int n_post)
 {
-    return dim == 3 && (n_pre == 1 || n_pre == 2) && (n_post == 1 || n_post == 2);
+    return (n_pre == 1 || n_pre == 2) && (n_post == 1 || n_post == 2);
 }
 
 // Blocks serve levels of at most 1024 of them (four per CU; batch members included): their
@@ -531,8 +531,9 @@ bool level_legs_fit(int dim, int n_pre, int n_post)
 // 129^3 20 + 49 against 51.
 constexpr long kTileBlocks = 1024;
 
-bool level_tile(const SGrid& g)
+bool level_tile(int dim, const SGrid& g)
 {
+    if (dim == 2) return true;
     const dim3 b = tl_grid(g);
     return (long)b.x * b.y <= kTileBlocks;
 }
@@ -559,8 +560,9 @@ static void up3(hipStream_t st, const LevelLeg& a, const T* u_in, const T* ring,
 template <typename T>
 void launch_level_down(hipStream_t st, const LevelLeg& a, int n_pre, bool rule, const T* u_in, const T* f, T* u_out, T* fc)
 {
+    if (a.dim == 2) return launch_tile2_down<T>(st, a, n_pre, rule, u_in, f, u_out, fc);
     if constexpr (sizeof(T) == 8) {
-        if (!level_tile(a.g)) return launch_stream_down(st, a, n_pre, rule, u_in, f, u_out, fc);
+        if (!level_tile(3, a.g)) return launch_stream_down(st, a, n_pre, rule, u_in, f, u_out, fc);
         if (!rule) {
             if (n_pre == 1) down3<T, 1, false>(st, a, u_in, f, u_out, fc);
             else down3<T, 2, false>(st, a, u_in, f, u_out, fc);
@@ -575,8 +577,9 @@ template <typename T>
 void launch_level_up(hipStream_t st, const LevelLeg& a, int n_post, bool rule, const T* u_in, const T* ring, const T* f,
                      T* u_out, const T* ec, unsigned long long* maxbits)
 {
+    if (a.dim == 2) return launch_tile2_up<T>(st, a, n_post, rule, u_in, ring, f, u_out, ec, maxbits);
     if constexpr (sizeof(T) == 8) {
-        if (!level_tile(a.g)) return launch_stream_up(st, a, n_post, rule, u_in, ring, f, u_out, ec, maxbits);
+        if (!level_tile(3, a.g)) return launch_stream_up(st, a, n_post, rule, u_in, ring, f, u_out, ec, maxbits);
         if (!rule) {
             if (n_post == 1) up3<T, 1, false>(st, a, u_in, ring, f, u_out, ec, maxbits);
             else up3<T, 2, false>(st, a, u_in, ring, f, u_out, ec, maxbits);

@@ -1,10 +1,12 @@
-"""Fused V-cycle legs (the default sweep mode, 3-D, one or two pre- and
-post-smoothing sweeps) against the per-pass kernels (sweep="half").
+"""Fused V-cycle legs (the default sweep mode, one or two pre- and post-smoothing
+sweeps) against the per-pass kernels (sweep="half").
 
-One launch takes a multigrid level down or up: blocks of the level in LDS on
-levels of at most 1024 blocks of 8 x 8 x 8 points (batch members included), in
+One launch takes a multigrid level down or up.  3-D: blocks of the level in LDS
+on levels of at most 1024 blocks of 8 x 8 x 8 points (batch members included), in
 FP64 columns streamed through it on the larger ones; in the mixed precisions the
-coarse levels that fit the block form.  Every operation and its order are those of
+coarse levels that fit the block form.  2-D: blocks of 16^2 points, of 32^2 for the leg
+with the norm where the small ones are more than 512; in the mixed precisions the
+coarse levels.  Every operation and its order are those of
 the per-pass kernels, so potentials, forces, cycle counts and residual histories
 are compared for equality, bit for bit.
 """
@@ -77,6 +79,26 @@ def test_batches(n):
 @pytest.mark.parametrize("wl", [W.c2_plummer(32), W.c2_plummer(132, 1), W.box_plummer_3d(4)], ids=lambda w: w.name)
 def test_coarse_levels_mixed(wl, kw, precision):
     _same(wl, precision=precision, inner_cycles="adaptive", **kw)
+
+
+# 2-D: blocks exactly filled and one point more, several blocks, both block sizes
+SIZES2 = [(8, 8), (16, 16), (30, 14), (32, 34), (62, 62), (126, 128), (254, 62), (128, 510), (510, 512), (1022, 1024)]
+
+
+@pytest.mark.parametrize("n", SIZES2, ids=lambda n: "x".join(map(str, n)))
+@pytest.mark.parametrize("pre,post", [(2, 1), (1, 2)])
+def test_sizes_2d(n, pre, post):
+    g = W.Geometry(dim=2, n=[n], off=[(0, 0, 0)], lo0=(0.0, 0.0, 0.0), dx0=1.0 / 32)
+    _same(W.Workload("one%s" % (n,), g, W.Gaussian(0.15, 1.0)), n_pre=pre, n_post=post, max_cycles=8)
+
+
+@pytest.mark.parametrize("kw", [dict(), dict(n_pre=1, coarse_post=2), dict(buffer="interp"), dict(stop_rule="force_delta"),
+                                dict(precision="fp32_dc", inner_cycles=2),
+                                dict(precision="fp16s_dc", inner_cycles="adaptive", n_pre=1, coarse_post=2)],
+                         ids=lambda kw: "-".join("%s=%s" % a for a in kw.items()) or "default")
+@pytest.mark.parametrize("wl", [W.c1_gaussian_2d(64), W.paper2d(256), W.box_gaussian_2d(2)], ids=lambda w: w.name)
+def test_nested_2d(wl, kw):
+    _same(wl, **kw)
 
 
 def test_large():
