@@ -132,7 +132,10 @@ __global__ void __launch_bounds__(S::NT) k_leg3(LegArgs A)
     const C* const ring = batch_at(A.ring, g);
     const C* const f = batch_at(A.f, g);
     C* const u_out = batch_at(A.u_out, g);
-    C* const pl = lds + S::PAD;  // plane i of parity s at pl + (2 i + s) PL
+    // plane i of parity s at pl + (2 i + s) PL: the threads' first rows, then their second
+    // ones, so that a wavefront reads consecutive elements (a row after the other as in
+    // the region, with two rows per thread, two in five LDS cycles went to bank conflicts)
+    C* const pl = lds + S::PAD;
     C* const resl = lds + 2 * NA * PL + 2 * S::PAD;
     C* const el = resl + 2 * RESN;
     const int Nx = g.nx - 2, Ny = g.ny - 2, Nz = g.nz - 2;
@@ -148,7 +151,6 @@ __global__ void __launch_bounds__(S::NT) k_leg3(LegArgs A)
     const int t = min(tid, S::NTH - 1);
     const bool in_reg = tid < S::NTH;
     const int lm = t / S::HC, lh = t - lm * S::HC;
-    const int col = 2 * lm * S::HC + lh;  // the first of the two rows; the second is HC further
     const int hs = (X0 - S::H) >> 1, ys = Y0 - S::H;
     const int hg = hs + lh, pj = ys + 2 * lm;
     // per row: byte offset in a plane; activity of the even and the odd point; byte offsets of
@@ -289,6 +291,19 @@ __global__ void __launch_bounds__(S::NT) k_leg3(LegArgs A)
     unsigned long long best = 0;
     constexpr int CTX = S::TX / 2, NCT = CTX * (S::TY / 2);
     static_assert(UP || NCT <= S::NT, "a thread per coarse point");
+    // down: residuals of the block by child (first or second along x and along y), each
+    // CTX x TY / 2 values in the order of the coarse points: where the odd point of a
+    // row goes (the even one is the coarse point's before, second child)
+    int rwo[2];
+    bool rw1[2], rw2[2];
+#pragma unroll
+    for (int r = 0; r < 2; r++) {
+        const int y = pj + r - Y0, kb = hg - ((X0 - 1) >> 1);
+        const bool yin = in_reg && y >= 0 && y < S::TY;
+        rwo[r] = 2 * ((S::H + r) & 1) * NCT + (y >> 1) * CTX + kb;
+        rw1[r] = yin && kb >= 0 && kb < CTX;
+        rw2[r] = yin && kb >= 1 && kb <= CTX;
+    }
     // down: a thread's coarse point, by parity of its x + y
     const unsigned cbytes = (unsigned)(gc.ps * sizeof(C));
     unsigned coff0 = kLegOob, coff1 = kLegOob;
@@ -318,8 +333,8 @@ __global__ void __launch_bounds__(S::NT) k_leg3(LegArgs A)
         // LDS planes of a's parity and of the other one.  Half sweep i reads its source's
         // plane a - i and writes its own plane a - i, each array holding one plane of
         // either parity: what is read in a step is not written in it
-        C* const pa = pl + pa1 * PL + col;
-        C* const pb = pl + (pa1 ^ 1) * PL + col;
+        C* const pa = pl + pa1 * PL + t;
+        C* const pb = pl + (pa1 ^ 1) * PL + t;
         // ---- every LDS read of the step, before anything waits for one: per stage the other
         // x-neighbour of either row, the row below the first and the row above the second (the
         // rows are each other's y-neighbours).  Stage NX is the red residual
@@ -329,19 +344,16 @@ __global__ void __launch_bounds__(S::NT) k_leg3(LegArgs A)
         for (int i = ZERO ? 1 : 0; i < NS; i++) {
             const C* const P = ((i & 1) ? pb : pa) + (i == 0 ? 0 : 2 * (X0A + i - 1)) * PL;
             lx[i][0] = P[dx];
-            lx[i][1] = P[S::HC - dx];
-            ly[i] = P[-S::HC];
-            lz[i] = P[2 * S::HC];
+            lx[i][1] = P[S::NTH - dx];
+            ly[i] = P[S::NTH - S::HC];
+            lz[i] = P[S::HC];
         }
         C rch[4];
         const int pp = a - NX - 1;  // down: the plane whose residuals were completed in the step before
         if constexpr (!UP) {
-            const int ci = tid % CTX, cj = tid / CTX;
-            const C* const rp = resl + (pa1 ^ 1) * RESN + (tid < NCT ? (2 * cj) * S::TX + 2 * ci : 0);
-            rch[0] = rp[0];
-            rch[1] = rp[1];
-            rch[2] = rp[S::TX];
-            rch[3] = rp[S::TX + 1];
+            const C* const rp = resl + (pa1 ^ 1) * RESN + (tid < NCT ? tid : 0);
+#pragma unroll
+            for (int e = 0; e < 4; e++) rch[e] = rp[e * NCT];
         }
 #pragma unroll
         for (int r = 0; r < 2; r++) {
@@ -481,10 +493,10 @@ __global__ void __launch_bounds__(S::NT) k_leg3(LegArgs A)
         // ---- LDS writes of the step
 #pragma unroll
         for (int r = 0; r < 2; r++) {
-            if constexpr (!ZERO) pb[r * S::HC] = b0p[r];
+            if constexpr (!ZERO) pb[r * S::NTH] = b0p[r];
 #pragma unroll
             for (int i = 0; i < NX; i++)
-                if (i < NX - 1 || RES) ((i & 1) ? pb : pa)[2 * (X0A + i) * PL + r * S::HC] = xn[i][r];
+                if (i < NX - 1 || RES) ((i & 1) ? pb : pa)[2 * (X0A + i) * PL + r * S::NTH] = xn[i][r];
         }
         // ---- results: the black points after the last half sweep, the red ones before it
 #pragma unroll
@@ -512,17 +524,13 @@ __global__ void __launch_bounds__(S::NT) k_leg3(LegArgs A)
                 leg_store(c0, coff0, (rsum * A.scale));
                 leg_store(c1, coff1, (rsum * A.scale));
             }
-            // both colours of plane a - NX, in natural order over the block
-            if (in_reg) {
+            // both colours of plane a - NX
 #pragma unroll
-                for (int r = 0; r < 2; r++) {
-                    const int xr = pi[r] - X0, xb = (pi[r] ^ 1) - X0, y = pj + r - Y0;
-                    C* const rw = resl + pa1 * RESN + y * S::TX;
-                    if (y >= 0 && y < S::TY) {
-                        if (xr >= 0 && xr < S::TX) rw[xr] = rr[r];
-                        if (xb >= 0 && xb < S::TX) rw[xb] = rbh[r];
-                    }
-                }
+            for (int r = 0; r < 2; r++) {
+                const bool od = r ? !par : par;  // the red point
+                C* const rw = resl + pa1 * RESN + rwo[r];
+                if (rw1[r]) rw[0] = od ? rr[r] : rbh[r];
+                if (rw2[r]) rw[NCT - 1] = od ? rbh[r] : rr[r];
             }
         }
         // ---- shift
