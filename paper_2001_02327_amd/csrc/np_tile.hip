@@ -7,7 +7,7 @@
 //   down: the pre-smoothing sweeps, the residual and its restriction;
 //   up:   the prolongation and correction, the post-smoothing sweeps and (for
 //         the stop test) the residual's max norm.
-// A workgroup owns a block of 8 x 8 x 8 points and takes it through every half
+// A workgroup owns a block of 8 x 8 x 8 or 16 x 16 x 8 points and takes it through every half
 // sweep of the leg in LDS, together with a halo one point wide per half sweep that
 // follows (H in all), which it recomputes: a point at distance d from the block is
 // relaxed only by the half sweeps whose values can still reach the block.  Halo
@@ -507,14 +507,21 @@ k_tile_up3(const T* __restrict__ u_in, const T* ring, const T* __restrict__ f, S
 }  // namespace
 
 // ------------------------------------------------------------------ launches
-// Block shape per halo width H (one point per half sweep or residual that follows): 8 x 8 x 8
-// points, the shortest chains and the most workgroups; G ranges of four planes.
-template <int H>
-using TlPick = TlShape<H, 8, 8, (8 + 2 * H + 3) / 4, 4>;
+// Block shapes per halo width H (one point per half sweep or residual that follows), G
+// ranges of PZ planes each.  Small: 8 x 8 x 8 points, the shortest chains and the most
+// workgroups; wide: 16 x 16 x 8 points, half the halo per point.
+template <int H, bool WIDE>
+struct TlPick {
+    using S = TlShape<H, 8, 8, (8 + 2 * H + 3) / 4, 4>;
+};
+template <> struct TlPick<2, true> { using S = TlShape<2, 16, 8, 3, 4>; };
+template <> struct TlPick<3, true> { using S = TlShape<3, 16, 8, 4, 4>; };
+template <> struct TlPick<4, true> { using S = TlShape<4, 16, 8, 3, 6>; };
+template <> struct TlPick<5, true> { using S = TlShape<5, 16, 8, 2, 10>; };
 
-static dim3 tl_grid(const SGrid& g)
+static long tl_blocks(const SGrid& g, int tx)
 {
-    return dim3((unsigned)((long)ceil_div(g.nx - 2, 8) * ceil_div(g.ny - 2, 8) * ceil_div(g.nz - 2, 8)), g.nb);
+    return (long)ceil_div(g.nx - 2, tx) * ceil_div(g.ny - 2, tx) * ceil_div(g.nz - 2, 8);
 }
 
 bool level_legs_fit(int n_pre, int n_post)
@@ -522,39 +529,50 @@ bool level_legs_fit(int n_pre, int n_post)
     return (n_pre == 1 || n_pre == 2) && (n_post == 1 || n_post == 2);
 }
 
-// Blocks serve levels of at most 1024 of them (four per CU; batch members included): their
-// halo costs four to six times the block's work, which idle CUs do for nothing.
-// Measured, down and up leg of two pre- and one post-smoothing sweep in FP64: 33^3 points
-// 10 + 7 us against 24 + 13 us streamed and 31 us per pass; 65^3 (729 blocks) 27 + 13
-// against 25 + 14 and 41; 129^3 in blocks of 16^3 points (as good as any at that size)
-// 57 + 45 against 42 + 26 and 80.  FP32, V(1,2): 65^3 9 + 19 us against 35 per pass,
-// 129^3 20 + 49 against 51.
-constexpr long kTileBlocks = 1024;
+// Small blocks while there is a CU for each; wide ones up to a workgroup per CU (1024 small
+// ones or 256 wide; batch members included).  Beyond that their halo (four to eight times
+// the block's work, which idle CUs do for nothing) costs more than streaming in FP64, and
+// than the per-pass kernels in FP32.  Measured in FP64, the coarse legs of two pre- and one
+// post-smoothing sweep (small / wide / streamed / per pass): 33^3 points (125 small blocks)
+// 9.9 + 7.5 / 14.7 + 9.9 / 22.8 + 13.2 / 31 us; 49^3 (343) 18.5 + 10.0 / 15.4 + 10.0 / 23.9
+// + 13.4; 65^3 (729) 27.0 + 12.5 / 15.8 + 10.1 / 23.7 + 13.5 / 41; 81^3 (1331) 48 + 20 /
+// 29.4 + 18.3 / 28.2 + 16.6.  FP32 V(1,2): 33^3 6.0 + 9.2 / 7.0 + 12.6, 65^3 9.2 + 18.9 /
+// 8.1 + 13.8 against 35 per pass, 129^3 20 + 49 (in blocks of 16^3) against 51.
+constexpr long kTileBlocks = 1024, kTileSmall = 256;
 
 bool level_tile(int dim, const SGrid& g)
 {
     if (dim == 2) return true;
-    const dim3 b = tl_grid(g);
-    return (long)b.x * b.y <= kTileBlocks;
+    return tl_blocks(g, 8) * g.nb <= kTileBlocks;
 }
+
+static bool tl_wide(const SGrid& g) { return tl_blocks(g, 8) * g.nb > kTileSmall; }
 
 template <typename T, int NPRE, bool RULE>
 static void down3(hipStream_t st, const LevelLeg& a, const T* u_in, const T* f, T* u_out, T* fc)
 {
-    using S = TlPick<2 * NPRE + !RULE>;
-    hipLaunchKernelGGL((k_tile_down3<T, NPRE, RULE, S>), tl_grid(a.g), dim3(S::NT), 0, st, u_in, f, a.g, u_out, (T)a.h2,
-                       (T)(1.0 / 6.0), (T)a.inv_h2, (T)0.125, grule<T>(a.rule), a.gc, fc, ceil_div(a.g.nx - 2, S::TX),
-                       ceil_div(a.g.ny - 2, S::TX), a.rev);
+    const auto go = [&](auto wide) {
+        using S = typename TlPick<2 * NPRE + !RULE, decltype(wide)::value>::S;
+        hipLaunchKernelGGL((k_tile_down3<T, NPRE, RULE, S>), dim3((unsigned)tl_blocks(a.g, S::TX), a.g.nb), dim3(S::NT), 0,
+                           st, u_in, f, a.g, u_out, (T)a.h2, (T)(1.0 / 6.0), (T)a.inv_h2, (T)0.125, grule<T>(a.rule), a.gc,
+                           fc, ceil_div(a.g.nx - 2, S::TX), ceil_div(a.g.ny - 2, S::TX), a.rev);
+    };
+    if (tl_wide(a.g)) go(std::true_type{});
+    else go(std::false_type{});
 }
 
 template <typename T, int NPOST, bool RULE>
 static void up3(hipStream_t st, const LevelLeg& a, const T* u_in, const T* ring, const T* f, T* u_out, const T* ec,
                 unsigned long long* maxbits)
 {
-    using S = TlPick<2 * NPOST + !RULE>;
-    hipLaunchKernelGGL((k_tile_up3<T, NPOST, RULE, S>), tl_grid(a.g), dim3(S::NT), 0, st, u_in, ring, f, a.g, u_out, (T)a.h2,
-                       (T)(1.0 / 6.0), (T)a.inv_h2, grule<T>(a.rule), a.gc, ec, grule<T>(a.coarse_rule),
-                       ceil_div(a.g.nx - 2, S::TX), ceil_div(a.g.ny - 2, S::TX), a.rev, maxbits);
+    const auto go = [&](auto wide) {
+        using S = typename TlPick<2 * NPOST + !RULE, decltype(wide)::value>::S;
+        hipLaunchKernelGGL((k_tile_up3<T, NPOST, RULE, S>), dim3((unsigned)tl_blocks(a.g, S::TX), a.g.nb), dim3(S::NT), 0, st,
+                           u_in, ring, f, a.g, u_out, (T)a.h2, (T)(1.0 / 6.0), (T)a.inv_h2, grule<T>(a.rule), a.gc, ec,
+                           grule<T>(a.coarse_rule), ceil_div(a.g.nx - 2, S::TX), ceil_div(a.g.ny - 2, S::TX), a.rev, maxbits);
+    };
+    if (tl_wide(a.g)) go(std::true_type{});
+    else go(std::false_type{});
 }
 
 template <typename T>
