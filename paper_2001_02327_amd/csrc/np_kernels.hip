@@ -748,6 +748,18 @@ __global__ void __launch_bounds__(kBlock) k_box_resid_norm3(SGrid g, const doubl
     block_max_to(best, maxbits);
 }
 
+// n reduction slots to pinned host memory, zeroed where they were, then the read's number
+__global__ void __launch_bounds__(64) k_publish(unsigned long long* bits, int n, unsigned long long* host,
+                                                unsigned long long* host_seq, unsigned long long seq)
+{
+    for (int t = threadIdx.x; t < n; t += 64) {
+        host[t] = bits[t];
+        bits[t] = 0;
+    }
+    __threadfence_system();
+    if (threadIdx.x == 0) __hip_atomic_store(host_seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 __global__ void k_set_u64(unsigned long long* p, int count, unsigned long long v)
 {
     int t = blockIdx.x * blockDim.x + threadIdx.x;
@@ -3154,6 +3166,12 @@ void launch_box_resid_norm3(hipStream_t st, SGrid g, const double* u, const doub
     const long nb = (long)((g.nx - 2 + kBox - 1) / kBox) * ((g.ny - 2 + kBox - 1) / kBox) *
                     ((g.nz - 2 + kBox - 1) / kBox);
     hipLaunchKernelGGL(k_box_resid_norm3, dim3(ceil_div(nb, kBlock)), dim3(kBlock), 0, st, g, u, f, inv_h2, maxbits);
+}
+
+void launch_publish(hipStream_t st, unsigned long long* bits, int n, unsigned long long* host, unsigned long long* host_seq,
+                    unsigned long long seq)
+{
+    hipLaunchKernelGGL(k_publish, dim3(1), dim3(64), 0, st, bits, n, host, host_seq, seq);
 }
 
 void launch_set_u64(hipStream_t st, unsigned long long* p, int count, unsigned long long v)

@@ -304,7 +304,8 @@ struct np_solver {
     float* mg_r32[NP_MAX_MG] = {};
     double* force_scratch = nullptr;  // FORCE_DELTA stop rule
     unsigned long long* d_bits = nullptr;  // device reduction slots
-    unsigned long long* h_bits = nullptr;  // pinned host copy
+    unsigned long long* h_bits = nullptr;  // pinned host copy, then the number of the last read
+    unsigned long long bits_seq = 0;       // number of the last read queued
     int fixed[NP_MAX_LEVELS];
     bool has_fixed = false;
     bool solved = false;
@@ -747,9 +748,42 @@ int vcycle_t(np_solver* s, int l, T0* u0, const T0* f0, double h2_0, double inv_
 // smaller ones with the half sweeps.
 constexpr long kFullSweepMinWaves = 4096;
 
+// Queues the read of n reduction slots from `slot` on, which zeroes them for their next
+// use, and waits for it: a kernel writes them to pinned memory with the read's number
+// behind them, and the host polls that number.  A copy and a synchronisation of the
+// stream took 20 us more per V-cycle.
+int read_slots(np_solver* s, int slot, int n)
+{
+    const unsigned long long seq = ++s->bits_seq;
+    launch_publish(s->stream, s->d_bits + slot, n, s->h_bits + slot, s->h_bits + kBitSlots, seq);
+    HIPCHK(s, hipGetLastError());
+    for (unsigned spin = 1;; spin++) {
+        if (__atomic_load_n(s->h_bits + kBitSlots, __ATOMIC_ACQUIRE) == seq) return NP_OK;
+        if (spin % 4096 == 0) {
+            // still running, done (the number is there, then), or failed
+            const hipError_t e = hipStreamQuery(s->stream);
+            if (e == hipErrorNotReady) {
+                (void)hipGetLastError();
+                continue;
+            }
+            HIPCHK(s, e);
+            if (__atomic_load_n(s->h_bits + kBitSlots, __ATOMIC_ACQUIRE) == seq) return NP_OK;
+            return set_err(s, NP_EHIP, "a stop test's norm did not reach the host");
+        }
+        __builtin_ia32_pause();
+    }
+}
+
+int read_norm(np_solver* s, int slot, double* out)
+{
+    const int rc = read_slots(s, slot, 1);
+    if (rc == NP_OK) *out = bits_to_double(s->h_bits[slot]);
+    return rc;
+}
+
 // The FP64 V-cycle as fused legs: u0 to the spare potential buffer and back to u0, whose
-// ghost layer both legs use.  The max norm of the result's residual goes to bits (zeroed
-// here; one slot per batch member).
+// ghost layer both legs use.  The max norm of the result's residual goes to bits (one slot
+// per batch member).
 int vcycle_legs(np_solver* s, int l, double* u0, const double* f0, const MGView<double>& v, unsigned long long* bits)
 {
     const np_config& c = s->cfg;
@@ -762,22 +796,9 @@ int vcycle_legs(np_solver* s, int l, double* u0, const double* f0, const MGView<
     int rc = run_coarse(s, l, v, s->coarse_exec);
     prof_end(s);
     if (rc) return rc;
-    launch_set_u64(st, bits, v.g[0].nb, 0ULL);
     prof_begin(s, big ? NP_KCLASS_FULL_RES : NP_KCLASS_SMOOTH);
     launch_level_up<double>(st, leg_of(s, l, v, 0, 1), c.n_post, false, s->phi_alt, u0, f0, u0, mg_result(s, l, v, 1), bits);
     prof_end(s);
-    return NP_OK;
-}
-
-// One such cycle and the residual norm of its result (host-synchronous).
-int vcycle_legs_sync(np_solver* s, int l, double* out)
-{
-    int rc = vcycle_legs(s, l, s->phi[l], s->f[l], mg_view<double>(s, l, s->mg_u, s->mg_f, s->mg_r), s->d_bits);
-    if (rc) return rc;
-    HIPCHK(s, hipGetLastError());
-    HIPCHK(s, hipMemcpyAsync(s->h_bits, s->d_bits, sizeof(unsigned long long), hipMemcpyDeviceToHost, s->stream));
-    HIPCHK(s, hipStreamSynchronize(s->stream));
-    *out = bits_to_double(s->h_bits[0]);
     return NP_OK;
 }
 
@@ -850,7 +871,6 @@ int vcycle_full(np_solver* s, int l, bool first_done)
     prof_begin(s, NP_KCLASS_PROLONG);
     launch_prolong_add<double, double>(d, st, v.g[1], v.u[1], v.g[0], s->phi[l], 1, rule_of(s, l, 1));
     prof_end(s);
-    launch_set_u64(st, s->d_bits, 1, 0ULL);
     prof_begin(s, NP_KCLASS_FULL);
     for (it = 0; it < c.n_post; it++) full_sweep(s, l, it == c.n_post - 1 ? kSweepResOut : 0);
     prof_end(s, c.n_post);
@@ -868,11 +888,7 @@ int full_sweep_norm_sync(np_solver* s, int l, double* out)
                               s->fs_rev, s->d_bits);
     prof_end(s);
     s->fs_rev ^= 1;
-    HIPCHK(s, hipGetLastError());
-    HIPCHK(s, hipMemcpyAsync(s->h_bits, s->d_bits, sizeof(unsigned long long), hipMemcpyDeviceToHost, s->stream));
-    HIPCHK(s, hipStreamSynchronize(s->stream));
-    *out = bits_to_double(s->h_bits[0]);
-    return NP_OK;
+    return read_norm(s, 0, out);
 }
 
 // Inner V-cycle of the defect correction, on the scaled level-0 problem
@@ -898,33 +914,28 @@ int vcycle_lo(np_solver* s, int l, bool red_done)
                                red_done, red_done && dc_seed_black(s, l));
 }
 
-// Queue a norm into slot `slot` and return it (host-synchronous).
-int norm_sync(np_solver* s, int l, int mode, double* out)
+// A norm into slot 0; norm_sync returns it (host-synchronous).
+void norm_launch(np_solver* s, int l, int mode)
 {
     double dx = level_dx(&s->cfg, l);
-    launch_set_u64(s->stream, s->d_bits, 1, 0ULL);
     prof_begin(s, NP_KCLASS_NORM);
     launch_norm(s->cfg.dim, s->stream, s->lg[l], s->phi[l], s->f[l], 1.0 / (dx * dx), mode, s->d_bits);
     prof_end(s);
-    HIPCHK(s, hipGetLastError());
-    HIPCHK(s, hipMemcpyAsync(s->h_bits, s->d_bits, sizeof(unsigned long long), hipMemcpyDeviceToHost, s->stream));
-    HIPCHK(s, hipStreamSynchronize(s->stream));
-    *out = bits_to_double(s->h_bits[0]);
-    return NP_OK;
 }
 
-int force_delta_sync(np_solver* s, int l, double* out)
+int norm_sync(np_solver* s, int l, int mode, double* out)
+{
+    norm_launch(s, l, mode);
+    return read_norm(s, 0, out);
+}
+
+// the force change into slot 1
+void force_delta(np_solver* s, int l)
 {
     double dx = level_dx(&s->cfg, l);
-    launch_set_u64(s->stream, s->d_bits + 1, 1, 0ULL);
     prof_begin(s, NP_KCLASS_NORM);
     launch_force_delta(s->cfg.dim, s->stream, s->lg[l], dx, s->phi[l], s->force_scratch, s->d_bits + 1);
     prof_end(s);
-    HIPCHK(s, hipGetLastError());
-    HIPCHK(s, hipMemcpyAsync(s->h_bits + 1, s->d_bits + 1, sizeof(unsigned long long), hipMemcpyDeviceToHost, s->stream));
-    HIPCHK(s, hipStreamSynchronize(s->stream));
-    *out = bits_to_double(s->h_bits[1]);
-    return NP_OK;
 }
 
 // Outer pass of the defect correction on level l (host-synchronous): with
@@ -940,7 +951,6 @@ int dc_outer_sync(np_solver* s, int l, bool update, double factor, double rscale
     void* e_in = update ? s->e_lo : nullptr;
     void* e_out = dc_seed_black(s, l) ? nullptr : (update ? s->e_nx : s->e_lo);
     double* p_out = update ? s->phi_alt : nullptr;
-    launch_set_u64(s->stream, s->d_bits, 1, 0ULL);
     prof_begin(s, NP_KCLASS_DC);
     if (c.precision == NP_PREC_FP16S_DC)
         launch_dc_outer<__half>(c.dim, s->stream, s->lg[l], s->phi[l], (const __half*)e_in, factor, p_out, s->f[l],
@@ -955,17 +965,14 @@ int dc_outer_sync(np_solver* s, int l, bool update, double factor, double rscale
         std::swap(s->phi[l], s->phi_alt);
         std::swap(s->phi_cap[l], s->alt_cap);
     }
-    HIPCHK(s, hipMemcpyAsync(s->h_bits, s->d_bits, sizeof(unsigned long long), hipMemcpyDeviceToHost, s->stream));
-    HIPCHK(s, hipStreamSynchronize(s->stream));
-    *out = bits_to_double(s->h_bits[0]);
-    return NP_OK;
+    return read_norm(s, 0, out);
 }
 
 // The level's starting residual for the defect correction: one pass of the
-// outer kernel without update that keeps f - lap phi in FP32 (r32) and returns
-// its max norm, so that the first scaled defect needs no second pass over phi
+// outer kernel without update that keeps f - lap phi in FP32 (r32) and takes
+// its max norm into slot 0, so that the first scaled defect needs no second pass over phi
 // and f (dc_scale_defect).
-int dc_first_residual(np_solver* s, int l, double* out)
+int dc_first_residual(np_solver* s, int l)
 {
     const np_config& c = s->cfg;
     double dx = level_dx(&c, l);
@@ -973,15 +980,10 @@ int dc_first_residual(np_solver* s, int l, double* out)
         HIPCHK(s, hipMemsetAsync(s->r32, 0, 2 * s->lg[l].cs * sizeof(float), s->stream));
         s->r32_grid = s->lg[l];
     }
-    launch_set_u64(s->stream, s->d_bits, 1, 0ULL);
     prof_begin(s, NP_KCLASS_NORM);
     launch_dc_outer<float>(c.dim, s->stream, s->lg[l], s->phi[l], nullptr, 0.0, nullptr, s->f[l], 1.0 / (dx * dx), 1.0,
                            s->r32, nullptr, 0, s->d_bits);
     prof_end(s);
-    HIPCHK(s, hipGetLastError());
-    HIPCHK(s, hipMemcpyAsync(s->h_bits, s->d_bits, sizeof(unsigned long long), hipMemcpyDeviceToHost, s->stream));
-    HIPCHK(s, hipStreamSynchronize(s->stream));
-    *out = bits_to_double(s->h_bits[0]);
     return NP_OK;
 }
 
@@ -1060,14 +1062,8 @@ int dc_settle(np_solver* s, int l)
 int box_resid_sync(np_solver* s, int l, double* out)
 {
     const double dx = level_dx(&s->cfg, l);
-    launch_set_u64(s->stream, s->d_bits + 3, 1, 0ULL);
     launch_box_resid_norm3(s->stream, s->lg[l], s->phi[l], s->f[l], 1.0 / (dx * dx), s->d_bits + 3);
-    HIPCHK(s, hipGetLastError());
-    HIPCHK(s, hipMemcpyAsync(s->h_bits + 3, s->d_bits + 3, sizeof(unsigned long long), hipMemcpyDeviceToHost,
-                             s->stream));
-    HIPCHK(s, hipStreamSynchronize(s->stream));
-    *out = bits_to_double(s->h_bits[3]);
-    return NP_OK;
+    return read_norm(s, 3, out);
 }
 
 // Learned initial guess of level l >= 1 (3-D): the network's prediction from
@@ -1167,7 +1163,6 @@ int solve_batch(np_solver* s, const PatchGroup& G, const double* const* rho, dou
     unsigned long long* slots = s->d_bits + kBatchSlot;
     // the members' fills (each from its own parent), max |f| of member b into slot b
     prof_begin(s, NP_KCLASS_FILL);
-    launch_set_u64(stm, slots, n, 0ULL);
     for (int b = 0; b < n; b++) {
         const int l = G.member[b];
         s->hist[l].clear();
@@ -1176,10 +1171,8 @@ int solve_batch(np_solver* s, const PatchGroup& G, const double* const* rho, dou
                               s->f[l], slots + b);
     }
     prof_end(s, n);
-    HIPCHK(s, hipGetLastError());
-    HIPCHK(s, hipMemcpyAsync(s->h_bits + kBatchSlot, slots, n * sizeof(unsigned long long), hipMemcpyDeviceToHost,
-                             stm));
-    HIPCHK(s, hipStreamSynchronize(stm));
+    int rc = read_slots(s, kBatchSlot, n);
+    if (rc) return rc;
     double scale[NP_MAX_LEVELS], r[NP_MAX_LEVELS], r0[NP_MAX_LEVELS];
     int q[NP_MAX_LEVELS] = {}, lvl[NP_MAX_LEVELS] = {};
     for (int b = 0; b < n; b++) {
@@ -1189,7 +1182,7 @@ int solve_batch(np_solver* s, const PatchGroup& G, const double* const* rho, dou
     for (int b = 0; b < n; b++) {
         if (scale[b] > 0.0) continue;
         // zero density: the residual of the zero potential sets the scale
-        int rc = norm_sync(s, G.member[b], 2, &scale[b]);
+        rc = norm_sync(s, G.member[b], 2, &scale[b]);
         if (rc) return rc;
         if (!std::isfinite(scale[b]))
             return set_err(s, NP_ENONFINITE, "level %d: non-finite boundary data", G.member[b]);
@@ -1204,22 +1197,21 @@ int solve_batch(np_solver* s, const PatchGroup& G, const double* const* rho, dou
     // legs the cycle has put them there), to the host
     auto norms = [&](bool first, bool launch) -> int {
         if (launch) {
-            launch_set_u64(stm, slots, n, 0ULL);
             prof_begin(s, NP_KCLASS_NORM);
             launch_norm(d, stm, g0, s->phi[m0], s->f[m0], 1.0 / (dx * dx), 0, slots);
             prof_end(s);
         }
-        HIPCHK(s, hipGetLastError());
-        HIPCHK(s, hipMemcpyAsync(s->h_bits + kBatchSlot, slots, n * sizeof(unsigned long long), hipMemcpyDeviceToHost,
-                                 stm));
-        HIPCHK(s, hipStreamSynchronize(stm));
+        const int e = read_slots(s, kBatchSlot, n);
+        if (e) return e;
         for (int b = 0; b < n; b++)
             if (first || s->h_act[b]) r[b] = bits_to_double(s->h_bits[kBatchSlot + b]);
         return NP_OK;
     };
     // which members go on: the rule of a single-patch solve, member by member
+    bool stopped = false;  // some member did in the last update
     auto update = [&]() -> bool {
         bool any = false;
+        stopped = false;
         for (int b = 0; b < n; b++) {
             if (!s->h_act[b]) continue;
             const int l = G.member[b];
@@ -1239,12 +1231,13 @@ int solve_batch(np_solver* s, const PatchGroup& G, const double* const* rho, dou
             }
             s->h_act[b] = go ? 1 : 0;
             any = any || go;
+            stopped = stopped || !go;
         }
         return any;
     };
     for (int b = 0; b < n; b++) s->h_act[b] = 1;
     HIPCHK(s, hipMemcpyAsync(s->d_act, s->h_act, n * sizeof(int), hipMemcpyHostToDevice, stm));
-    int rc = norms(true, true);
+    rc = norms(true, true);
     if (rc) return rc;
     for (int b = 0; b < n; b++) {
         r0[b] = r[b];
@@ -1253,7 +1246,7 @@ int solve_batch(np_solver* s, const PatchGroup& G, const double* const* rho, dou
     }
     bool any = update();
     while (any) {
-        HIPCHK(s, hipMemcpyAsync(s->d_act, s->h_act, n * sizeof(int), hipMemcpyHostToDevice, stm));
+        if (stopped) HIPCHK(s, hipMemcpyAsync(s->d_act, s->h_act, n * sizeof(int), hipMemcpyHostToDevice, stm));
         if (legs)
             rc = vcycle_legs(s, m0, s->phi[m0], s->f[m0], v, slots);
         else
@@ -1533,7 +1526,7 @@ int nested_poisson_create(const np_config* cfg, void* hip_stream, np_solver** ou
     if (rc == NP_OK && cfg->stop_rule == NP_STOP_FORCE_DELTA)
         rc = alloc_dev(s, (void**)&s->force_scratch, (size_t)d * max_cells * sizeof(double));
     if (rc == NP_OK) rc = alloc_dev(s, (void**)&s->d_bits, kBitSlots * sizeof(unsigned long long));
-    if (rc == NP_OK && hipHostMalloc((void**)&s->h_bits, kBitSlots * sizeof(unsigned long long), hipHostMallocDefault) != hipSuccess) {
+    if (rc == NP_OK && hipHostMalloc((void**)&s->h_bits, (kBitSlots + 1) * sizeof(unsigned long long), hipHostMallocCoherent) != hipSuccess) {
         (void)hipGetLastError();
         s->h_bits = nullptr;
         rc = NP_ENOMEM;
@@ -1591,6 +1584,8 @@ int nested_poisson_solve(np_solver* s, const double* const* rho, const double* p
     s->solved = false;
     int status = NP_OK;
     auto t_all = std::chrono::steady_clock::now();
+    // every read zeroes the slots it took; a solve that failed may have left some
+    launch_set_u64(s->stream, s->d_bits, kBitSlots, 0ULL);
     for (int gi = 0; gi < s->ngroups; gi++) {
         if (s->groups[gi].n > 1) {
             int rc = solve_batch(s, s->groups[gi], rho, fourpiG, st, status);
@@ -1605,7 +1600,6 @@ int nested_poisson_solve(np_solver* s, const double* const* rho, const double* p
         s->hist[l].clear();
         prof_begin(s, NP_KCLASS_FILL);
         // the fill also reduces max |f| into slot 2
-        launch_set_u64(s->stream, s->d_bits + 2, 1, 0ULL);
         if (l == 0) {
             launch_level0_init(d, s->stream, s->lg[0], rho[0], phi_outer, fourpiG, s->phi[0], s->f[0], s->d_bits + 2);
         } else {
@@ -1615,16 +1609,33 @@ int nested_poisson_solve(np_solver* s, const double* const* rho, const double* p
         }
         prof_end(s);
         HIPCHK(s, hipGetLastError());
-        HIPCHK(s, hipMemcpyAsync(s->h_bits + 2, s->d_bits + 2, sizeof(unsigned long long), hipMemcpyDeviceToHost,
-                                 s->stream));
-        HIPCHK(s, hipStreamSynchronize(s->stream));
-        const double fnorm = bits_to_double(s->h_bits[2]);
         int rc = NP_OK;
-        if (!std::isfinite(fnorm)) return set_err(s, NP_ENONFINITE, "level %d: non-finite density", l);
-        double scale = fnorm;
+        // with the defect correction the starting residual pass also keeps
+        // f - lap phi in FP32, the source of the level's first scaled defect
+        // (unless the learned guess changes phi after it)
+        const bool dc = c.precision != NP_PREC_FP64;
+        // the learned guess runs unless it was found not to pay on this level
+        const bool net = l > 0 && c.guess == NP_GUESS_LEARNED && s->have_weights && !(c.guess_gate && s->guess_off[l]);
+        const bool r32_start = dc && !net;
         // comparison scheme: Omega^l alone is relaxed, with the interpolated inner
         // buffer layer as its Dirichlet data; its |f| sets the stop test's scale
         const bool interp_buffer = l > 0 && c.buffer == NP_BUFFER_INTERP;
+        // the starting residual's norm (slot 0), read together with max |f|
+        const auto first_residual = [&]() -> int {
+            if (r32_start) return dc_first_residual(s, l);
+            norm_launch(s, l, 0);
+            return NP_OK;
+        };
+        if (!interp_buffer) {
+            rc = first_residual();
+            if (rc) return rc;
+        }
+        rc = read_slots(s, 0, 3);
+        if (rc) return rc;
+        double r = bits_to_double(s->h_bits[0]);
+        const double fnorm = bits_to_double(s->h_bits[2]);
+        if (!std::isfinite(fnorm)) return set_err(s, NP_ENONFINITE, "level %d: non-finite density", l);
+        double scale = fnorm;
         // last padded index of Omega^l in the relaxed domain's array, per axis
         const int box_hi[3] = {level_n(&c, l, 0) + 1, level_n(&c, l, 1) + 1, level_n(&c, l, 2) + 1};
         if (interp_buffer) {
@@ -1644,16 +1655,12 @@ int nested_poisson_solve(np_solver* s, const double* const* rho, const double* p
             if (rc) return rc;
             if (!std::isfinite(scale)) return set_err(s, NP_ENONFINITE, "level %d: non-finite boundary data", l);
         }
-        // with the defect correction the starting residual pass also keeps
-        // f - lap phi in FP32, the source of the level's first scaled defect
-        // (unless the learned guess changes phi after it)
-        const bool dc = c.precision != NP_PREC_FP64;
-        // the learned guess runs unless it was found not to pay on this level
-        const bool net = l > 0 && c.guess == NP_GUESS_LEARNED && s->have_weights && !(c.guess_gate && s->guess_off[l]);
-        const bool r32_start = dc && !net;
-        double r = 0.0;
-        rc = r32_start ? dc_first_residual(s, l, &r) : norm_sync(s, l, 0, &r);
-        if (rc) return rc;
+        if (interp_buffer) {
+            rc = first_residual();
+            if (rc) return rc;
+            rc = read_norm(s, 0, &r);
+            if (rc) return rc;
+        }
         st.interp_rel_residual[l] = scale > 0 ? r / scale : r;
         const double rho_p = l > 0 && s->rho_meas[c.parent[l]] > 0.0 ? s->rho_meas[c.parent[l]] : kAdaptiveRho0;
         double t_guess = 0.0;
@@ -1667,9 +1674,10 @@ int nested_poisson_solve(np_solver* s, const double* const* rho, const double* p
         }
         double Fdelta = 0.0;
         bool pinned = s->has_fixed && s->fixed[l] >= 0;
-        if (c.stop_rule == NP_STOP_FORCE_DELTA && !pinned) {
-            rc = force_delta_sync(s, l, &Fdelta);  // seeds the previous-force buffer
-            if (rc) return rc;
+        const bool fdelta = c.stop_rule == NP_STOP_FORCE_DELTA && !pinned;
+        if (fdelta) {
+            force_delta(s, l);  // seeds the previous-force buffer; the change is not used
+            launch_set_u64(s->stream, s->d_bits + 1, 1, 0ULL);
         }
         const double r0 = r;
         s->hist[l].push_back(scale > 0 ? r / scale : r);
@@ -1737,9 +1745,14 @@ int nested_poisson_solve(np_solver* s, const double* const* rho, const double* p
                     rho = m < 0.02 ? 0.02 : (m > 0.95 ? 0.95 : m);
                 }
             } else if (legs) {
-                rc = vcycle_legs_sync(s, l, &r);
+                rc = vcycle_legs(s, l, s->phi[l], s->f[l], mg_view<double>(s, l, s->mg_u, s->mg_f, s->mg_r), s->d_bits);
+                if (rc) return rc;
+                if (fdelta) force_delta(s, l);
+                rc = read_slots(s, 0, 2);
                 if (rc) return rc;
                 q++;
+                r = bits_to_double(s->h_bits[0]);
+                Fdelta = bits_to_double(s->h_bits[1]);
             } else if (fs) {
                 rc = vcycle_full(s, l, first_done);
                 if (rc) return rc;
@@ -1759,9 +1772,12 @@ int nested_poisson_solve(np_solver* s, const double* const* rho, const double* p
             s->hist[l].push_back(scale > 0 ? r / scale : r);
             if (!std::isfinite(r)) { lvl = NP_ENONFINITE; break; }
             if (r0 > 0 && r > 1e3 * r0) { lvl = NP_EDIVERGED; break; }
-            if (c.stop_rule == NP_STOP_FORCE_DELTA && !pinned) {
-                rc = force_delta_sync(s, l, &Fdelta);
-                if (rc) return rc;
+            if (fdelta) {
+                if (!legs) {
+                    force_delta(s, l);
+                    rc = read_norm(s, 1, &Fdelta);
+                    if (rc) return rc;
+                }
                 if (Fdelta < c.tol) break;
             }
         }

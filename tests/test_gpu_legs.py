@@ -104,3 +104,22 @@ def test_nested_2d(wl, kw):
 def test_large():
     # 260^3: streamed legs on the three largest levels, blocks below
     _same(W.c2_plummer(260, 1))
+
+
+def test_norms_after_a_failed_solve():
+    """A solve that ends early (non-finite density) leaves nothing behind in the norms of the
+    handle's next one."""
+    wl = W.c2_plummer(32)
+    rho, po = W.make_inputs(wl.geom, wl.prob, device="cuda")
+    ref, hist, cycles = _solve(wl)
+    s = NestedPoissonSolver(wl.geom)
+    bad = [r.clone() for r in rho]
+    bad[1][3, 4, 5] = float("nan")
+    with pytest.raises(Exception):
+        s.solve(bad, po)
+    st = s.solve(rho, po)
+    assert list(st["cycles"]) == cycles
+    assert [s.history(l) for l in range(wl.geom.nlevels)] == hist
+    for l in range(wl.geom.nlevels):
+        assert np.array_equal(s.potential(l).cpu().numpy(), ref[l])
+    s.close()
