@@ -363,7 +363,7 @@ int np_net_conv3d_fwd_round(const float* in, int cin, const unsigned short* w_bf
 /* A layer of the network on the matrix cores (the inference path), for
  * (cin, cout) = (2, 16), (16, 16) or (16, 1): bfloat16 activations in,
  * bfloat16 out (cout 16) or FP32 out (cout 1), FP32 accumulation
- * (v_mfma_f32_16x16x16 bf16); `in` aligned to 4 * cin bytes.  Other shapes:
+ * (v_mfma_f32_16x16x32 bf16); `in` aligned to 4 * cin bytes.  Other shapes:
  * NP_EINVAL. */
 int np_net_conv3d_fwd_mfma(const unsigned short* in_bf16, int cin, const unsigned short* w_bf16, const float* bias,
                            int cout, int relu, int batch, int nz, int ny, int nx, void* out, void* stream);

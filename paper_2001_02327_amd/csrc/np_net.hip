@@ -397,152 +397,196 @@ __global__ void k_lap7(const float* __restrict__ in, int B, int Z, int Y, int X,
 }
 
 // ------------------------------------------------------------------ inference on the matrix cores
-// Operand layout of v_mfma_f32_16x16x16 bf16: lane l supplies A[row l%16][k
-// 4(l/16)..+3] and B[k 4(l/16)..+3][col l%16], and receives D[rows
-// 4(l/16)..+3][col l%16].  Rows are 16 consecutive voxels along x, columns the
-// output channels.
-typedef short v4s __attribute__((ext_vector_type(4)));
+// v_mfma_f32_16x16x32 bf16: lane l = 16 q + r supplies A[row r][k 8q..+7] and
+// B[k 8q..+7][col r], and receives D[rows 4q..+3][col r].  Rows are output channels
+// (A: weights), columns 16 voxels along x (B: activations), so a lane ends with four
+// neighbouring channels of a voxel and a wavefront stores 16 voxels in one piece.
+typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
+typedef __bf16 v4bf __attribute__((ext_vector_type(4)));
 typedef float v4f __attribute__((ext_vector_type(4)));
+typedef unsigned v4u __attribute__((ext_vector_type(4)));
+typedef unsigned v2u __attribute__((ext_vector_type(2)));
 
-// Matrix-core convolution with the input block staged in LDS (the inference
-// path of all three layers).  A workgroup loads its weights once and then runs
-// a contiguous range of 16 (x) x 4 (y) x 4 (z) blocks of output voxels: for
-// each it copies the 18 x 6 x 6 input voxels around the block (zero outside the
-// volume) into LDS, and each of its 4 wavefronts produces 4 rows of 16 voxels,
-// taking the A operand of every tap from LDS, so that an input voxel is read
-// from memory about 2.5 times instead of 27.  The
-// K dimension of the products: CIN = 16, one tap's 16 channels per MFMA (27
-// products, in tap order); CIN = 2, (tap, channel) pairs,
-// 16 per MFMA (4 products, taps past 27 zero).  COUT = 1 pads the weight
-// columns with zeros and writes FP32; COUT = 16 writes bfloat16.
-constexpr int kCTx = 16, kCTy = 4, kCTz = 4;
-constexpr long kConvWorkgroups = 2048;
+// A layer of the inference path.  A wavefront owns 16 voxels along x and R rows and
+// marches along z with the outputs of three planes in flight: the input rows of
+// a plane come from memory straight into the B operand and are used for every
+// output that they reach (three planes, up to three rows), so nothing is staged in
+// LDS and no wavefront waits for another.  A row past an edge of the volume is a
+// buffer of no bytes and a voxel past it an offset outside its row: they read zero.
+//   CIN = 16: an input row is two operands, the taps dx = 0 and 1 (lanes q < 2 and
+//     q >= 2, 8 channels each) and the tap dx = 2 (the other half zero); 72 products
+//     per plane for 4 rows.
+//   CIN = 2: the three input rows of an output row are one operand (q: dy, then dx and
+//     channel; the fourth dx and q = 3 are zero): 12 products per plane.
+// COUT = 1 pads the weight rows with zeros and writes FP32; COUT = 16 writes bfloat16.
+//
+// What bounds it: with 16 input channels the matrix cores (316 GFLOP issued per 258^3
+// voxels, a third of it the zero halves and edges of blocks: 270 us at the 1.17 PFLOP/s
+// that a large bf16 product reaches here) and, as much, memory (64 or 36 B per voxel);
+// with 2 channels memory (36 B).  Measured, 2 -> 16 / 16 -> 16 / 16 -> 1 channels: 258^3
+// voxels 208 / 360 / 243 us, 66^3 8.7 / 11.3 / 9.5, 18^3 4.7 / 4.5 / 4.6 (blocks of 16 x 4 x 4
+// voxels staged in LDS, products of K = 16, a store per channel: 450 / 560 / 520,
+// 8.7 / 15 / 19, 4.9 / 5.7 / 6.5 us).
+constexpr int kCvWaves = 4;
+constexpr unsigned kCvOob = 0x80000000u;
+// With 16 input channels four rows per wavefront read 1.5 input rows per output row, two
+// rows 2, but two give twice the wavefronts: from this many pieces of 16 x 16 voxels on
+// four are faster (16 -> 16, two / four rows: 66^3 voxels, 1650 pieces, 11.1 / 12.7 us;
+// 130^3, 10530, 48.7 / 41.4 us).  With 2 channels the rows share nothing: two.
+constexpr long kCvLarge = 4096;
 
-template <int CIN, int COUT, typename TO>
-__global__ void __launch_bounds__(256) k_conv_mfma_lds(const uint16_t* __restrict__ in, const uint16_t* __restrict__ w,
-                                                      const float* __restrict__ bias, int relu, int B, int Z, int Y,
-                                                      int X, TO* __restrict__ out, long per_block)
+template <int CIN, int COUT, int R, typename TO>
+__global__ void __launch_bounds__(64 * kCvWaves, CIN == 16 ? 2 : 6)
+k_conv_mfma(const uint16_t* __restrict__ in, const uint16_t* __restrict__ w, const float* __restrict__ bias, int relu,
+            int Z, int Y, int X, TO* __restrict__ out, int ntx, int nty, int ntz, int kz)
 {
-    constexpr int SX = kCTx + 2, SY = kCTy + 2, SZ = kCTz + 2, NV = SX * SY * SZ;
-    constexpr int NMF = CIN == 16 ? 27 : 4;
-    // LDS stride per voxel in bfloat16 elements: 16 channels padded to 24 so that
-    // the 16 voxels of an A-operand read fall into different banks
-    constexpr int VS = CIN == 16 ? 24 : 2;
-    __shared__ __align__(16) uint16_t tile[NV * VS];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int row = lane & 15, kq = lane >> 4;
-    const int ntx = (X + kCTx - 1) / kCTx, nty = (Y + kCTy - 1) / kCTy, ntz = (Z + kCTz - 1) / kCTz;
-    const long ntiles = (long)B * ntz * nty * ntx;
-    // weights of the lane's B operand for every product (once per workgroup,
-    // which then runs a contiguous range of output blocks)
-    v4s bw[NMF];
+    constexpr int NA = CIN == 16 ? 18 : 3;           // A operands: (dz, dy, half) or dz
+    constexpr int NF = CIN == 16 ? 2 * (R + 2) : R;  // B operands of a plane
+    const int lane = threadIdx.x & 63, r = lane & 15, q = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    int t = (int)blockIdx.x;
+    const int bx = t % ntx;
+    t /= ntx;
+    const int by = t % nty;
+    t /= nty;
+    const int bz = t % ntz, b = t / ntz;
+    const int x0 = 16 * bx, y0 = R * (kCvWaves * by + wave), z0 = kz * bz, z1 = min(z0 + kz, Z) - 1;
+    if (y0 >= Y) return;
+    const bool wide = ((uintptr_t)out & 7) == 0;  // a voxel's four channels in one store
+
+    // byte offsets of the lane's voxels: CIN = 16 in an input row, CIN = 2 in the rows of a
+    // plane that the wavefront reads (voxels x0 + r - 1 .. + 2 of row y0 + j - 1 + q)
+    constexpr int VB = CIN * 2;
+    const unsigned row_bytes = (unsigned)X * VB;
+    const auto x_off = [&](int x, bool on) -> unsigned { return on && x >= 0 && x < X ? (unsigned)(x * VB) : kCvOob; };
+    const unsigned o01 = x_off(x0 + r - 1 + (q >> 1), true) + 16 * (q & 1), o2 = x_off(x0 + r + 1, q < 2) + 16 * (q & 1);
+    const bool x_edge = x0 == 0 || x0 + 18 > X;
+    const auto load = [&](v4u (&f)[NF], int iz) {
+        const bool zin = iz >= 0 && iz < Z;
+        const uint16_t* const plane = in + ((long)b * Z + iz) * (long)Y * X * CIN;
+        if constexpr (CIN == 16) {
 #pragma unroll
-    for (int sI = 0; sI < NMF; sI++) {
-#pragma unroll
-        for (int e = 0; e < 4; e++) {
-            int t, c;
-            if (CIN == 16) {
-                t = sI;
-                c = 4 * kq + e;
-            } else {
-                t = 8 * sI + 2 * kq + (e >> 1);
-                c = e & 1;
+            for (int j = 0; j < R + 2; j++) {
+                const int iy = y0 - 1 + j;
+                const auto rs = __builtin_amdgcn_make_buffer_rsrc((void*)(plane + (long)iy * X * CIN), 0,
+                                                                  zin && iy >= 0 && iy < Y ? (int)row_bytes : 0, 0x00027000);
+                f[2 * j] = __builtin_amdgcn_raw_buffer_load_b128(rs, o01, 0, 0);
+                f[2 * j + 1] = __builtin_amdgcn_raw_buffer_load_b128(rs, o2, 0, 0);
             }
-            bw[sI][e] = (row < COUT && t < 27) ? (short)w[(t * COUT + row) * CIN + c] : (short)0;
+        } else {
+            const int yb = max(y0 - 1, 0), ny = min(y0 + R + 1, Y) - yb;
+            const auto rs = __builtin_amdgcn_make_buffer_rsrc((void*)(plane + (long)yb * X * CIN), 0,
+                                                              zin ? (int)(row_bytes * ny) : 0, 0x00027000);
+#pragma unroll
+            for (int j = 0; j < R; j++) {
+                const int iy = y0 + j - 1 + q;
+                const bool yin = q < 3 && iy >= 0 && iy < Y;
+                if (x_edge) {
+#pragma unroll
+                    for (int e = 0; e < 3; e++) {
+                        const unsigned o = x_off(x0 + r - 1 + e, yin);
+                        f[j][e] = __builtin_amdgcn_raw_buffer_load_b32(rs, o == kCvOob ? o : o + (unsigned)(iy - yb) * row_bytes, 0, 0);
+                    }
+                } else {
+                    // (the fourth voxel, outside the taps, is dropped before the product)
+                    f[j] = __builtin_amdgcn_raw_buffer_load_b128(
+                        rs, yin ? (unsigned)(iy - yb) * row_bytes + (unsigned)(x0 + r - 1) * VB : kCvOob, 0, 0);
+                }
+            }
         }
+    };
+    v4u fa[NF], fb[NF];
+    load(fa, z0 - 1);
+    load(fb, z0);
+
+    // weights [tap][cout][cin]; the rows of channels past COUT zero
+    v8bf aw[NA];
+    const int wr = min(r, COUT - 1);
+#pragma unroll
+    for (int a = 0; a < NA; a++) {
+        v4u u = {0, 0, 0, 0};
+        if constexpr (CIN == 16) {
+            const int tap = (a >> 1) * 3 + ((a & 1) ? 2 : q >> 1);  // a >> 1 = 3 dz + dy
+            __builtin_memcpy(&u, w + (tap * COUT + wr) * 16 + 8 * (q & 1), 16);
+            if ((a & 1) && q >= 2) u = v4u{0, 0, 0, 0};
+        } else {
+            for (int dx = 0; dx < 3; dx++) __builtin_memcpy((char*)&u + 4 * dx, w + ((9 * a + 3 * min(q, 2) + dx) * COUT + wr) * 2, 4);
+            if (q == 3) u = v4u{0, 0, 0, 0};
+        }
+        if (r >= COUT) u = v4u{0, 0, 0, 0};
+        aw[a] = __builtin_bit_cast(v8bf, u);
     }
-    const float bo = row < COUT ? bias[row] : 0.0f;
-    const long first = (long)blockIdx.x * per_block;
-    const long last = first + per_block < ntiles ? first + per_block : ntiles;
-    for (long bid = first; bid < last; bid++) {
-        long rem = bid;
-        const int bx = (int)(rem % ntx);
-        rem /= ntx;
-        const int by = (int)(rem % nty);
-        rem /= nty;
-        const int bz = (int)(rem % ntz);
-        const int b = (int)(rem / ntz);
-        const int x0 = bx * kCTx, y0 = by * kCTy, z0 = bz * kCTz;
-        __syncthreads();  // the previous block's operands have been read
-        // stage the input block
-        for (int v = threadIdx.x; v < NV; v += 256) {
-            const int lx = v % SX, ly = (v / SX) % SY, lz = v / (SX * SY);
-            const int gx = x0 - 1 + lx, gy = y0 - 1 + ly, gz = z0 - 1 + lz;
-            const bool inside = gx >= 0 && gx < X && gy >= 0 && gy < Y && gz >= 0 && gz < Z;
-            const uint16_t* src = in + ((((long)b * Z + gz) * Y + gy) * X + gx) * CIN;
-            if (CIN == 16) {
-                uint4 q0 = make_uint4(0, 0, 0, 0), q1 = q0;
-                if (inside) {
-                    q0 = ((const uint4*)src)[0];
-                    q1 = ((const uint4*)src)[1];
-                }
-                ((uint4*)(tile + v * VS))[0] = q0;
-                ((uint4*)(tile + v * VS))[1] = q1;
+    float bo[4];
+#pragma unroll
+    for (int k = 0; k < 4; k++) bo[k] = 4 * q + k < COUT ? bias[4 * q + k] : 0.0f;
+
+    // outputs of planes iz - 1, iz and iz + 1
+    v4f acc[3][R];
+#pragma unroll
+    for (int s = 0; s < 3; s++)
+#pragma unroll
+        for (int y = 0; y < R; y++) acc[s][y] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+    const auto plane = [&](v4u (&f)[NF], int iz) {
+        if constexpr (CIN == 2) {
+#pragma unroll
+            for (int y = 0; y < R; y++) f[y][3] = 0;
+        }
+#pragma unroll
+        for (int s = 0; s < 3; s++) {
+            if (iz - 1 + s < z0 || iz - 1 + s > z1) continue;  // another workgroup's plane
+            if constexpr (CIN == 16) {
+#pragma unroll
+                for (int j = 0; j < R + 2; j++)
+#pragma unroll
+                    for (int h = 0; h < 2; h++)
+#pragma unroll
+                        for (int dy = 0; dy < 3; dy++) {
+                            const int y = j - dy;
+                            if (y < 0 || y >= R) continue;
+                            acc[s][y] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aw[2 * (3 * (2 - s) + dy) + h],
+                                                                                 __builtin_bit_cast(v8bf, f[2 * j + h]),
+                                                                                 acc[s][y], 0, 0, 0);
+                        }
             } else {
-                ((uint32_t*)tile)[v] = inside ? *(const uint32_t*)src : 0u;
+#pragma unroll
+                for (int y = 0; y < R; y++)
+                    acc[s][y] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aw[2 - s], __builtin_bit_cast(v8bf, f[y]), acc[s][y],
+                                                                         0, 0, 0);
             }
         }
-        __syncthreads();
-        // A operand of product sI for the wave's output row it (rows of 16 voxels
-        // at (y0 + ly, z0 + lz)); rows outside the volume read zeros and are not stored
-        auto afrag = [&](int it, int sI) -> v4s {
-            const int rid = wave * 4 + it;
-            const int ly = rid % kCTy, lz = rid / kCTy;
-            if (CIN == 16) {
-                const int dz = sI / 9, dy = (sI / 3) % 3, dx = sI % 3;
-                const int lv = ((lz + dz) * SY + (ly + dy)) * SX + (row + dx);
-                return *(const v4s*)(tile + lv * VS + 4 * kq);
+        const int z = iz - 1, x = x0 + r;
+#pragma unroll
+        for (int y = 0; y < R; y++) {
+            const bool on = z >= z0 && z <= z1 && y0 + y < Y;
+            TO* const row = out + (((long)b * Z + z) * Y + y0 + y) * (long)X * COUT;
+            float v[4];
+#pragma unroll
+            for (int k = 0; k < 4; k++) {
+                v[k] = acc[0][y][k] + bo[k];
+                if (relu) v[k] = fmaxf(v[k], 0.0f);
             }
-            short e4[4] = {0, 0, 0, 0};
-    #pragma unroll
-            for (int h = 0; h < 2; h++) {
-                const int t = 8 * sI + 2 * kq + h;
-                if (t < 27) {
-                    const int dz = t / 9, dy = (t / 3) % 3, dx = t % 3;
-                    const int lv = ((lz + dz) * SY + (ly + dy)) * SX + (row + dx);
-                    const uint32_t pr = ((const uint32_t*)tile)[lv];
-                    e4[2 * h] = (short)(pr & 0xffffu);
-                    e4[2 * h + 1] = (short)(pr >> 16);
-                }
+            const auto rs = __builtin_amdgcn_make_buffer_rsrc((void*)row, 0, on ? (int)(X * COUT * sizeof(TO)) : 0, 0x00027000);
+            if constexpr (COUT == 1) {
+                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v[0]), rs, q == 0 && x < X ? (unsigned)x * 4 : kCvOob, 0, 0);
+            } else if (wide) {
+                const v4bf u = {(__bf16)v[0], (__bf16)v[1], (__bf16)v[2], (__bf16)v[3]};
+                __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(v2u, u), rs, x < X ? (unsigned)(x * 32 + 8 * q) : kCvOob, 0, 0);
+            } else if (on && x < X) {
+#pragma unroll
+                for (int k = 0; k < 4; k++) st(row + x * COUT + 4 * q + k, v[k]);
             }
-            return v4s{e4[0], e4[1], e4[2], e4[3]};
-        };
-        auto store = [&](int it, const v4f& acc) {
-            const int rid = wave * 4 + it;
-            const int y = y0 + rid % kCTy, z = z0 + rid / kCTy;
-            if (y >= Y || z >= Z) return;
-            // lane holds D[voxels 4 kq .. 4 kq + 3][channel row]
-            const long base = (((long)b * Z + z) * Y + y) * X;
-            for (int q = 0; q < 4; q++) {
-                const int x = x0 + 4 * kq + q;
-                if (x >= X || row >= COUT) continue;
-                float v = acc[q] + bo;
-                if (relu) v = fmaxf(v, 0.0f);
-                st(out + (base + x) * COUT + row, v);
-            }
-        };
-        // two rows at a time on two independent accumulation chains; the A
-        // operands of a plane of taps (9 products) are read before its products
-        for (int p = 0; p < 4; p += 2) {
-            v4f acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = acc0;
-            constexpr int G = CIN == 16 ? 9 : NMF;
-    #pragma unroll
-            for (int g0 = 0; g0 < NMF; g0 += G) {
-                v4s a0[G], a1[G];
-    #pragma unroll
-                for (int q = 0; q < G; q++) {
-                    a0[q] = afrag(p, g0 + q);
-                    a1[q] = afrag(p + 1, g0 + q);
-                }
-    #pragma unroll
-                for (int q = 0; q < G; q++) {
-                    acc0 = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a0[q], bw[g0 + q], acc0, 0, 0, 0);
-                    acc1 = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a1[q], bw[g0 + q], acc1, 0, 0, 0);
-                }
-            }
-            store(p, acc0);
-            store(p + 1, acc1);
+            acc[0][y] = acc[1][y];
+            acc[1][y] = acc[2][y];
+            acc[2][y] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
         }
+    };
+    for (int iz = z0 - 1;; iz += 2) {
+        plane(fa, iz);
+        if (iz > z1) break;
+        load(fa, iz + 2);
+        plane(fb, iz + 1);
+        if (iz + 1 > z1) break;
+        load(fb, iz + 3);
     }
 }
 
@@ -1271,19 +1315,40 @@ void net_conv_fwd_bf16_to_f32(hipStream_t st, const uint16_t* in, int cin, const
 void net_conv_mfma(hipStream_t st, const uint16_t* in, int cin, const uint16_t* w, const float* bias, int cout, int relu,
                    int B, int Z, int Y, int X, void* out)
 {
-    const long tiles = (long)B * ((Z + kCTz - 1) / kCTz) * ((Y + kCTy - 1) / kCTy) * ((X + kCTx - 1) / kCTx);
-    // persistent workgroups, each over a contiguous range of output blocks
-    const long per = (tiles + kConvWorkgroups - 1) / kConvWorkgroups;
-    const dim3 grid((unsigned)((tiles + per - 1) / per));
-    if (cin == 16 && cout == 16)
-        hipLaunchKernelGGL((k_conv_mfma_lds<16, 16, uint16_t>), grid, dim3(256), 0, st, in, w, bias, relu, B, Z, Y, X,
-                           (uint16_t*)out, per);
-    else if (cin == 2 && cout == 16)
-        hipLaunchKernelGGL((k_conv_mfma_lds<2, 16, uint16_t>), grid, dim3(256), 0, st, in, w, bias, relu, B, Z, Y, X,
-                           (uint16_t*)out, per);
-    else if (cin == 16 && cout == 1)
-        hipLaunchKernelGGL((k_conv_mfma_lds<16, 1, float>), grid, dim3(256), 0, st, in, w, bias, relu, B, Z, Y, X,
-                           (float*)out, per);
+    const auto launch = [&](auto ci, auto co, auto rows, auto* o, int per_cu) {
+        constexpr int R = decltype(rows)::value;
+        const int ntx = cdiv(X, 16), nty = cdiv(Y, R * kCvWaves);
+        // planes per workgroup: a range reads two more than its own, the ranges run in
+        // rounds of per_cu workgroups per CU
+        const long cols = (long)ntx * nty * B, slots = 256L * per_cu;
+        int kz = Z;
+        long best = 0;
+        for (int n = 1; n <= Z; n++) {
+            const int k = (Z + n - 1) / n;
+            const long cost = (cols * ((Z + k - 1) / k) + slots - 1) / slots * (k + 2);
+            if (n == 1 || cost < best) {
+                best = cost;
+                kz = k;
+            }
+        }
+        const int ntz = (Z + kz - 1) / kz;
+        hipLaunchKernelGGL((k_conv_mfma<decltype(ci)::value, decltype(co)::value, R, std::remove_pointer_t<decltype(o)>>),
+                           dim3((unsigned)(cols * ntz)), dim3(64 * kCvWaves), 0, st, in, w, bias, relu, Z, Y, X, o, ntx, nty,
+                           ntz, kz);
+    };
+    const auto go = [&](auto ci, auto co, auto* o, int per_cu) {
+        if constexpr (decltype(ci)::value == 16) {
+            if ((long)B * Z * cdiv(X, 16) * cdiv(Y, 16) >= kCvLarge)
+                return launch(ci, co, std::integral_constant<int, 4>{}, o, per_cu);
+        }
+        launch(ci, co, std::integral_constant<int, 2>{}, o, per_cu);
+    };
+    using C1 = std::integral_constant<int, 1>;
+    using C2 = std::integral_constant<int, 2>;
+    using C16 = std::integral_constant<int, 16>;
+    if (cin == 16 && cout == 16) go(C16{}, C16{}, (uint16_t*)out, 2);
+    else if (cin == 2 && cout == 16) go(C2{}, C16{}, (uint16_t*)out, 4);
+    else if (cin == 16 && cout == 1) go(C16{}, C1{}, (float*)out, 2);
 }
 
 void net_conv_bwd_data(hipStream_t st, const float* gout, int cout, const uint16_t* w, int cin, int B, int Z, int Y,
