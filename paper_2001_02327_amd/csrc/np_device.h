@@ -68,11 +68,11 @@ __device__ __forceinline__ int zmarch_block(int rev)
 // DPP wave shift; lane 0 (previous) and lane 63 (next) get 0.
 __device__ __forceinline__ unsigned dpp_prev(unsigned v)
 {
-    return (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x138, 0xf, 0xf, false);  // wave_shr:1
+    return (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x138, 0xf, 0xf, true);  // wave_shr:1
 }
 __device__ __forceinline__ unsigned dpp_next(unsigned v)
 {
-    return (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x130, 0xf, 0xf, false);  // wave_shl:1
+    return (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x130, 0xf, 0xf, true);  // wave_shl:1
 }
 __device__ __forceinline__ float dpp_prev(float x) { return __uint_as_float(dpp_prev(__float_as_uint(x))); }
 __device__ __forceinline__ float dpp_next(float x) { return __uint_as_float(dpp_next(__float_as_uint(x))); }

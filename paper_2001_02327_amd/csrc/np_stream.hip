@@ -94,13 +94,21 @@ __device__ __forceinline__ double leg_load(__amdgpu_buffer_rsrc_t b, unsigned of
     return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(b, off, 0, 0));
 }
 
-// rule_pair without branches on the rule's kind
+// rule_pair without branches; ql: the index for the test of the lower wall
 template <typename C>
-__device__ __forceinline__ void leg_rule(int q, int N, C self, C& lo, C& hi, const GRule<C>& gr, int ax)
+__device__ __forceinline__ void leg_rule(int ql, int q, int N, C self, C& lo, C& hi, const GRule<C>& gr, int ax)
 {
-    lo = q == 1 ? -self : lo;
+    lo = ql == 1 ? -self : lo;
     const C up = (gr.xn1[ax] ? (C)-1 : gr.coef[ax]) * (gr.xn1[ax] ? lo : self);
     hi = q == N ? up : hi;
+}
+
+// m ? a : b without a branch around what forms a (the compiler made one of every select
+// in the steps beside a boundary, which took half as long again as the others)
+__device__ __forceinline__ double leg_select(bool m, double a, double b)
+{
+    asm volatile("" : "+v"(a));
+    return m ? a : b;
 }
 
 typedef unsigned LegV2 __attribute__((ext_vector_type(2)));
@@ -314,11 +322,16 @@ __global__ void __launch_bounds__(S::NT) k_leg3(LegArgs A)
     }
 
     const auto step = [&](auto edge_tag, auto par_tag, int a, const Feed& q, C (&ep)[NE]) {
-        constexpr bool E = decltype(edge_tag)::value;
+        // 0: every point of the step is inside the level; 1: in x and y some are not; 2: nor in z
+        constexpr int E = decltype(edge_tag)::value;
         // x = 2 hg + par for every stage of this step in the first row, the other point in the second
         constexpr int par = decltype(par_tag)::value;
         constexpr int pa1 = (par + S::H) & 1;  // parity of a
         constexpr int dx = par ? 1 : -1;
+        // (tests against a wall are formed in each step: kept as masks they are more than the
+        // scalar registers hold)
+        int Nx_ = Nx, Ny_ = Ny;
+        asm volatile("" : "+s"(Nx_), "+s"(Ny_));
         bool mx[2];
         unsigned so[2], soo[2];
         int pi[2];
@@ -343,8 +356,9 @@ __global__ void __launch_bounds__(S::NT) k_leg3(LegArgs A)
 #pragma unroll
         for (int i = ZERO ? 1 : 0; i < NS; i++) {
             const C* const P = ((i & 1) ? pb : pa) + (i == 0 ? 0 : 2 * (X0A + i - 1)) * PL;
-            lx[i][0] = P[dx];
-            lx[i][1] = P[S::NTH - dx];
+            const C (&c)[2] = i == 0 ? b0c : x1[i > 0 ? i - 1 : 0];
+            lx[i][0] = dx > 0 ? dpp_next(c[0]) : dpp_prev(c[0]);
+            lx[i][1] = dx > 0 ? dpp_prev(c[1]) : dpp_next(c[1]);
             ly[i] = P[S::NTH - S::HC];
             lz[i] = P[S::HC];
         }
@@ -385,9 +399,8 @@ __global__ void __launch_bounds__(S::NT) k_leg3(LegArgs A)
                     const bool od = r ? !par : par;
                     const C vc = od ? v1c[r] : v0c[r], vn = od ? v1n[r] : v0n[r];
                     const C e = pa1 ? prolong34(vc, vn) : prolong34(vn, vc);
-                    const C v = (b0p[r] + e);
-                    if constexpr (E) b0p[r] = mx[r] && z >= 1 && z <= Nz ? v : (RULE ? (C)0 : q.gb[r]);
-                    else b0p[r] = v;
+                    b0p[r] = b0p[r] + e;
+                    if constexpr (E && !RULE) b0p[r] = leg_select(mx[r] && (E == 1 || (z >= 1 && z <= Nz)), b0p[r], q.gb[r]);
                     if constexpr (E && RULE) {
                         // the start's red point of plane a (the first half sweep's ghost values need it)
                         red0[r] = (q.r[r] + ered[r]);
@@ -411,13 +424,20 @@ __global__ void __launch_bounds__(S::NT) k_leg3(LegArgs A)
                 z1[r] = zp[r];
             }
             if constexpr (E && RULE) {
-                // by wavefront: most hold no point beside a wall
-                if (wall_x)
-                    for (int r = 0; r < 2; r++) leg_rule(pi[r], Nx, me[r], xm[r], xp[r], A.gr, 0);
-                if (wall_y)
-                    for (int r = 0; r < 2; r++) leg_rule(pj + r, Ny, me[r], y0[r], y1[r], A.gr, 1);
-                if (p == 1 || p == Nz)
-                    for (int r = 0; r < 2; r++) leg_rule(p, Nz, me[r], z0[r], z1[r], A.gr, 2);
+                // by wavefront: many hold no point beside a wall (the lower ones are odd)
+                if (wall_x) {
+#pragma unroll
+                    for (int r = 0; r < 2; r++) leg_rule((r ? !par : par) ? pi[r] : 0, pi[r], Nx_, me[r], xm[r], xp[r], A.gr, 0);
+                }
+                if (wall_y) {
+#pragma unroll
+                    for (int r = 0; r < 2; r++)
+                        leg_rule(((1 + S::H + r) & 1) ? pj + r : 0, pj + r, Ny_, me[r], y0[r], y1[r], A.gr, 1);
+                }
+                if (E == 2 && (p == 1 || p == Nz)) {
+#pragma unroll
+                    for (int r = 0; r < 2; r++) leg_rule(p, p, Nz, me[r], z0[r], z1[r], A.gr, 2);
+                }
             }
 #pragma unroll
             for (int r = 0; r < 2; r++) {
@@ -438,7 +458,6 @@ __global__ void __launch_bounds__(S::NT) k_leg3(LegArgs A)
 #pragma unroll
                 for (int r = 0; r < 2; r++) {
                     xn[0][r] = ((C)0 - A.h2 * frh[0][r]) * A.inv2d;
-                    if constexpr (E) xn[0][r] = mx[r] && zin ? xn[0][r] : (C)0;
                 }
                 continue;
             }
@@ -453,10 +472,8 @@ __global__ void __launch_bounds__(S::NT) k_leg3(LegArgs A)
             for (int r = 0; r < 2; r++) {
                 const C fv = (i & 1) ? fbh[i > 0 ? i - 1 : 0][r] : frh[i][r];
                 C v = fma_t(-A.h2, fv, s[r]) * A.inv2d;
-                if constexpr (E) {
-                    const C keep = i == 0 ? q.r[r] : old[r];
-                    v = mx[r] && zin ? v : (RULE ? (C)0 : keep);
-                }
+                // (with a rule what stands outside the level is read by no point inside)
+                if constexpr (E && !RULE) v = leg_select(mx[r] && (E == 1 || zin), v, i == 0 ? q.r[r] : old[r]);
                 xn[i][r] = v;
             }
             if (i == NX - 1 && RES) {
@@ -467,7 +484,7 @@ __global__ void __launch_bounds__(S::NT) k_leg3(LegArgs A)
                 for (int r = 0; r < 2; r++) {
                     const C fv = fbh[NX - 2][r];
                     sb[r] = fma_t(-A.inv_h2, fma_t((C)-6, xn[i][r], s2[r]), fv);
-                    if constexpr (E) sb[r] = mx[r] && zin ? sb[r] : (C)0;
+                    if constexpr (E && !UP) sb[r] = leg_select(mx[r] && (E == 1 || zin), sb[r], (C)0);
                 }
             }
         }
@@ -481,7 +498,7 @@ __global__ void __launch_bounds__(S::NT) k_leg3(LegArgs A)
 #pragma unroll
             for (int r = 0; r < 2; r++) {
                 rr[r] = fma_t(-A.inv_h2, fma_t((C)-6, x2[NX - 2][r], s[r]), frh[NX][r]);
-                if constexpr (E) rr[r] = mx[r] && zin ? rr[r] : (C)0;
+                if constexpr (E && !UP) rr[r] = leg_select(mx[r] && (E == 1 || zin), rr[r], (C)0);
                 if constexpr (UP) {
                     if (p >= Z0 && p <= Z1) {
                         if (so[r] != kLegOob) best = max(best, abs_bits((double)rr[r]));
@@ -580,15 +597,15 @@ __global__ void __launch_bounds__(S::NT) k_leg3(LegArgs A)
     using P0 = std::integral_constant<int, (S::H + kStepPar) & 1>;
     using P1 = std::integral_constant<int, (S::H + kStepPar + 1) & 1>;
     // steps between a load and its use: three, two where registers are short
-    constexpr int LEAD = sizeof(C) == 8 && N == 2 ? 2 : 3;
+    constexpr int LEAD = N == 2 ? 2 : 3;
     Feed q0, q1, q2, q3;
     load(P0{}, q0, as);
     load(P1{}, q1, as + 1);
     if constexpr (LEAD == 3) load(P0{}, q2, as + 2);
     const auto any_step = [&](auto par_tag, int a, const Feed& q, C (&ep)[NE]) {
-        // every stage of the step inside the level
-        if (!edge && a - NX >= 2 && a + 1 < Nz) step(std::false_type{}, par_tag, a, q, ep);
-        else step(std::true_type{}, par_tag, a, q, ep);
+        if (a - NX < 2 || a + 1 >= Nz) step(std::integral_constant<int, 2>{}, par_tag, a, q, ep);
+        else if (edge) step(std::integral_constant<int, 1>{}, par_tag, a, q, ep);
+        else step(std::integral_constant<int, 0>{}, par_tag, a, q, ep);
     };
     const auto next = [&](auto par_tag, Feed& two, Feed& three, int a) {
         if constexpr (LEAD == 3) load(std::integral_constant<int, 1 - decltype(par_tag)::value>{}, three, a + 3);
@@ -617,10 +634,10 @@ __global__ void __launch_bounds__(S::NT) k_leg3(LegArgs A)
 // a CU takes; the halo's share of the work is least (1.3 to 1.7 times the points).
 template <int H>
 struct LegPick;
-template <> struct LegPick<2> { using S = LegShape<2, 40, 40>; };
-template <> struct LegPick<3> { using S = LegShape<3, 40, 38>; };
-template <> struct LegPick<4> { using S = LegShape<4, 36, 36>; };
-template <> struct LegPick<5> { using S = LegShape<5, 36, 34>; };
+template <> struct LegPick<2> { using S = LegShape<2, 58, 28>; };
+template <> struct LegPick<3> { using S = LegShape<3, 58, 26>; };
+template <> struct LegPick<4> { using S = LegShape<4, 54, 24>; };
+template <> struct LegPick<5> { using S = LegShape<5, 54, 22>; };
 
 // Planes per chunk: a chunk takes its planes and `extra` steps (filling the pipeline,
 // the halo), the workgroups run in rounds of one per CU.
