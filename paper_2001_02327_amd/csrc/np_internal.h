@@ -223,8 +223,8 @@ bool level_tile(int dim, const SGrid& g);
 // colours.  u_out must not be u_in (with rule u_in is not read)
 template <typename T>
 void launch_level_down(hipStream_t st, const LevelLeg& a, int n_pre, bool rule, const T* u_in, const T* f, T* u_out, T* fc);
-void launch_stream_down(hipStream_t st, const LevelLeg& a, int n_pre, bool rule, const double* u_in, const double* f,
-                        double* u_out, double* fc);
+template <typename T>
+void launch_stream_down(hipStream_t st, const LevelLeg& a, int n_pre, bool rule, const T* u_in, const T* f, T* u_out, T* fc);
 template <typename T>
 void launch_tile2_down(hipStream_t st, const LevelLeg& a, int n_pre, bool rule, const T* u_in, const T* f, T* u_out, T* fc);
 // u_in (as launch_level_down left it) plus the prolonged ec, n_post sweeps, into u_out
@@ -234,8 +234,9 @@ void launch_tile2_down(hipStream_t st, const LevelLeg& a, int n_pre, bool rule, 
 template <typename T>
 void launch_level_up(hipStream_t st, const LevelLeg& a, int n_post, bool rule, const T* u_in, const T* ring, const T* f,
                      T* u_out, const T* ec, unsigned long long* maxbits);
-void launch_stream_up(hipStream_t st, const LevelLeg& a, int n_post, bool rule, const double* u_in, const double* ring,
-                      const double* f, double* u_out, const double* ec, unsigned long long* maxbits);
+template <typename T>
+void launch_stream_up(hipStream_t st, const LevelLeg& a, int n_post, bool rule, const T* u_in, const T* ring, const T* f,
+                      T* u_out, const T* ec, unsigned long long* maxbits);
 template <typename T>
 void launch_tile2_up(hipStream_t st, const LevelLeg& a, int n_post, bool rule, const T* u_in, const T* ring, const T* f,
                      T* u_out, const T* ec, unsigned long long* maxbits);

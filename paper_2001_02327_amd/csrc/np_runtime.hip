@@ -535,8 +535,13 @@ int tail_level(const np_solver* s, int l, size_t esz)
 
 // First multigrid level of nested level l that runs as fused legs, as do the levels
 // from there to the coarse tail; nmg if none does.  FP64: every level (level 0
-// too), the mixed precisions: the coarse levels that the block form serves (their
-// larger levels are as fast or faster per pass, and level 0 is stored in 16 bits).
+// too).  The mixed precisions (level 0 is stored in 16 bits, or starts from its defect):
+// the coarse levels, from the first one on if that has 2^23 points, otherwise from the
+// first one on that the block form serves.  FP32 per cycle, streamed / per pass: 257^3
+// points V(2,1) 127 / 184 us, V(1,1) 113 / 141, V(1,2) 162 / 181; 129^3 47.5 / 45.5, 36.5 /
+// 34.6, 59 / 47; together the larger one decides.
+constexpr size_t kStreamPoints32 = 1 << 23;
+
 int legs_level(const np_solver* s, int l)
 {
     const int nmg = s->plan.nmg[l];
@@ -546,6 +551,8 @@ int legs_level(const np_solver* s, int l)
     if (Lt == 0) return nmg;
     // (the streamed form addresses a plane of a colour by 31 bits)
     if (fp64) return s->cfg.dim == 2 || s->lg[l].ps * sizeof(double) < (1ULL << 31) ? 0 : nmg;
+    const SGrid g = mg_grid(s, l, 1);
+    if (s->cfg.dim == 3 && (size_t)g.nx * g.ny * g.nz >= kStreamPoints32 && Lt > 1) return 1;
     for (int L = 1; L < Lt; L++)
         if (level_tile(s->cfg.dim, mg_grid(s, l, L))) return L;
     return nmg;

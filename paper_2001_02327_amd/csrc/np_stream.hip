@@ -1,7 +1,8 @@
-// Fused V-cycle legs of a large 3-D multigrid level in FP64 (gfx950).
+// Fused V-cycle legs of a large 3-D multigrid level (gfx950): FP64, and the largest coarse
+// levels in FP32.
 //
 // A V(2,1) cycle in kernels that each make one pass over the level moves 89 B per
-// point, where 36 B would do.  Here a whole leg of the cycle is one launch:
+// point in FP64, where 36 B would do.  Here a whole leg of the cycle is one launch:
 //   down: the pre-smoothing sweeps, the residual and its restriction;
 //   up:   the prolongation and correction, the post-smoothing sweeps and on
 //         multigrid level 0 (for the stop test) the residual's max norm.
@@ -27,13 +28,13 @@
 // of the per-pass kernels (np_kernels.hip), so the iterates are the same bit for
 // bit.
 //
-// What bounds it: memory on the large levels, the issue of a step's instructions and
-// its barrier (1 us) on levels with few steps.  Measured, V(2,1) on 514^3
-// points: down 0.88 ms (18 B per point, 2.8 TB/s beside the halo's re-reads) and up
-// 0.90 ms (21 B, 3.2 TB/s) against 2.79 ms in full sweeps, restriction and
-// prolongation; 258^3 123 + 124 us against 419; 130^3 35 + 29 against 87.
-// Planes loaded one step ahead instead of three, behind branches on what a step
-// needs: 1.15 and 1.03 ms at 514^3.
+// What bounds it: a step is some 200 instructions per wavefront, 25 LDS accesses and a
+// barrier, with the registers of two wavefronts per SIMD in FP64: 1.2 to 1.4 us, and the
+// columns along the boundary, whose steps are the longest, decide; at 514^3 points the
+// memory system as much.  Measured, V(2,1) in FP64, down + up: 514^3 729 + 816 us (18 and 21 B
+// per point: 3.4 and 3.5 TB/s) against 2.79 ms in full sweeps, restriction and prolongation;
+// 258^3 107 + 114 us against 419; 130^3 32 + 26 against 87; coarse 129^3 35 + 22 against 80.
+// FP32, two workgroups per CU: coarse 257^3 67 + 60 us against 184.
 #include <algorithm>
 #include <type_traits>
 
@@ -60,19 +61,20 @@ struct LegShape {
     static constexpr int NT = (NTH + 63) / 64 * 64;
     static constexpr int PAD = HC + 1;           // a neighbour read beside the region stays in LDS
     static constexpr int CX = HC + 1, CY = RY / 2 + 2;  // coarse points under the region
-    static_assert(NT <= 1024 && RY % 2 == 0, "two rows per thread");
+    static_assert(HC == 32 && NT == NTH && RY % 2 == 0, "whole rows per wavefront, two rows per thread");
 };
 
+template <typename T>
 struct LegArgs {
-    const double* u_in;  // the state the leg starts from (up: the down leg's result)
-    const double* ring;  // up, multigrid level 0: the ghost layer
-    const double* f;
-    double* u_out;
-    double* fc;          // down: coarse right-hand side
-    const double* ec;    // up: coarse correction
+    const T* u_in;  // the state the leg starts from (up: the down leg's result)
+    const T* ring;  // up, multigrid level 0: the ghost layer
+    const T* f;
+    T* u_out;
+    T* fc;          // down: coarse right-hand side
+    const T* ec;    // up: coarse correction
     SGrid g, gc;
-    double h2, inv2d, inv_h2, scale;
-    GRule<double> gr, gcr;
+    T h2, inv2d, inv_h2, scale;
+    GRule<T> gr, gcr;
     int nbx, nby, kz;  // columns along x and y, planes per chunk
     int rev;
     unsigned long long* maxbits;
@@ -84,14 +86,17 @@ struct LegArgs {
 // several steps (behind branches the compiler has to wait as if none was issued).
 constexpr unsigned kLegOob = 0x80000000u;
 
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t leg_plane(const double* p, bool on, unsigned bytes)
+template <typename T>
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t leg_plane(const T* p, bool on, unsigned bytes)
 {
     return __builtin_amdgcn_make_buffer_rsrc((void*)p, 0, on ? (int)bytes : 0, 0x00027000);
 }
 
-__device__ __forceinline__ double leg_load(__amdgpu_buffer_rsrc_t b, unsigned off)
+template <typename T>
+__device__ __forceinline__ T leg_load(__amdgpu_buffer_rsrc_t b, unsigned off)
 {
-    return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(b, off, 0, 0));
+    if constexpr (sizeof(T) == 8) return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(b, off, 0, 0));
+    else return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(b, off, 0, 0));
 }
 
 // rule_pair without branches; ql: the index for the test of the lower wall
@@ -105,7 +110,8 @@ __device__ __forceinline__ void leg_rule(int ql, int q, int N, C self, C& lo, C&
 
 // m ? a : b without a branch around what forms a (the compiler made one of every select
 // in the steps beside a boundary, which took half as long again as the others)
-__device__ __forceinline__ double leg_select(bool m, double a, double b)
+template <typename T>
+__device__ __forceinline__ T leg_select(bool m, T a, T b)
 {
     asm volatile("" : "+v"(a));
     return m ? a : b;
@@ -113,18 +119,20 @@ __device__ __forceinline__ double leg_select(bool m, double a, double b)
 
 typedef unsigned LegV2 __attribute__((ext_vector_type(2)));
 
-__device__ __forceinline__ void leg_store(__amdgpu_buffer_rsrc_t b, unsigned off, double v)
+template <typename T>
+__device__ __forceinline__ void leg_store(__amdgpu_buffer_rsrc_t b, unsigned off, T v)
 {
-    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(LegV2, v), b, off, 0, 0);
+    if constexpr (sizeof(T) == 8) __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(LegV2, v), b, off, 0, 0);
+    else __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), b, off, 0, 0);
 }
 
 // N sweeps, up or down.  RULE: a coarse level (ghost values by its rule, the down leg
 // starts from zero); otherwise multigrid level 0 (ghost layer in memory, the up leg
 // forms the max norm of the residual).
-template <int N, bool RULE, bool UP, typename S>
-__global__ void __launch_bounds__(S::NT) k_leg3(LegArgs A)
+template <typename T, int N, bool RULE, bool UP, typename S>
+__global__ void __launch_bounds__(S::NT, sizeof(T) == 8 ? 2 : 4) k_leg3(LegArgs<T> A)
 {
-    using C = double;
+    using C = T;
     constexpr bool ZERO = RULE && !UP, NORM = UP && !RULE;
     constexpr bool RES = !UP || NORM;
     constexpr int NX = 2 * N;                          // half sweeps
@@ -268,8 +276,8 @@ __global__ void __launch_bounds__(S::NT) k_leg3(LegArgs A)
         const auto br = leg_plane(fz, on, pbytes), bb = leg_plane(fz + g.cs, on, pbytes);
 #pragma unroll
         for (int r = 0; r < 2; r++) {
-            q.fr[r] = leg_load(br, off[r]);
-            q.fb[r] = leg_load(bb, off[r]);
+            q.fr[r] = leg_load<C>(br, off[r]);
+            q.fb[r] = leg_load<C>(bb, off[r]);
         }
         if constexpr (!ZERO) {
             const ptrdiff_t pb = (ptrdiff_t)(a + 1) * (ptrdiff_t)g.ps + (ptrdiff_t)g.cs;
@@ -281,9 +289,9 @@ __global__ void __launch_bounds__(S::NT) k_leg3(LegArgs A)
 #pragma unroll
             for (int r = 0; r < 2; r++) {
                 const int od = r ? !par : par;
-                q.b[r] = leg_load(ub, RING ? offi[r][od] : off[r]);
-                q.r[r] = leg_load(rr, off[r]);
-                if constexpr (RING) q.gb[r] = leg_load(gb, inz ? offg[r][od] : off[r]);
+                q.b[r] = leg_load<C>(ub, RING ? offi[r][od] : off[r]);
+                q.r[r] = leg_load<C>(rr, off[r]);
+                if constexpr (RING) q.gb[r] = leg_load<C>(gb, inz ? offg[r][od] : off[r]);
             }
         }
     };
@@ -597,7 +605,7 @@ __global__ void __launch_bounds__(S::NT) k_leg3(LegArgs A)
     using P0 = std::integral_constant<int, (S::H + kStepPar) & 1>;
     using P1 = std::integral_constant<int, (S::H + kStepPar + 1) & 1>;
     // steps between a load and its use: three, two where registers are short
-    constexpr int LEAD = N == 2 ? 2 : 3;
+    constexpr int LEAD = sizeof(C) == 8 && N == 2 ? 2 : 3;
     Feed q0, q1, q2, q3;
     load(P0{}, q0, as);
     load(P1{}, q1, as + 1);
@@ -630,8 +638,11 @@ __global__ void __launch_bounds__(S::NT) k_leg3(LegArgs A)
 }  // namespace
 
 // ------------------------------------------------------------------ launches
-// Column of a workgroup per halo width: 512 threads, with FP64's registers all that
-// a CU takes; the halo's share of the work is least (1.3 to 1.7 times the points).
+// Column of a workgroup per halo width: 512 threads, with FP64's registers all that a CU
+// takes (in FP32 it takes two), each wavefront two rows of 32 compact points, so that
+// a lane's x-neighbours are the lanes beside it.  The halo makes the work 1.3 to 1.7
+// times the points (with 256 threads and two workgroups per CU in FP64 1.6 times for
+// H = 3: 1.4 times as long).
 template <int H>
 struct LegPick;
 template <> struct LegPick<2> { using S = LegShape<2, 58, 28>; };
@@ -640,14 +651,14 @@ template <> struct LegPick<4> { using S = LegShape<4, 54, 24>; };
 template <> struct LegPick<5> { using S = LegShape<5, 54, 22>; };
 
 // Planes per chunk: a chunk takes its planes and `extra` steps (filling the pipeline,
-// the halo), the workgroups run in rounds of one per CU.
-static int leg_planes(long cols, int nz, int extra)
+// the halo), the workgroups run in rounds of occ per CU.
+static int leg_planes(long cols, int nz, int extra, int occ)
 {
     long best = 0;
     int kz_best = 2;
     for (int nch = 1; nch <= (nz + 1) / 2; nch++) {
         const int kz = ((nz + nch - 1) / nch + 1) & ~1;
-        const long wgs = cols * ((nz + kz - 1) / kz), cost = (wgs + 255) / 256 * (kz + extra);
+        const long wgs = cols * ((nz + kz - 1) / kz), cost = (wgs + 256 * occ - 1) / (256 * occ) * (kz + extra);
         if (nch == 1 || cost < best) {
             best = cost;
             kz_best = kz;
@@ -657,22 +668,23 @@ static int leg_planes(long cols, int nz, int extra)
     return kz_best;
 }
 
-template <int N, bool RULE, bool UP>
-static void leg3(hipStream_t st, LegArgs A)
+template <typename T, int N, bool RULE, bool UP>
+static void leg3(hipStream_t st, LegArgs<T> A)
 {
     constexpr int H = 2 * N + !RULE;  // a halo point per half sweep or residual that follows
     using S = typename LegPick<H>::S;
     A.nbx = ceil_div(A.g.nx - 2, S::TX);
     A.nby = ceil_div(A.g.ny - 2, S::TY);
-    A.kz = leg_planes((long)A.nbx * A.nby * A.g.nb, A.g.nz - 2, 2 * H + 2 * N + 3);
+    A.kz = leg_planes((long)A.nbx * A.nby * A.g.nb, A.g.nz - 2, 2 * H + 2 * N + 3, sizeof(T) == 8 ? 1 : 2);
     const dim3 grid((unsigned)((long)A.nbx * A.nby * ceil_div(A.g.nz - 2, A.kz)), A.g.nb);
-    hipLaunchKernelGGL((k_leg3<N, RULE, UP, S>), grid, dim3(S::NT), 0, st, A);
+    hipLaunchKernelGGL((k_leg3<T, N, RULE, UP, S>), grid, dim3(S::NT), 0, st, A);
 }
 
-static LegArgs leg_args(const LevelLeg& a, const double* u_in, const double* ring, const double* f, double* u_out, double* fc,
-                        const double* ec, unsigned long long* maxbits)
+template <typename T>
+static LegArgs<T> leg_args(const LevelLeg& a, const T* u_in, const T* ring, const T* f, T* u_out, T* fc, const T* ec,
+                           unsigned long long* maxbits)
 {
-    LegArgs A{};
+    LegArgs<T> A{};
     A.u_in = u_in;
     A.ring = ring;
     A.f = f;
@@ -681,41 +693,54 @@ static LegArgs leg_args(const LevelLeg& a, const double* u_in, const double* rin
     A.ec = ec;
     A.g = a.g;
     A.gc = a.gc;
-    A.h2 = a.h2;
-    A.inv2d = 1.0 / 6.0;
-    A.inv_h2 = a.inv_h2;
-    A.scale = 0.125;
-    A.gr = grule<double>(a.rule);
-    A.gcr = grule<double>(a.coarse_rule);
+    A.h2 = (T)a.h2;
+    A.inv2d = (T)(1.0 / 6.0);
+    A.inv_h2 = (T)a.inv_h2;
+    A.scale = (T)0.125;
+    A.gr = grule<T>(a.rule);
+    A.gcr = grule<T>(a.coarse_rule);
     A.rev = a.rev;
     A.maxbits = maxbits;
     return A;
 }
 
-void launch_stream_down(hipStream_t st, const LevelLeg& a, int n_pre, bool rule, const double* u_in, const double* f,
-                        double* u_out, double* fc)
+template <typename T>
+void launch_stream_down(hipStream_t st, const LevelLeg& a, int n_pre, bool rule, const T* u_in, const T* f, T* u_out, T* fc)
 {
-    const LegArgs A = leg_args(a, u_in, u_in, f, u_out, fc, nullptr, nullptr);
-    if (rule) {
-        if (n_pre == 1) leg3<1, true, false>(st, A);
-        else leg3<2, true, false>(st, A);
-    } else {
-        if (n_pre == 1) leg3<1, false, false>(st, A);
-        else leg3<2, false, false>(st, A);
+    const LegArgs<T> A = leg_args<T>(a, u_in, u_in, f, u_out, fc, nullptr, nullptr);
+    if constexpr (sizeof(T) == 8) {
+        if (!rule) {
+            if (n_pre == 1) leg3<T, 1, false, false>(st, A);
+            else leg3<T, 2, false, false>(st, A);
+            return;
+        }
     }
+    if (n_pre == 1) leg3<T, 1, true, false>(st, A);
+    else leg3<T, 2, true, false>(st, A);
 }
 
-void launch_stream_up(hipStream_t st, const LevelLeg& a, int n_post, bool rule, const double* u_in, const double* ring,
-                      const double* f, double* u_out, const double* ec, unsigned long long* maxbits)
+template <typename T>
+void launch_stream_up(hipStream_t st, const LevelLeg& a, int n_post, bool rule, const T* u_in, const T* ring, const T* f,
+                      T* u_out, const T* ec, unsigned long long* maxbits)
 {
-    const LegArgs A = leg_args(a, u_in, ring, f, u_out, nullptr, ec, maxbits);
-    if (rule) {
-        if (n_post == 1) leg3<1, true, true>(st, A);
-        else leg3<2, true, true>(st, A);
-    } else {
-        if (n_post == 1) leg3<1, false, true>(st, A);
-        else leg3<2, false, true>(st, A);
+    const LegArgs<T> A = leg_args<T>(a, u_in, ring, f, u_out, nullptr, ec, maxbits);
+    if constexpr (sizeof(T) == 8) {
+        if (!rule) {
+            if (n_post == 1) leg3<T, 1, false, true>(st, A);
+            else leg3<T, 2, false, true>(st, A);
+            return;
+        }
     }
+    if (n_post == 1) leg3<T, 1, true, true>(st, A);
+    else leg3<T, 2, true, true>(st, A);
 }
+
+template void launch_stream_down<double>(hipStream_t, const LevelLeg&, int, bool, const double*, const double*, double*,
+                                         double*);
+template void launch_stream_down<float>(hipStream_t, const LevelLeg&, int, bool, const float*, const float*, float*, float*);
+template void launch_stream_up<double>(hipStream_t, const LevelLeg&, int, bool, const double*, const double*, const double*,
+                                       double*, const double*, unsigned long long*);
+template void launch_stream_up<float>(hipStream_t, const LevelLeg&, int, bool, const float*, const float*, const float*,
+                                      float*, const float*, unsigned long long*);
 
 }  // namespace np
