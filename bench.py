@@ -384,11 +384,11 @@ def run_variant(name, wl, rho, phi_outer, Fs, steps, warmup, inner_cycles, stop_
     #   reads P's red points: 3 e.
     elem = ELEM[v["precision"]]
     npts = math.prod(v + 2 for v in geom.ext(0))
-    #   fused legs (the FP64 variants): down: read black, f of both colours, write black and the
-    #   coarse right-hand side: 2.125 e; up: read black, f and the coarse correction, write
-    #   both colours: 2.625 e; on small grids the two legs are one class of that mean.
+    #   fused legs (FP64 and FP32 storage): down: read black, f of both colours, write black and
+    #   the coarse right-hand side: 2.125 e (from zero 1.625 e); up: read black, f and the
+    #   coarse correction, write both colours: 2.625 e; FP32 and small grids: one class.
     per_point = dict(smooth=1.5, seeded=2.0 if v.get("n_pre", 2) == 1 else 1.5, full=2.5, full_res=3.0)
-    if elem == 8 and v.get("sweep", "full") == "full":
+    if elem >= 4 and v.get("sweep", "full") == "full":
         per_point.update(smooth=2.375, full=2.125, full_res=2.625)
     uniform = len(set(geom.ext(l) for l in range(geom.nlevels))) == 1
     sweeps = {}
@@ -586,8 +586,8 @@ def main():
         "roofline": None if not uniform else {
             "bound": "hbm",
             "kernel": "level-0 red-black %s of variant %s (%d-byte storage)"
-                      % ("half sweep" if sm["elem_bytes"] < 8 and sm["kind"] == "smooth" else
-                         "fused V-cycle leg" if sm["elem_bytes"] == 8 else "full sweep (one pass, two buffers)", best,
+                      % ("half sweep" if sm["elem_bytes"] == 2 and sm["kind"] == "smooth" else
+                         "fused V-cycle leg" if sm["elem_bytes"] >= 4 else "full sweep (one pass, two buffers)", best,
                          sm["elem_bytes"]),
             "achieved": sm["GBps"],
             "peak": PEAK_HBM_GBS,

@@ -95,7 +95,8 @@ extern "C" {
  * prolongation, the post-smoothing sweeps and on multigrid level 0 the stop
  * test's residual norm.  FP64: every level above the coarse tail, from the
  * level's potential into a second buffer (the handle's) and back; the defect
- * correction: the coarse levels, 3-D those of up to 1024 blocks of 8^3 points.
+ * correction: 3-D with FP32 storage and n_post = 1 every level as well, otherwise the
+ * coarse levels (3-D: the larger ones only below a first one of 2^23 points).
  * With other sweep counts, 3-D FP64: on level grids whose full sweep starts at least 4096
  * wavefronts (cubic levels from about 420^3 cells; on smaller or thin grids
  * the half sweeps, which occupy the chip better, run), each

@@ -223,8 +223,12 @@ bool level_tile(int dim, const SGrid& g);
 // colours.  u_out must not be u_in (with rule u_in is not read)
 template <typename T>
 void launch_level_down(hipStream_t st, const LevelLeg& a, int n_pre, bool rule, const T* u_in, const T* f, T* u_out, T* fc);
+// (streamed: kLegRule as with rule, kLegWarm as without it, FP32 as well; kLegZero as
+// kLegWarm from zero, FP32; the restricted residual times out_scale)
+constexpr int kLegRule = 0, kLegWarm = 1, kLegZero = 2;
 template <typename T>
-void launch_stream_down(hipStream_t st, const LevelLeg& a, int n_pre, bool rule, const T* u_in, const T* f, T* u_out, T* fc);
+void launch_stream_down(hipStream_t st, const LevelLeg& a, int n_pre, int mode, const T* u_in, const T* f, T* u_out, T* fc,
+                        double out_scale);
 template <typename T>
 void launch_tile2_down(hipStream_t st, const LevelLeg& a, int n_pre, bool rule, const T* u_in, const T* f, T* u_out, T* fc);
 // u_in (as launch_level_down left it) plus the prolonged ec, n_post sweeps, into u_out
@@ -234,8 +238,9 @@ void launch_tile2_down(hipStream_t st, const LevelLeg& a, int n_pre, bool rule, 
 template <typename T>
 void launch_level_up(hipStream_t st, const LevelLeg& a, int n_post, bool rule, const T* u_in, const T* ring, const T* f,
                      T* u_out, const T* ec, unsigned long long* maxbits);
+// (streamed, FP32: no norm)
 template <typename T>
-void launch_stream_up(hipStream_t st, const LevelLeg& a, int n_post, bool rule, const T* u_in, const T* ring, const T* f,
+void launch_stream_up(hipStream_t st, const LevelLeg& a, int n_post, int mode, const T* u_in, const T* ring, const T* f,
                       T* u_out, const T* ec, unsigned long long* maxbits);
 template <typename T>
 void launch_tile2_up(hipStream_t st, const LevelLeg& a, int n_post, bool rule, const T* u_in, const T* ring, const T* f,

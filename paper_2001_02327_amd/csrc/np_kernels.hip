@@ -1033,7 +1033,15 @@ __global__ void __launch_bounds__(kSmoothPairBlock) k_smooth_zmarch3_pair(T* __r
                                                                 typename Compute<T>::type inv2d, int pblocks)
 {
     using C = typename Compute<T>::type;
-    const auto sv = [&](T v) -> T { return SEED ? (T)(((C)0 - h2 * (C)v) * inv2d) : v; };
+    // (in FP32 rounded before it is used, as a stored value is)
+    const auto rounded = [&](C v) -> C {
+#pragma clang fp contract(off)
+        return ((C)0 - h2 * v) * inv2d;
+    };
+    const auto sv = [&](T v) -> T {
+        if constexpr (SEED && sizeof(T) == sizeof(C)) return rounded(v);
+        else return SEED ? (T)(((C)0 - h2 * (C)v) * inv2d) : v;
+    };
     const auto sp = [&](Pair<T> v) -> Pair<T> {
         if (SEED) {
             v.a = sv(v.a);

@@ -533,13 +533,26 @@ int tail_level(const np_solver* s, int l, size_t esz)
     return 0;
 }
 
+// Whether the outer pass leaves the next correction's start unstored: its
+// first black half sweep then forms the red values (the red half sweep from
+// zero) from the defect, and stores them when no red half sweep follows that
+// black one (n_pre = 1).  Needs the paired level-0 sweep.
+bool dc_seed_black(const np_solver* s, int l)
+{
+    const np_config& c = s->cfg;
+    return c.precision != NP_PREC_FP64 && c.dim == 3 && c.n_pre >= 1 && (s->lg[l].hx % 2) == 0;
+}
+
 // First multigrid level of nested level l that runs as fused legs, as do the levels
 // from there to the coarse tail; nmg if none does.  FP64: every level (level 0
-// too).  The mixed precisions (level 0 is stored in 16 bits, or starts from its defect):
-// the coarse levels, from the first one on if that has 2^23 points, otherwise from the
-// first one on that the block form serves.  FP32 per cycle, streamed / per pass: 257^3
-// points V(2,1) 127 / 184 us, V(1,1) 113 / 141, V(1,2) 162 / 181; 129^3 47.5 / 45.5, 36.5 /
-// 34.6, 59 / 47; together the larger one decides.
+// too).  FP32 with one post-smoothing sweep: the same (66^3 points, V(2,1) per cycle 27 us
+// against 41 per pass, 130^3 46 against 62, 258^3 121 against 160; with two sweeps the leg up
+// has no registers left, 260^3 7.7 against 7.2 ms per solve).  Otherwise the coarse levels of
+// the mixed precisions, from the first one on if that has 2^23 points, or from the
+// first one on that the block form serves: FP32 streamed / per pass 257^3 points V(2,1)
+// 127 / 184 us, V(1,1) 113 / 141, V(1,2) 162 / 181; 129^3 47.5 / 45.5, 36.5 / 34.6, 59 / 47;
+// together the larger one decides.  (FP16 storage is as fast or faster per pass: 514^3 points
+// V(1,1) 567 us, streamed 790.)
 constexpr size_t kStreamPoints32 = 1 << 23;
 
 int legs_level(const np_solver* s, int l)
@@ -551,8 +564,13 @@ int legs_level(const np_solver* s, int l)
     if (Lt == 0) return nmg;
     // (the streamed form addresses a plane of a colour by 31 bits)
     if (fp64) return s->cfg.dim == 2 || s->lg[l].ps * sizeof(double) < (1ULL << 31) ? 0 : nmg;
-    const SGrid g = mg_grid(s, l, 1);
-    if (s->cfg.dim == 3 && (size_t)g.nx * g.ny * g.nz >= kStreamPoints32 && Lt > 1) return 1;
+    if (s->cfg.dim == 3) {
+        if (s->cfg.precision == NP_PREC_FP32_DC && dc_seed_black(s, l) && s->cfg.n_post == 1 &&
+            s->lg[l].ps * sizeof(float) < (1ULL << 31))
+            return 0;
+        const SGrid g = mg_grid(s, l, 1);
+        if (Lt > 1 && (size_t)g.nx * g.ny * g.nz >= kStreamPoints32 && g.ps * sizeof(float) < (1ULL << 31)) return 1;
+    }
     for (int L = 1; L < Lt; L++)
         if (level_tile(s->cfg.dim, mg_grid(s, l, L))) return L;
     return nmg;
@@ -902,21 +920,37 @@ int full_sweep_norm_sync(np_solver* s, int l, double* out)
 // L e'' = r'' (L = h^2 lap, the integer stencil, r'' = r / ||r||) in low
 // precision TL, with FP32 coarse levels: the coarse right-hand side is
 // R(r'' - L e'') / h^2, in the same units as e''.
-// Whether the outer pass leaves the next correction's start unstored: its
-// first black half sweep then forms the red values (the red half sweep from
-// zero) from the defect, and stores them when no red half sweep follows that
-// black one (n_pre = 1).  Needs the paired level-0 sweep.
-bool dc_seed_black(const np_solver* s, int l)
-{
-    const np_config& c = s->cfg;
-    return c.precision != NP_PREC_FP64 && c.dim == 3 && c.n_pre >= 1 && (s->lg[l].hx % 2) == 0;
-}
-
 template <typename TL>
 int vcycle_lo(np_solver* s, int l, bool red_done)
 {
     MGView<float> v = mg_view<float>(s, l, s->mg_u32, s->mg_f32, s->mg_r32);
     double h = v.h[0];
+    if constexpr (std::is_same<TL, float>::value) {
+        if (use_legs(s, l)) {
+            // the step's first cycle starts from zero and leaves its result in the other
+            // correction (both have a zero ghost layer); later ones come back to their own
+            float* const e = (float*)s->e_lo;
+            float* const mid = red_done ? e : (float*)s->e_nx;
+            float* const out = red_done ? (float*)s->e_nx : e;
+            LevelLeg a = leg_of(s, l, v, 0, 0);
+            a.h2 = a.inv_h2 = 1.0;
+            prof_begin(s, NP_KCLASS_SMOOTH);
+            launch_stream_down<float>(s->stream, a, s->cfg.n_pre, red_done ? kLegZero : kLegWarm, e, (const float*)s->r_lo,
+                                      mid, v.f[1], 1.0 / (h * h));
+            prof_end(s);
+            prof_begin(s, NP_KCLASS_COARSE);
+            int rc = run_coarse(s, l, v, s->coarse_exec32);
+            prof_end(s);
+            if (rc) return rc;
+            a.rev = 1;
+            prof_begin(s, NP_KCLASS_SMOOTH);
+            launch_stream_up<float>(s->stream, a, s->cfg.n_post, kLegWarm, mid, e, (const float*)s->r_lo, out,
+                                    mg_result(s, l, v, 1), nullptr);
+            prof_end(s);
+            if (red_done) std::swap(s->e_lo, s->e_nx);
+            return NP_OK;
+        }
+    }
     return vcycle_t<TL, float>(s, l, (TL*)s->e_lo, (const TL*)s->r_lo, 1.0, 1.0, 1.0 / (h * h), v, s->coarse_exec32,
                                red_done, red_done && dc_seed_black(s, l));
 }

@@ -126,14 +126,14 @@ __device__ __forceinline__ void leg_store(__amdgpu_buffer_rsrc_t b, unsigned off
     else __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), b, off, 0, 0);
 }
 
-// N sweeps, up or down.  RULE: a coarse level (ghost values by its rule, the down leg
-// starts from zero); otherwise multigrid level 0 (ghost layer in memory, the up leg
-// forms the max norm of the residual).
-template <typename T, int N, bool RULE, bool UP, typename S>
+// N sweeps, up or down.  kLegRule: a coarse level (ghost values by its rule, the down leg
+// starts from zero); otherwise multigrid level 0 with its ghost layer in memory: kLegWarm from
+// u_in, the up leg in FP64 with the max norm of the residual, kLegZero from zero.
+template <typename T, int N, int MODE, bool UP, typename S>
 __global__ void __launch_bounds__(S::NT, sizeof(T) == 8 ? 2 : 4) k_leg3(LegArgs<T> A)
 {
     using C = T;
-    constexpr bool ZERO = RULE && !UP, NORM = UP && !RULE;
+    constexpr bool RULE = MODE == kLegRule, ZERO = MODE != kLegWarm && !UP, NORM = UP && !RULE && sizeof(T) == 8;
     constexpr bool RES = !UP || NORM;
     constexpr int NX = 2 * N;                          // half sweeps
     constexpr int NA = (ZERO ? 0 : 1) + NX - (RES ? 0 : 1);  // planes other threads read: the start, each half sweep
@@ -466,6 +466,7 @@ __global__ void __launch_bounds__(S::NT, sizeof(T) == 8 ? 2 : 4) k_leg3(LegArgs<
 #pragma unroll
                 for (int r = 0; r < 2; r++) {
                     xn[0][r] = ((C)0 - A.h2 * frh[0][r]) * A.inv2d;
+                    if constexpr (E && !RULE) xn[0][r] = leg_select(mx[r] && (E == 1 || zin), xn[0][r], (C)0);
                 }
                 continue;
             }
@@ -668,16 +669,17 @@ static int leg_planes(long cols, int nz, int extra, int occ)
     return kz_best;
 }
 
-template <typename T, int N, bool RULE, bool UP>
+template <typename T, int N, int MODE, bool UP>
 static void leg3(hipStream_t st, LegArgs<T> A)
 {
-    constexpr int H = 2 * N + !RULE;  // a halo point per half sweep or residual that follows
+    // a halo point per half sweep or residual that follows
+    constexpr int H = UP ? 2 * N + (MODE != kLegRule && sizeof(T) == 8) : 2 * N + (MODE == kLegWarm);
     using S = typename LegPick<H>::S;
     A.nbx = ceil_div(A.g.nx - 2, S::TX);
     A.nby = ceil_div(A.g.ny - 2, S::TY);
     A.kz = leg_planes((long)A.nbx * A.nby * A.g.nb, A.g.nz - 2, 2 * H + 2 * N + 3, sizeof(T) == 8 ? 1 : 2);
     const dim3 grid((unsigned)((long)A.nbx * A.nby * ceil_div(A.g.nz - 2, A.kz)), A.g.nb);
-    hipLaunchKernelGGL((k_leg3<T, N, RULE, UP, S>), grid, dim3(S::NT), 0, st, A);
+    hipLaunchKernelGGL((k_leg3<T, N, MODE, UP, S>), grid, dim3(S::NT), 0, st, A);
 }
 
 template <typename T>
@@ -696,7 +698,6 @@ static LegArgs<T> leg_args(const LevelLeg& a, const T* u_in, const T* ring, cons
     A.h2 = (T)a.h2;
     A.inv2d = (T)(1.0 / 6.0);
     A.inv_h2 = (T)a.inv_h2;
-    A.scale = (T)0.125;
     A.gr = grule<T>(a.rule);
     A.gcr = grule<T>(a.coarse_rule);
     A.rev = a.rev;
@@ -705,42 +706,42 @@ static LegArgs<T> leg_args(const LevelLeg& a, const T* u_in, const T* ring, cons
 }
 
 template <typename T>
-void launch_stream_down(hipStream_t st, const LevelLeg& a, int n_pre, bool rule, const T* u_in, const T* f, T* u_out, T* fc)
+void launch_stream_down(hipStream_t st, const LevelLeg& a, int n_pre, int mode, const T* u_in, const T* f, T* u_out, T* fc,
+                        double out_scale)
 {
-    const LegArgs<T> A = leg_args<T>(a, u_in, u_in, f, u_out, fc, nullptr, nullptr);
-    if constexpr (sizeof(T) == 8) {
-        if (!rule) {
-            if (n_pre == 1) leg3<T, 1, false, false>(st, A);
-            else leg3<T, 2, false, false>(st, A);
-            return;
-        }
+    LegArgs<T> A = leg_args<T>(a, u_in, u_in, f, u_out, fc, nullptr, nullptr);
+    A.scale = (T)0.125 * (T)out_scale;
+    const auto go = [&](auto m) {
+        if (n_pre == 1) leg3<T, 1, decltype(m)::value, false>(st, A);
+        else leg3<T, 2, decltype(m)::value, false>(st, A);
+    };
+    if (mode == kLegRule) return go(std::integral_constant<int, kLegRule>{});
+    if constexpr (sizeof(T) == 4) {
+        if (mode == kLegZero) return go(std::integral_constant<int, kLegZero>{});
     }
-    if (n_pre == 1) leg3<T, 1, true, false>(st, A);
-    else leg3<T, 2, true, false>(st, A);
+    go(std::integral_constant<int, kLegWarm>{});
 }
 
 template <typename T>
-void launch_stream_up(hipStream_t st, const LevelLeg& a, int n_post, bool rule, const T* u_in, const T* ring, const T* f,
+void launch_stream_up(hipStream_t st, const LevelLeg& a, int n_post, int mode, const T* u_in, const T* ring, const T* f,
                       T* u_out, const T* ec, unsigned long long* maxbits)
 {
     const LegArgs<T> A = leg_args<T>(a, u_in, ring, f, u_out, nullptr, ec, maxbits);
-    if constexpr (sizeof(T) == 8) {
-        if (!rule) {
-            if (n_post == 1) leg3<T, 1, false, true>(st, A);
-            else leg3<T, 2, false, true>(st, A);
-            return;
-        }
-    }
-    if (n_post == 1) leg3<T, 1, true, true>(st, A);
-    else leg3<T, 2, true, true>(st, A);
+    const auto go = [&](auto m) {
+        if (n_post == 1) leg3<T, 1, decltype(m)::value, true>(st, A);
+        else leg3<T, 2, decltype(m)::value, true>(st, A);
+    };
+    if (mode == kLegRule) go(std::integral_constant<int, kLegRule>{});
+    else go(std::integral_constant<int, kLegWarm>{});
 }
 
-template void launch_stream_down<double>(hipStream_t, const LevelLeg&, int, bool, const double*, const double*, double*,
-                                         double*);
-template void launch_stream_down<float>(hipStream_t, const LevelLeg&, int, bool, const float*, const float*, float*, float*);
-template void launch_stream_up<double>(hipStream_t, const LevelLeg&, int, bool, const double*, const double*, const double*,
+template void launch_stream_down<double>(hipStream_t, const LevelLeg&, int, int, const double*, const double*, double*,
+                                         double*, double);
+template void launch_stream_down<float>(hipStream_t, const LevelLeg&, int, int, const float*, const float*, float*, float*,
+                                        double);
+template void launch_stream_up<double>(hipStream_t, const LevelLeg&, int, int, const double*, const double*, const double*,
                                        double*, const double*, unsigned long long*);
-template void launch_stream_up<float>(hipStream_t, const LevelLeg&, int, bool, const float*, const float*, const float*,
+template void launch_stream_up<float>(hipStream_t, const LevelLeg&, int, int, const float*, const float*, const float*,
                                       float*, const float*, unsigned long long*);
 
 }  // namespace np

@@ -579,7 +579,7 @@ template <typename T>
 void launch_level_down(hipStream_t st, const LevelLeg& a, int n_pre, bool rule, const T* u_in, const T* f, T* u_out, T* fc)
 {
     if (a.dim == 2) return launch_tile2_down<T>(st, a, n_pre, rule, u_in, f, u_out, fc);
-    if (!level_tile(3, a.g)) return launch_stream_down<T>(st, a, n_pre, rule, u_in, f, u_out, fc);
+    if (!level_tile(3, a.g)) return launch_stream_down<T>(st, a, n_pre, rule ? kLegRule : kLegWarm, u_in, f, u_out, fc, 1.0);
     if constexpr (sizeof(T) == 8) {
         if (!rule) {
             if (n_pre == 1) down3<T, 1, false>(st, a, u_in, f, u_out, fc);
@@ -596,7 +596,7 @@ void launch_level_up(hipStream_t st, const LevelLeg& a, int n_post, bool rule, c
                      T* u_out, const T* ec, unsigned long long* maxbits)
 {
     if (a.dim == 2) return launch_tile2_up<T>(st, a, n_post, rule, u_in, ring, f, u_out, ec, maxbits);
-    if (!level_tile(3, a.g)) return launch_stream_up<T>(st, a, n_post, rule, u_in, ring, f, u_out, ec, maxbits);
+    if (!level_tile(3, a.g)) return launch_stream_up<T>(st, a, n_post, rule ? kLegRule : kLegWarm, u_in, ring, f, u_out, ec, maxbits);
     if constexpr (sizeof(T) == 8) {
         if (!rule) {
             if (n_post == 1) up3<T, 1, false>(st, a, u_in, ring, f, u_out, ec, maxbits);

@@ -2,9 +2,9 @@
 sweeps) against the per-pass kernels (sweep="half").
 
 One launch takes a multigrid level down or up.  3-D: blocks of the level in LDS
-on levels of at most 1024 blocks of 8 x 8 x 8 points (batch members included), in
-FP64 columns streamed through it on the larger ones; in the mixed precisions the
-coarse levels that fit the block form.  2-D: blocks of 16^2 points, of 32^2 for the leg
+on levels of at most 1024 blocks of 8 x 8 x 8 points (batch members included),
+columns streamed through it on the larger ones; FP64 and FP32 every level, FP16
+storage the coarse levels that fit the block form.  2-D: blocks of 16^2 points, of 32^2 for the leg
 with the norm where the small ones are more than 512; in the mixed precisions the
 coarse levels.  Every operation and its order are those of
 the per-pass kernels, so potentials, forces, cycle counts and residual histories
@@ -77,7 +77,7 @@ def test_batches(n):
 @pytest.mark.parametrize("kw", [dict(), dict(n_pre=1, coarse_post=2), dict(n_pre=1, n_post=2)],
                          ids=lambda kw: "-".join("%s=%s" % a for a in kw.items()) or "default")
 @pytest.mark.parametrize("wl", [W.c2_plummer(32), W.c2_plummer(132, 1), W.box_plummer_3d(4)], ids=lambda w: w.name)
-def test_coarse_levels_mixed(wl, kw, precision):
+def test_mixed(wl, kw, precision):
     _same(wl, precision=precision, inner_cycles="adaptive", **kw)
 
 
@@ -123,3 +123,16 @@ def test_norms_after_a_failed_solve():
     for l in range(wl.geom.nlevels):
         assert np.array_equal(s.potential(l).cpu().numpy(), ref[l])
     s.close()
+
+
+@pytest.mark.parametrize("n", [(8, 8, 8), (10, 8, 14), (16, 18, 20), (54, 22, 30), (58, 28, 40), (110, 46, 62), (120, 54, 34),
+                               (24, 100, 90), (200, 200, 12), (260, 260, 260)], ids=lambda n: "x".join(map(str, n)))
+@pytest.mark.parametrize("pre,cycles", [(2, 2), (1, "adaptive")])
+def test_sizes_fp32(n, pre, cycles):
+    # multigrid level 0 streamed at every size, from zero and from the previous cycle
+    _same(_one(*n), precision="fp32_dc", n_pre=pre, inner_cycles=cycles, max_cycles=12)
+
+
+def test_largest_coarse_levels():
+    # a first coarse level of 2^23 points and more: streamed in FP32 under FP16 storage too
+    _same(W.c2_plummer(512, 1), precision="fp16s_dc", inner_cycles="adaptive", n_pre=1, coarse_post=2, max_cycles=6)
