@@ -109,8 +109,7 @@ void launch_export(int dim, hipStream_t st, SGrid g, const double* a, double* ou
 // the active part of u taken as zero); result is max of the bit patterns of |value|
 void launch_norm(int dim, hipStream_t st, SGrid g, const double* u, const double* f, double inv_h2, int mode,
                  unsigned long long* maxbits);
-void launch_publish(hipStream_t st, unsigned long long* bits, int n, unsigned long long* host, unsigned long long* host_seq,
-                    unsigned long long seq);
+void launch_publish(hipStream_t st, unsigned long long* bits, int n, unsigned long long* host, unsigned seq);
 void launch_set_u64(hipStream_t st, unsigned long long* p, int count, unsigned long long v);
 // 3-D: max over boxes of 4^3 active points of |mean of f - lap u| (the residual
 // restricted twice), as a bit pattern into maxbits (atomic maximum)

@@ -748,16 +748,18 @@ __global__ void __launch_bounds__(kBlock) k_box_resid_norm3(SGrid g, const doubl
     block_max_to(best, maxbits);
 }
 
-// n reduction slots to pinned host memory, zeroed where they were, then the read's number
-__global__ void __launch_bounds__(64) k_publish(unsigned long long* bits, int n, unsigned long long* host,
-                                                unsigned long long* host_seq, unsigned long long seq)
+// n reduction slots to pinned host memory, zeroed where they were: two words per slot, each
+// half of its bits with the read's number above them, so that the host sees by the
+// word itself that it has come (a number stored behind the slots needs a system fence, which
+// writes the L2 back: 4.1 against 2 us)
+__global__ void __launch_bounds__(64) k_publish(unsigned long long* bits, int n, unsigned long long* host, unsigned seq)
 {
     for (int t = threadIdx.x; t < n; t += 64) {
-        host[t] = bits[t];
+        const unsigned long long v = bits[t], s = (unsigned long long)seq << 32;
         bits[t] = 0;
+        __hip_atomic_store(host + 2 * t, s | (v & 0xffffffffULL), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        __hip_atomic_store(host + 2 * t + 1, s | (v >> 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
-    __threadfence_system();
-    if (threadIdx.x == 0) __hip_atomic_store(host_seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 __global__ void k_set_u64(unsigned long long* p, int count, unsigned long long v)
@@ -3176,10 +3178,9 @@ void launch_box_resid_norm3(hipStream_t st, SGrid g, const double* u, const doub
     hipLaunchKernelGGL(k_box_resid_norm3, dim3(ceil_div(nb, kBlock)), dim3(kBlock), 0, st, g, u, f, inv_h2, maxbits);
 }
 
-void launch_publish(hipStream_t st, unsigned long long* bits, int n, unsigned long long* host, unsigned long long* host_seq,
-                    unsigned long long seq)
+void launch_publish(hipStream_t st, unsigned long long* bits, int n, unsigned long long* host, unsigned seq)
 {
-    hipLaunchKernelGGL(k_publish, dim3(1), dim3(64), 0, st, bits, n, host, host_seq, seq);
+    hipLaunchKernelGGL(k_publish, dim3(1), dim3(64), 0, st, bits, n, host, seq);
 }
 
 void launch_set_u64(hipStream_t st, unsigned long long* p, int count, unsigned long long v)

@@ -304,8 +304,9 @@ struct np_solver {
     float* mg_r32[NP_MAX_MG] = {};
     double* force_scratch = nullptr;  // FORCE_DELTA stop rule
     unsigned long long* d_bits = nullptr;  // device reduction slots
-    unsigned long long* h_bits = nullptr;  // pinned host copy, then the number of the last read
-    unsigned long long bits_seq = 0;       // number of the last read queued
+    unsigned long long* h_words = nullptr;  // pinned: two words per slot (read_slots)
+    unsigned long long h_bits[kBitSlots] = {};  // the slots last read
+    unsigned bits_seq = 0;                 // number of the last read queued
     int fixed[NP_MAX_LEVELS];
     bool has_fixed = false;
     bool solved = false;
@@ -774,29 +775,38 @@ int vcycle_t(np_solver* s, int l, T0* u0, const T0* f0, double h2_0, double inv_
 constexpr long kFullSweepMinWaves = 4096;
 
 // Queues the read of n reduction slots from `slot` on, which zeroes them for their next
-// use, and waits for it: a kernel writes them to pinned memory with the read's number
-// behind them, and the host polls that number.  A copy and a synchronisation of the
+// use, and waits for it: a kernel writes them to pinned memory with the read's number in
+// every word, and the host polls the words.  A copy and a synchronisation of the
 // stream took 20 us more per V-cycle.
 int read_slots(np_solver* s, int slot, int n)
 {
-    const unsigned long long seq = ++s->bits_seq;
-    launch_publish(s->stream, s->d_bits + slot, n, s->h_bits + slot, s->h_bits + kBitSlots, seq);
+    if (++s->bits_seq == 0) s->bits_seq = 1;  // (0: never written)
+    const unsigned seq = s->bits_seq;
+    unsigned long long* const w = s->h_words + 2 * slot;
+    launch_publish(s->stream, s->d_bits + slot, n, w, seq);
     HIPCHK(s, hipGetLastError());
-    for (unsigned spin = 1;; spin++) {
-        if (__atomic_load_n(s->h_bits + kBitSlots, __ATOMIC_ACQUIRE) == seq) return NP_OK;
+    int got = 0;  // words that have come
+    const auto poll = [&]() -> bool {
+        for (; got < 2 * n; got++)
+            if ((unsigned)(__atomic_load_n(w + got, __ATOMIC_ACQUIRE) >> 32) != seq) return false;
+        return true;
+    };
+    for (unsigned spin = 1; !poll(); spin++) {
         if (spin % 4096 == 0) {
-            // still running, done (the number is there, then), or failed
+            // still running, done (the words are there, then), or failed
             const hipError_t e = hipStreamQuery(s->stream);
             if (e == hipErrorNotReady) {
                 (void)hipGetLastError();
                 continue;
             }
             HIPCHK(s, e);
-            if (__atomic_load_n(s->h_bits + kBitSlots, __ATOMIC_ACQUIRE) == seq) return NP_OK;
+            if (poll()) break;
             return set_err(s, NP_EHIP, "a stop test's norm did not reach the host");
         }
         __builtin_ia32_pause();
     }
+    for (int b = 0; b < n; b++) s->h_bits[slot + b] = (w[2 * b] & 0xffffffffULL) | w[2 * b + 1] << 32;
+    return NP_OK;
 }
 
 int read_norm(np_solver* s, int slot, double* out)
@@ -1393,10 +1403,10 @@ void free_all(np_solver* s)
     s->ab_phi = s->ab_f = nullptr;
     if (s->force_scratch) (void)hipFree(s->force_scratch);
     if (s->d_bits) (void)hipFree(s->d_bits);
-    if (s->h_bits) (void)hipHostFree(s->h_bits);
+    if (s->h_words) (void)hipHostFree(s->h_words);
     s->force_scratch = nullptr;
     s->d_bits = nullptr;
-    s->h_bits = nullptr;
+    s->h_words = nullptr;
 }
 
 int alloc_dev(np_solver* s, void** p, size_t bytes)
@@ -1567,11 +1577,12 @@ int nested_poisson_create(const np_config* cfg, void* hip_stream, np_solver** ou
     if (rc == NP_OK && cfg->stop_rule == NP_STOP_FORCE_DELTA)
         rc = alloc_dev(s, (void**)&s->force_scratch, (size_t)d * max_cells * sizeof(double));
     if (rc == NP_OK) rc = alloc_dev(s, (void**)&s->d_bits, kBitSlots * sizeof(unsigned long long));
-    if (rc == NP_OK && hipHostMalloc((void**)&s->h_bits, (kBitSlots + 1) * sizeof(unsigned long long), hipHostMallocCoherent) != hipSuccess) {
+    if (rc == NP_OK && hipHostMalloc((void**)&s->h_words, 2 * kBitSlots * sizeof(unsigned long long), hipHostMallocCoherent) != hipSuccess) {
         (void)hipGetLastError();
-        s->h_bits = nullptr;
+        s->h_words = nullptr;
         rc = NP_ENOMEM;
     }
+    if (rc == NP_OK) memset(s->h_words, 0, 2 * kBitSlots * sizeof(unsigned long long));
     if (rc == NP_OK) rc = alloc_dev(s, (void**)&s->d_act, NP_MAX_LEVELS * sizeof(int));
     if (rc == NP_OK && hipHostMalloc((void**)&s->h_act, NP_MAX_LEVELS * sizeof(int), hipHostMallocDefault) != hipSuccess) {
         (void)hipGetLastError();
