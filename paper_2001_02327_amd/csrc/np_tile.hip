@@ -17,12 +17,15 @@
 // for bit.
 //
 // Threads: a thread owns one compact column (h, y) of the region for both
-// colours and a range of PZ planes; it keeps their right-hand sides in registers,
-// the potential of the region lies in LDS (colour-split, so that lanes read
-// consecutive elements).  The z-neighbours of a column are read once per half
-// sweep, the other three neighbours per point.  A leg is the latency of its half
-// sweeps' LDS round trips and additions (about 1 us each): 10 us down and 7 us up for
-// V(2,1) on 33^3 points in FP64, 31 us in per-pass kernels.
+// colours and a range of PZ planes; it keeps their right-hand sides and values in
+// registers, and the potential of the region lies in LDS too for the neighbours in x and
+// y and at the ends of the range (colour-split, so that lanes read consecutive elements):
+// three loads per point.  A leg is bound by its half sweeps' LDS loads and additions
+// (about 1 us each): 9.1 us down and 6.6 us up for V(2,1) on 33^3 points in FP64, against
+// 31 us in per-pass kernels.  With the columns' values read back from LDS (4.5 loads per
+// point, 5.5 beside the boundary) and the boundary rule formed by selects per neighbour:
+// 9.8 + 7.2 us (a half sweep 2300 cycles, 3000 beside the boundary); 65^3 15.3 + 9.6
+// against 13.4 + 8.6, FP32 V(1,2) up 13.0 against 11.9.
 #include <type_traits>
 
 #include "np_device.h"
@@ -113,16 +116,53 @@ __device__ __forceinline__ TlRange tl_range(const P& p, int rho)
     return r;
 }
 
+// How a pass reads the x and y neighbours outside a thread's column in a block at the
+// boundary: offsets from the point in the other colour's array and factors.  A ghost
+// value is a factor times the point itself or the neighbour opposite, so a thread
+// whose neighbour is a ghost reads that value's address instead; no test per point.
+template <typename C>
+struct TlNb {
+    int xa, xb, y0, y1;      // x: in the thread's even and odd planes
+    C fxa, fxb, fy0, fy1;
+    bool ga, gb, far;        // the column's own x neighbour is a ghost, and (far) of the neighbour opposite
+    C fg;
+};
+
+template <int COLOUR, typename S, typename C, typename P>
+__device__ __forceinline__ TlNb<C> tl_nb(const P& p, int par0, const GRule<C>& gr)
+{
+    constexpr int self = COLOUR ? S::CS : -S::CS;  // from the other colour's array to this one's
+    const C fx = gr.xn1[0] ? (C)-1 : gr.coef[0], fy = gr.xn1[1] ? (C)-1 : gr.coef[1];
+    const bool lo = p.hg == 0, hi = 2 * p.hg == p.Nx, hi_odd = 2 * p.hg + 1 == p.Nx;
+    TlNb<C> n;
+    const int x1 = hi_odd ? (gr.xn1[0] ? 0 : self) : 1;  // the odd point's
+    const C f1 = hi_odd ? fx : (C)1;
+    n.xa = par0 ? x1 : -1;
+    n.xb = par0 ? -1 : x1;
+    n.fxa = par0 ? f1 : (C)1;
+    n.fxb = par0 ? (C)1 : f1;
+    n.ga = par0 ? lo : hi;
+    n.gb = par0 ? hi : lo;
+    n.far = hi && gr.xn1[0];
+    n.fg = lo ? (C)-1 : fx;
+    n.y0 = p.pj == 1 ? self : -S::HC;
+    n.fy0 = p.pj == 1 ? (C)-1 : (C)1;
+    n.y1 = p.pj == p.Ny ? (gr.xn1[1] ? -S::HC : self) : S::HC;
+    n.fy1 = p.pj == p.Ny ? fy : (C)1;
+    return n;
+}
+
 // One half sweep of COLOUR over the points within rho of the block, or (RESID)
-// f - lap u at the block's points of that colour into rr.  fv: the thread's
-// right-hand sides of the colour.  Every load of SB planes is issued before the first
+// f - lap u at the block's points of that colour into rr.  uo, uw: the thread's column of
+// the other colour and of this one, as they are in LDS; fv: its right-hand sides of this
+// colour.  STORE: other threads read the result.  Every load of SB planes is issued before the first
 // is used and nothing branches in between (points out of range are formed
 // and dropped: their store goes to a slot in front of the array): with a branch
 // per point the compiler put each point's loads behind it and every plane
 // cost an LDS round trip and the chain of its additions, 14 us per leg on one block.
-template <int COLOUR, bool RULE, bool EDGE, bool RESID, typename S, typename C, typename P>
-__device__ __forceinline__ void tl_pass(C* R, C* B, const C (&fv)[S::PZ], const P& p, int rho, C h2, C inv2d,
-                                        const GRule<C>& gr, C (&rr)[S::PZ])
+template <int COLOUR, bool RULE, bool EDGE, bool RESID, bool STORE, typename S, typename C, typename P>
+__device__ __forceinline__ void tl_pass(C* R, C* B, const C (&uo)[S::PZ], C (&uw)[S::PZ], const C (&fv)[S::PZ], const P& p,
+                                        int rho, C h2, C inv2d, const GRule<C>& gr, C (&rr)[S::PZ])
 {
     const C* o = COLOUR ? R : B;
     C* w = COLOUR ? B : R;
@@ -131,6 +171,8 @@ __device__ __forceinline__ void tl_pass(C* R, C* B, const C (&fv)[S::PZ], const 
     const int par0 = (COLOUR + p.pj + p.pk0 + 3) & 1;
     const int dx0 = par0 ? 1 : -1;
     const bool va = par0 ? r.v1 : r.v0, vb = par0 ? r.v0 : r.v1;
+    TlNb<C> nb;
+    if constexpr (RULE && EDGE) nb = tl_nb<COLOUR, S>(p, par0, gr);
     if constexpr (RESID) {
 #pragma unroll
         for (int j = 0; j < S::PZ; j++) rr[j] = (C)0;
@@ -139,61 +181,76 @@ __device__ __forceinline__ void tl_pass(C* R, C* B, const C (&fv)[S::PZ], const 
     for (int jb = 0; jb < S::PZ; jb += S::SB) {
         if (p.pk0 + jb > r.zhi || p.pk0 + jb + S::SB - 1 < r.zlo) continue;  // uniform over the wavefront
         const int at0 = (p.zl0 + jb) * S::NCOL + p.col;
-        C ov[S::SB + 2], xo[S::SB], ya[S::SB], yb[S::SB], me[S::SB];
+        C ov[S::SB + 2], xo[S::SB], ya[S::SB], yb[S::SB];
 #pragma unroll
-        for (int j = 0; j < S::SB + 2; j++) ov[j] = o[at0 + (j - 1) * S::NCOL];
+        for (int j = 0; j < S::SB + 2; j++) {
+            const int k = jb + j - 1;
+            ov[j] = k >= 0 && k < S::PZ ? uo[k < 0 || k >= S::PZ ? 0 : k] : o[at0 + (j - 1) * S::NCOL];
+        }
 #pragma unroll
         for (int j = 0; j < S::SB; j++) {
             const int at = at0 + j * S::NCOL;
-            xo[j] = o[at + (((jb + j) & 1) ? -dx0 : dx0)];
-            ya[j] = o[at - S::HC];
-            yb[j] = o[at + S::HC];
-            if constexpr (RESID || (RULE && EDGE)) me[j] = w[at];
+            if constexpr (RULE && EDGE) {
+                xo[j] = o[at + (((jb + j) & 1) ? nb.xb : nb.xa)];
+                ya[j] = o[at + nb.y0];
+                yb[j] = o[at + nb.y1];
+            } else {
+                xo[j] = o[at + (((jb + j) & 1) ? -dx0 : dx0)];
+                ya[j] = o[at - S::HC];
+                yb[j] = o[at + S::HC];
+            }
         }
         C v[S::SB];
 #pragma unroll
         for (int j = 0; j < S::SB; j++) {
             C y0 = ya[j], y1 = yb[j], z0 = ov[j], z1 = ov[j + 2], xm = ov[j + 1], xp = xo[j];
+            const C me = uw[jb + j];
             if constexpr (RULE && EDGE) {
-                const int par = ((jb + j) & 1) ? par0 ^ 1 : par0;
-                const int pi = 2 * p.hg + par, pk = p.pk0 + jb + j;
-                xm = par ? ov[j + 1] : xo[j];
-                xp = par ? xo[j] : ov[j + 1];
-                rule_pair(pi, p.Nx, me[j], xm, xp, gr, 0);
-                rule_pair(p.pj, p.Ny, me[j], y0, y1, gr, 1);
-                rule_pair(pk, p.Nz, me[j], z0, z1, gr, 2);
+                const bool odd = (jb + j) & 1;
+                const C ghost = nb.fg * (nb.far ? xp : me);
+                xp = (odd ? nb.fxb : nb.fxa) * xp;
+                xm = (odd ? nb.gb : nb.ga) ? ghost : xm;
+                y0 = nb.fy0 * y0;
+                y1 = nb.fy1 * y1;
+                rule_pair(p.pk0 + jb + j, p.Nz, me, z0, z1, gr, 2);
             }
             C s = xm + xp;
             s = s + y0;
             s = s + y1;
             s = s + z0;
             s = s + z1;
-            if constexpr (RESID) v[j] = fma_t(-h2, fma_t((C)-6, me[j], s), fv[jb + j]);  // (h2: 1 / h^2)
+            if constexpr (RESID) v[j] = fma_t(-h2, fma_t((C)-6, me, s), fv[jb + j]);  // (h2: 1 / h^2)
             else v[j] = (fma_t(-h2, fv[jb + j], s) * inv2d);
         }
 #pragma unroll
         for (int j = 0; j < S::SB; j++) {
             const int pk = p.pk0 + jb + j;
             const bool live = (((jb + j) & 1) ? vb : va) && pk >= r.zlo && pk <= r.zhi;
-            if constexpr (RESID) rr[jb + j] = live ? v[j] : (C)0;
-            else w[live ? at0 + j * S::NCOL : -S::FRONT] = v[j];
+            if constexpr (RESID) {
+                rr[jb + j] = live ? v[j] : (C)0;
+            } else {
+                uw[jb + j] = live ? v[j] : uw[jb + j];
+                if constexpr (STORE) w[live ? at0 + j * S::NCOL : -S::FRONT] = v[j];
+            }
         }
     }
 }
 
-template <int COLOUR, bool RULE, bool EDGE, typename S, typename C, typename P>
-__device__ __forceinline__ void tl_sweep(C* R, C* B, const C (&fv)[S::PZ], const P& p, int rho, C h2, C inv2d,
-                                         const GRule<C>& gr)
+template <int COLOUR, bool RULE, bool EDGE, bool STORE, typename S, typename C, typename P>
+__device__ __forceinline__ void tl_sweep(C* R, C* B, C (&ur)[S::PZ], C (&ub)[S::PZ], const C (&fv)[S::PZ], const P& p,
+                                         int rho, C h2, C inv2d, const GRule<C>& gr)
 {
     C none[S::PZ];
-    tl_pass<COLOUR, RULE, EDGE, false, S>(R, B, fv, p, rho, h2, inv2d, gr, none);
+    if constexpr (COLOUR) tl_pass<1, RULE, EDGE, false, STORE, S>(R, B, ur, ub, fv, p, rho, h2, inv2d, gr, none);
+    else tl_pass<0, RULE, EDGE, false, STORE, S>(R, B, ub, ur, fv, p, rho, h2, inv2d, gr, none);
 }
 
 template <int COLOUR, bool RULE, bool EDGE, typename S, typename C, typename P>
-__device__ __forceinline__ void tl_resid(C* R, C* B, const C (&fv)[S::PZ], const P& p, C inv_h2, const GRule<C>& gr,
-                                         C (&rr)[S::PZ])
+__device__ __forceinline__ void tl_resid(C* R, C* B, C (&ur)[S::PZ], C (&ub)[S::PZ], const C (&fv)[S::PZ], const P& p,
+                                         C inv_h2, const GRule<C>& gr, C (&rr)[S::PZ])
 {
-    tl_pass<COLOUR, RULE, EDGE, true, S>(R, B, fv, p, 0, inv_h2, (C)0, gr, rr);
+    if constexpr (COLOUR) tl_pass<1, RULE, EDGE, true, false, S>(R, B, ur, ub, fv, p, 0, inv_h2, (C)0, gr, rr);
+    else tl_pass<0, RULE, EDGE, true, false, S>(R, B, ub, ur, fv, p, 0, inv_h2, (C)0, gr, rr);
 }
 
 // loads the thread's columns of both colours of a global array (0 outside the grid)
@@ -212,6 +269,19 @@ __device__ __forceinline__ void tl_load(const T* __restrict__ a, const SGrid& g,
             b[j] = (C)a[g.cs + (size_t)pk * g.ps + base];
         }
     }
+}
+
+// puts the thread's columns of both colours in LDS
+template <typename S, typename C, typename P>
+__device__ __forceinline__ void tl_keep(C* R, C* B, const P& p, const C (&r)[S::PZ], const C (&b)[S::PZ])
+{
+#pragma unroll
+    for (int j = 0; j < S::PZ; j++)
+        if (p.zl0 + j < S::RZ && p.in_col) {
+            const int at = (p.zl0 + j) * S::NCOL + p.col;
+            R[at] = r[j];
+            B[at] = b[j];
+        }
 }
 
 // The down leg.  WARM: from u_in (whose ghost layer is fixed, in memory);
@@ -241,8 +311,8 @@ k_tile_down3(const T* __restrict__ u_in, const T* __restrict__ f, SGrid g, T* __
     const TlPlace<S> p(g, nbx, nby, rev);
     C fr[S::PZ], fb[S::PZ];
     tl_load<S>(f, g, p, fr, fb);
+    C ur[S::PZ], ub[S::PZ];
     if constexpr (WARM) {
-        C ur[S::PZ], ub[S::PZ];
         const bool ok = p.in_col && p.hg >= 0 && p.hg < g.hx && p.pj >= 0 && p.pj < g.ny;
         const size_t base = (size_t)p.pj * g.hx + p.hg;
         const int x0 = 2 * p.hg;
@@ -261,13 +331,6 @@ k_tile_down3(const T* __restrict__ u_in, const T* __restrict__ f, SGrid g, T* __
                     ur[j] = (C)u_in[(size_t)pk * g.ps + base];
             }
         }
-#pragma unroll
-        for (int j = 0; j < S::PZ; j++)
-            if (p.zl0 + j < S::RZ && p.in_col) {
-                const int at = (p.zl0 + j) * S::NCOL + p.col;
-                R[at] = ur[j];
-                B[at] = ub[j];
-            }
     } else {
         // the first red half sweep from zero needs the right-hand side only
         const TlRange r = tl_range<S>(p, H);
@@ -276,14 +339,12 @@ k_tile_down3(const T* __restrict__ u_in, const T* __restrict__ f, SGrid g, T* __
 #pragma unroll
         for (int j = 0; j < S::PZ; j++) {
             const int pk = p.pk0 + j;
-            if (p.zl0 + j < S::RZ && p.in_col) {
-                const bool live = pk >= r.zlo && pk <= r.zhi && ((j & 1) ? vb : va);
-                const int at = (p.zl0 + j) * S::NCOL + p.col;
-                R[at] = live ? (((C)0 - h2 * fr[j]) * inv2d) : (C)0;
-                B[at] = (C)0;
-            }
+            const bool live = pk >= r.zlo && pk <= r.zhi && ((j & 1) ? vb : va);
+            ur[j] = live ? (((C)0 - h2 * fr[j]) * inv2d) : (C)0;
+            ub[j] = (C)0;
         }
     }
+    tl_keep<S>(R, B, p, ur, ub);
     __syncthreads();
     C rr[S::PZ], rb[S::PZ];
     const auto leg = [&](auto edge) {
@@ -291,14 +352,14 @@ k_tile_down3(const T* __restrict__ u_in, const T* __restrict__ f, SGrid g, T* __
 #pragma unroll
         for (int it = 0; it < NPRE; it++) {
             if (WARM || it > 0) {
-                tl_sweep<0, RULE, E, S>(R, B, fr, p, 2 * (NPRE - it), h2, inv2d, gr);
+                tl_sweep<0, RULE, E, true, S>(R, B, ur, ub, fr, p, 2 * (NPRE - it), h2, inv2d, gr);
                 __syncthreads();
             }
-            tl_sweep<1, RULE, E, S>(R, B, fb, p, 2 * (NPRE - it) - 1, h2, inv2d, gr);
+            tl_sweep<1, RULE, E, true, S>(R, B, ur, ub, fb, p, 2 * (NPRE - it) - 1, h2, inv2d, gr);
             __syncthreads();
         }
-        tl_resid<0, RULE, E, S>(R, B, fr, p, inv_h2, gr, rr);
-        tl_resid<1, RULE, E, S>(R, B, fb, p, inv_h2, gr, rb);
+        tl_resid<0, RULE, E, S>(R, B, ur, ub, fr, p, inv_h2, gr, rr);
+        tl_resid<1, RULE, E, S>(R, B, ur, ub, fb, p, inv_h2, gr, rb);
     };
     if (RULE && p.edge()) leg(std::true_type{});
     else leg(std::false_type{});
@@ -312,9 +373,8 @@ k_tile_down3(const T* __restrict__ u_in, const T* __restrict__ f, SGrid g, T* __
         for (int j = 0; j < S::PZ; j++) {
             const int pk = p.pk0 + j;
             if (pk < r.zlo || pk > r.zhi) continue;
-            const int at = (p.zl0 + j) * S::NCOL + p.col;
-            if ((j & 1) ? ra : rb_) u_out[g.cs + (size_t)pk * g.ps + base] = B[at];
-            if (RULE && ((j & 1) ? rb_ : ra)) u_out[(size_t)pk * g.ps + base] = R[at];
+            if ((j & 1) ? ra : rb_) u_out[g.cs + (size_t)pk * g.ps + base] = ub[j];
+            if (RULE && ((j & 1) ? rb_ : ra)) u_out[(size_t)pk * g.ps + base] = ur[j];
         }
     }
     __syncthreads();
@@ -417,13 +477,6 @@ k_tile_up3(const T* __restrict__ u_in, const T* ring, const T* __restrict__ f, S
             }
         }
     }
-#pragma unroll
-    for (int j = 0; j < S::PZ; j++)
-        if (p.zl0 + j < S::RZ && p.in_col) {
-            const int at = (p.zl0 + j) * S::NCOL + p.col;
-            R[at] = ur[j];
-            B[at] = ub[j];
-        }
     __syncthreads();
     {
         // Interpolation: the x parent and neighbour of a column's points are
@@ -459,26 +512,30 @@ k_tile_up3(const T* __restrict__ u_in, const T* ring, const T* __restrict__ f, S
             const bool zin = pk >= r.zlo && pk <= r.zhi;
             const bool par = (j & 1) ? !par0 : (bool)par0;  // the red point is the odd one
             const bool vr = (j & 1) ? rb : ra, vbk = (j & 1) ? ra : rb;
-            const int at = (p.zl0 + j) * S::NCOL + p.col;
-            if (RULE && zin && vr) R[at] = (R[at] + (par ? o : e));
-            if (zin && vbk) B[at] = (B[at] + (par ? e : o));
+            if (RULE && zin && vr) ur[j] = (ur[j] + (par ? o : e));
+            if (zin && vbk) ub[j] = (ub[j] + (par ? e : o));
         }
     }
+    tl_keep<S>(R, B, p, ur, ub);
     __syncthreads();
     unsigned long long best = 0;
     const auto leg = [&](auto edge) {
         constexpr bool Ed = decltype(edge)::value;
 #pragma unroll
         for (int it = 0; it < NPOST; it++) {
-            tl_sweep<0, RULE, Ed, S>(R, B, fr, p, 2 * (NPOST - it) - 1 + NORM, h2, inv2d, gr);
+            tl_sweep<0, RULE, Ed, true, S>(R, B, ur, ub, fr, p, 2 * (NPOST - it) - 1 + NORM, h2, inv2d, gr);
             __syncthreads();
-            tl_sweep<1, RULE, Ed, S>(R, B, fb, p, 2 * (NPOST - it) - 2 + NORM, h2, inv2d, gr);
-            __syncthreads();
+            if (NORM || it + 1 < NPOST) {
+                tl_sweep<1, RULE, Ed, true, S>(R, B, ur, ub, fb, p, 2 * (NPOST - it) - 2 + NORM, h2, inv2d, gr);
+                __syncthreads();
+            } else {
+                tl_sweep<1, RULE, Ed, false, S>(R, B, ur, ub, fb, p, 0, h2, inv2d, gr);
+            }
         }
         if constexpr (NORM) {
             C rr[S::PZ], rb[S::PZ];
-            tl_resid<0, RULE, Ed, S>(R, B, fr, p, inv_h2, gr, rr);
-            tl_resid<1, RULE, Ed, S>(R, B, fb, p, inv_h2, gr, rb);
+            tl_resid<0, RULE, Ed, S>(R, B, ur, ub, fr, p, inv_h2, gr, rr);
+            tl_resid<1, RULE, Ed, S>(R, B, ur, ub, fb, p, inv_h2, gr, rb);
 #pragma unroll
             for (int j = 0; j < S::PZ; j++) {
                 const unsigned long long a = abs_bits((double)rr[j]), b = abs_bits((double)rb[j]);
@@ -496,9 +553,8 @@ k_tile_up3(const T* __restrict__ u_in, const T* ring, const T* __restrict__ f, S
         for (int j = 0; j < S::PZ; j++) {
             const int pk = p.pk0 + j;
             if (pk < r.zlo || pk > r.zhi) continue;
-            const int at = (p.zl0 + j) * S::NCOL + p.col;
-            if ((j & 1) ? rb : ra) u_out[(size_t)pk * g.ps + base] = R[at];
-            if ((j & 1) ? ra : rb) u_out[g.cs + (size_t)pk * g.ps + base] = B[at];
+            if ((j & 1) ? rb : ra) u_out[(size_t)pk * g.ps + base] = ur[j];
+            if ((j & 1) ? ra : rb) u_out[g.cs + (size_t)pk * g.ps + base] = ub[j];
         }
     }
     if constexpr (NORM) block_max_to_w<S::NT / 64, true>(best, maxbits);
@@ -531,13 +587,13 @@ bool level_legs_fit(int n_pre, int n_post)
 
 // Small blocks while there is a CU for each; wide ones up to a workgroup per CU (1024 small
 // ones or 256 wide; batch members included).  Beyond that their halo (four to eight times
-// the block's work, which idle CUs do for nothing) costs more than streaming in FP64, and
-// than the per-pass kernels in FP32.  Measured in FP64, the coarse legs of two pre- and one
-// post-smoothing sweep (small / wide / streamed / per pass): 33^3 points (125 small blocks)
-// 9.9 + 7.5 / 14.7 + 9.9 / 22.8 + 13.2 / 31 us; 49^3 (343) 18.5 + 10.0 / 15.4 + 10.0 / 23.9
-// + 13.4; 65^3 (729) 27.0 + 12.5 / 15.8 + 10.1 / 23.7 + 13.5 / 41; 81^3 (1331) 48 + 20 /
-// 29.4 + 18.3 / 28.2 + 16.6.  FP32 V(1,2): 33^3 6.0 + 9.2 / 7.0 + 12.6, 65^3 9.2 + 18.9 /
-// 8.1 + 13.8 against 35 per pass, 129^3 20 + 49 (in blocks of 16^3) against 51.
+// the block's work, which idle CUs do for nothing) costs about what streaming does in FP64,
+// and more than the per-pass kernels in FP32.  Measured in FP64, the coarse legs of two pre-
+// and one post-smoothing sweep (small / wide / streamed / per pass): 33^3 points (125 small
+// blocks) 9.1 + 6.6 / 13.1 + 8.3 / 22.8 + 13.2 / 31 us; 49^3 (343) 16.3 + 9.1 / 13.3 + 8.5 /
+// 23.9 + 13.4; 65^3 (729) 23.9 + 13.9 / 13.5 + 8.6 / 23.7 + 13.5 / 41; 81^3 (1331) 43 + 21 /
+// 25.5 + 15.1 / 28.2 + 16.6.  FP32 V(1,2): 33^3 5.5 + 8.1 / 6.5 + 11.0, 65^3 8.7 + 16.9 /
+// 6.7 + 11.9 against 35 per pass, 129^3 20 + 49 (in blocks of 16^3) against 51.
 constexpr long kTileBlocks = 1024, kTileSmall = 256;
 
 bool level_tile(int dim, const SGrid& g)

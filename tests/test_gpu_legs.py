@@ -59,6 +59,17 @@ def test_sizes_fp64(n, pre, post):
     _same(_one(*n), n_pre=pre, n_post=post, max_cycles=8)
 
 
+# the coarse levels' boundary rules in block form, on each axis in turn: last point x_N = 1 with N
+# odd (51) and even (22, 28) on the second level, below it a coefficient of -3 with N odd (11) and
+# even (14)
+@pytest.mark.parametrize("n", [(200, 84, 108), (84, 108, 200), (108, 200, 84)], ids=lambda n: "x".join(map(str, n)))
+@pytest.mark.parametrize("kw", [dict(n_pre=2, n_post=1), dict(n_pre=1, n_post=2),
+                                dict(precision="fp32_dc", inner_cycles=2), dict(precision="fp16s_dc", inner_cycles=2, n_pre=1, coarse_post=2)],
+                         ids=lambda kw: "-".join("%s=%s" % a for a in kw.items()))
+def test_boundary_rules(n, kw):
+    _same(_one(*n), max_cycles=8, **kw)
+
+
 @pytest.mark.parametrize("kw", [dict(), dict(n_pre=1), dict(n_post=2), dict(n_pre=1, coarse_post=2),
                                 dict(buffer="interp"), dict(stop_rule="force_delta")],
                          ids=lambda kw: "-".join("%s=%s" % a for a in kw.items()) or "default")
