@@ -7,7 +7,7 @@
 //   down: the pre-smoothing sweeps, the residual and its restriction;
 //   up:   the prolongation and correction, the post-smoothing sweeps and (for
 //         the stop test) the residual's max norm.
-// A workgroup owns a block of 8 x 8 x 8 or 16 x 16 x 8 points and takes it through every half
+// A workgroup owns a block of 4 x 4 x 4 to 16 x 16 x 8 points and takes it through every half
 // sweep of the leg in LDS, together with a halo one point wide per half sweep that
 // follows (H in all), which it recomputes: a point at distance d from the block is
 // relaxed only by the half sweeps whose values can still reach the block.  Halo
@@ -21,11 +21,11 @@
 // registers, and the potential of the region lies in LDS too for the neighbours in x and
 // y and at the ends of the range (colour-split, so that lanes read consecutive elements):
 // three loads per point.  A leg is bound by its half sweeps' LDS loads and additions
-// (about 1 us each): 9.1 us down and 6.6 us up for V(2,1) on 33^3 points in FP64, against
-// 31 us in per-pass kernels.  With the columns' values read back from LDS (4.5 loads per
+// (up to 1 us each): 8.6 us down and 5.5 us up for V(2,1) on 33^3 points in FP64, against
+// 31 us in per-pass kernels.  In blocks of 8 x 8 x 8 points, with the columns' values read back from LDS (4.5 loads per
 // point, 5.5 beside the boundary) and the boundary rule formed by selects per neighbour:
-// 9.8 + 7.2 us (a half sweep 2300 cycles, 3000 beside the boundary); 65^3 15.3 + 9.6
-// against 13.4 + 8.6, FP32 V(1,2) up 13.0 against 11.9.
+// 9.8 + 7.2 us against 9.1 + 6.6 (a half sweep 2300 cycles, 3000 beside the boundary); 65^3
+// in wide blocks 15.3 + 9.6 against 13.4 + 8.6, FP32 V(1,2) up 13.0 against 11.9.
 #include <type_traits>
 
 #include "np_device.h"
@@ -564,20 +564,27 @@ k_tile_up3(const T* __restrict__ u_in, const T* ring, const T* __restrict__ f, S
 
 // ------------------------------------------------------------------ launches
 // Block shapes per halo width H (one point per half sweep or residual that follows), G
-// ranges of PZ planes each.  Small: 8 x 8 x 8 points, the shortest chains and the most
-// workgroups; wide: 16 x 16 x 8 points, half the halo per point.
-template <int H, bool WIDE>
-struct TlPick {
-    using S = TlShape<H, 8, 8, (8 + 2 * H + 3) / 4, 4>;
-};
-template <> struct TlPick<2, true> { using S = TlShape<2, 16, 8, 3, 4>; };
-template <> struct TlPick<3, true> { using S = TlShape<3, 16, 8, 4, 4>; };
-template <> struct TlPick<4, true> { using S = TlShape<4, 16, 8, 3, 6>; };
-template <> struct TlPick<5, true> { using S = TlShape<5, 16, 8, 2, 10>; };
+// ranges of PZ planes each.  The smaller a block, the shorter its chains and the more
+// halo per point: 4 x 4 x 4, 8 x 8 x 4, 8 x 8 x 8 or 16 x 16 x 8 points.  Two planes per
+// thread where that fits 16 wavefronts.
+enum class Form { tiny, flat, small, wide };
 
-static long tl_blocks(const SGrid& g, int tx)
+template <int H, int TX, int TZ, int PZ>
+using TlEven = TlShape<H, TX, TZ, (TZ + 2 * H + PZ - 1) / PZ, PZ>;
+
+template <int H, Form F>
+struct TlPick;
+template <int H> struct TlPick<H, Form::tiny> { using S = TlEven<H, 4, 4, 2>; };
+template <int H> struct TlPick<H, Form::flat> { using S = TlEven<H, 8, 4, (H <= 3 ? 2 : 4)>; };
+template <int H> struct TlPick<H, Form::small> { using S = TlEven<H, 8, 8, (H <= 3 ? 2 : 4)>; };
+template <> struct TlPick<2, Form::wide> { using S = TlShape<2, 16, 8, 3, 4>; };
+template <> struct TlPick<3, Form::wide> { using S = TlShape<3, 16, 8, 4, 4>; };
+template <> struct TlPick<4, Form::wide> { using S = TlShape<4, 16, 8, 3, 6>; };
+template <> struct TlPick<5, Form::wide> { using S = TlShape<5, 16, 8, 2, 10>; };
+
+static long tl_blocks(const SGrid& g, int tx, int tz)
 {
-    return (long)ceil_div(g.nx - 2, tx) * ceil_div(g.ny - 2, tx) * ceil_div(g.nz - 2, 8);
+    return (long)ceil_div(g.nx - 2, tx) * ceil_div(g.ny - 2, tx) * ceil_div(g.nz - 2, tz);
 }
 
 bool level_legs_fit(int n_pre, int n_post)
@@ -585,50 +592,57 @@ bool level_legs_fit(int n_pre, int n_post)
     return (n_pre == 1 || n_pre == 2) && (n_post == 1 || n_post == 2);
 }
 
-// Small blocks while there is a CU for each; wide ones up to a workgroup per CU (1024 small
-// ones or 256 wide; batch members included).  Beyond that their halo (four to eight times
+// The smallest blocks of which there is at most one per CU; wide ones up to 1024 small blocks'
+// worth (256 wide; batch members included).  Beyond that their halo (four to eight times
 // the block's work, which idle CUs do for nothing) costs about what streaming does in FP64,
 // and more than the per-pass kernels in FP32.  Measured in FP64, the coarse legs of two pre-
-// and one post-smoothing sweep (small / wide / streamed / per pass): 33^3 points (125 small
-// blocks) 9.1 + 6.6 / 13.1 + 8.3 / 22.8 + 13.2 / 31 us; 49^3 (343) 16.3 + 9.1 / 13.3 + 8.5 /
-// 23.9 + 13.4; 65^3 (729) 23.9 + 13.9 / 13.5 + 8.6 / 23.7 + 13.5 / 41; 81^3 (1331) 43 + 21 /
-// 25.5 + 15.1 / 28.2 + 16.6.  FP32 V(1,2): 33^3 5.5 + 8.1 / 6.5 + 11.0, 65^3 8.7 + 16.9 /
-// 6.7 + 11.9 against 35 per pass, 129^3 20 + 49 (in blocks of 16^3) against 51.
-constexpr long kTileBlocks = 1024, kTileSmall = 256;
+// and one post-smoothing sweep (tiny / flat / small / wide), down + up: 17^3 points (125 tiny
+// blocks) 6.3 + 4.9 / 8.5 + 5.4 / 8.9 + 5.9 us; 25^3 (343) 8.9 + 5.5 / 8.5 + 5.4 / 9.0 + 6.0;
+// 33^3 (225 flat) 12.1 + 6.4 / 8.6 + 5.5 / 9.1 + 6.1 / 13.1 + 8.3; 41^3 (396) - / 15.5 + 7.0 /
+// 9.2 + 6.1; and small / wide / streamed / per pass: 33^3 - / - / 22.8 + 13.2 / 31; 49^3 (343
+// small) 16.3 + 9.1 / 13.3 + 8.5 / 23.9 + 13.4; 65^3 (729) 23.9 + 13.9 / 13.5 + 8.6 / 23.7 +
+// 13.5 / 41; 81^3 (1331) 43 + 21 / 25.5 + 15.1 / 28.2 + 16.6.  FP32 V(1,2): 17^3 4.2 + 6.1 /
+// 4.5 + 7.7 / 5.0 + 7.8, 33^3 5.2 + 11.7 / 4.6 + 7.9 / 5.1 + 8.1 / 6.5 + 11.0, 65^3 wide 6.7 +
+// 11.9 against 35 per pass, 129^3 20 + 49 (in blocks of 16^3) against 51.
+constexpr long kTileBlocks = 1024, kTileCUs = 256;
 
 bool level_tile(int dim, const SGrid& g)
 {
     if (dim == 2) return true;
-    return tl_blocks(g, 8) * g.nb <= kTileBlocks;
+    return tl_blocks(g, 8, 8) * g.nb <= kTileBlocks;
 }
 
-static bool tl_wide(const SGrid& g) { return tl_blocks(g, 8) * g.nb > kTileSmall; }
+// calls go with the form of the level's blocks
+template <typename Fn>
+static void tl_form(const SGrid& g, Fn go)
+{
+    if (tl_blocks(g, 4, 4) * g.nb <= kTileCUs) go(std::integral_constant<Form, Form::tiny>{});
+    else if (tl_blocks(g, 8, 4) * g.nb <= kTileCUs) go(std::integral_constant<Form, Form::flat>{});
+    else if (tl_blocks(g, 8, 8) * g.nb <= kTileCUs) go(std::integral_constant<Form, Form::small>{});
+    else go(std::integral_constant<Form, Form::wide>{});
+}
 
 template <typename T, int NPRE, bool RULE>
 static void down3(hipStream_t st, const LevelLeg& a, const T* u_in, const T* f, T* u_out, T* fc)
 {
-    const auto go = [&](auto wide) {
-        using S = typename TlPick<2 * NPRE + !RULE, decltype(wide)::value>::S;
-        hipLaunchKernelGGL((k_tile_down3<T, NPRE, RULE, S>), dim3((unsigned)tl_blocks(a.g, S::TX), a.g.nb), dim3(S::NT), 0,
+    tl_form(a.g, [&](auto form) {
+        using S = typename TlPick<2 * NPRE + !RULE, decltype(form)::value>::S;
+        hipLaunchKernelGGL((k_tile_down3<T, NPRE, RULE, S>), dim3((unsigned)tl_blocks(a.g, S::TX, S::TZ), a.g.nb), dim3(S::NT), 0,
                            st, u_in, f, a.g, u_out, (T)a.h2, (T)(1.0 / 6.0), (T)a.inv_h2, (T)0.125, grule<T>(a.rule), a.gc,
                            fc, ceil_div(a.g.nx - 2, S::TX), ceil_div(a.g.ny - 2, S::TX), a.rev);
-    };
-    if (tl_wide(a.g)) go(std::true_type{});
-    else go(std::false_type{});
+    });
 }
 
 template <typename T, int NPOST, bool RULE>
 static void up3(hipStream_t st, const LevelLeg& a, const T* u_in, const T* ring, const T* f, T* u_out, const T* ec,
                 unsigned long long* maxbits)
 {
-    const auto go = [&](auto wide) {
-        using S = typename TlPick<2 * NPOST + !RULE, decltype(wide)::value>::S;
-        hipLaunchKernelGGL((k_tile_up3<T, NPOST, RULE, S>), dim3((unsigned)tl_blocks(a.g, S::TX), a.g.nb), dim3(S::NT), 0, st,
+    tl_form(a.g, [&](auto form) {
+        using S = typename TlPick<2 * NPOST + !RULE, decltype(form)::value>::S;
+        hipLaunchKernelGGL((k_tile_up3<T, NPOST, RULE, S>), dim3((unsigned)tl_blocks(a.g, S::TX, S::TZ), a.g.nb), dim3(S::NT), 0, st,
                            u_in, ring, f, a.g, u_out, (T)a.h2, (T)(1.0 / 6.0), (T)a.inv_h2, grule<T>(a.rule), a.gc, ec,
                            grule<T>(a.coarse_rule), ceil_div(a.g.nx - 2, S::TX), ceil_div(a.g.ny - 2, S::TX), a.rev, maxbits);
-    };
-    if (tl_wide(a.g)) go(std::true_type{});
-    else go(std::false_type{});
+    });
 }
 
 template <typename T>

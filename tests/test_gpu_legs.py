@@ -59,6 +59,16 @@ def test_sizes_fp64(n, pre, post):
     _same(_one(*n), n_pre=pre, n_post=post, max_cycles=8)
 
 
+# both sides of the limits between the block shapes (256 blocks), on level 0 (24 | 26, 40 | 42,
+# 48 | 52 points an axis) and on the first coarse level (24 | 26, 38 | 41)
+@pytest.mark.parametrize("n", [22, 24, 38, 40, 46, 50, 74, 80])
+@pytest.mark.parametrize("kw", [dict(n_pre=2, n_post=1), dict(n_pre=1, n_post=2), dict(precision="fp32_dc", inner_cycles=2),
+                                dict(precision="fp32_dc", n_pre=1, inner_cycles=2, coarse_post=2)],
+                         ids=lambda kw: "-".join("%s=%s" % a for a in kw.items()))
+def test_block_shapes(n, kw):
+    _same(_one(n, n, n), max_cycles=8, **kw)
+
+
 # the coarse levels' boundary rules in block form, on each axis in turn: last point x_N = 1 with N
 # odd (51) and even (22, 28) on the second level, below it a coefficient of -3 with N odd (11) and
 # even (14)
