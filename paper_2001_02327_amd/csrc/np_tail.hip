@@ -135,6 +135,31 @@ __device__ __forceinline__ C tail_sum(const C* lds, const TailPoint<D, C>& p)
     return s;
 }
 
+// Where the residuals of a coarse point's children lie (fine level of Nf points in
+// natural order): the first child's and the steps to the second one along each axis, 0
+// where that is outside the fine level (what is read instead is dropped).  The slot past an
+// odd N_x (of the coarse level) holds no point: it takes the last point's children, so
+// that every read stays inside the fine level's residuals.
+struct TailKids {
+    int at, dx, dy, dz;
+    bool inx, iny, inz;
+};
+
+template <int D>
+__host__ __device__ __forceinline__ TailKids tail_kids(int i, int j, int k, int N, const int (&Nf)[3])
+{
+    const int i0 = 2 * (i < N ? i : N) - 2, j0 = 2 * j - 2, k0 = D == 3 ? 2 * k - 2 : 0;
+    TailKids q;
+    q.inx = i0 + 1 < Nf[0];
+    q.iny = j0 + 1 < Nf[1];
+    q.inz = D == 3 && k0 + 1 < Nf[2];
+    q.at = (k0 * Nf[1] + j0) * Nf[0] + i0;
+    q.dx = q.inx ? 1 : 0;
+    q.dy = q.iny ? Nf[0] : 0;
+    q.dz = q.inz ? Nf[0] * Nf[1] : 0;
+    return q;
+}
+
 // a level's parameters from LDS into scalar registers
 template <typename C>
 __device__ __forceinline__ TailLevel<C> tail_uniform(const TailLevel<C>& level)
@@ -231,19 +256,15 @@ struct TailVisit {
 #pragma unroll
             for (int c = 0; c < 2; c++) {
                 const TailPoint<D, C>& p = q.p[c];
-                // children outside the fine level: the last one inside, dropped
-                const int i0 = 2 * p.i - 2, j0 = 2 * q.j - 2, k0 = D == 3 ? 2 * q.k - 2 : 0;
-                const bool inx = i0 + 1 < Nf[0], iny = j0 + 1 < Nf[1], inz = D == 3 && k0 + 1 < Nf[2];
-                const int at = min((k0 * Nf[1] + j0) * Nf[0] + i0, Nf[0] * Nf[1] * Nf[2] - 1);
-                const int dx = inx ? 1 : 0, dy = iny ? Nf[0] : 0, dz = inz ? Nf[0] * Nf[1] : 0;
+                const TailKids kid = tail_kids<D>(p.i, q.j, q.k, v.N[0], Nf);
                 C ch[1 << D];
 #pragma unroll
                 for (int e = 0; e < (1 << D); e++)
-                    ch[e] = res[at + ((e & 1) ? dx : 0) + ((e & 2) ? dy : 0) + ((e & 4) ? dz : 0)];
+                    ch[e] = res[kid.at + ((e & 1) ? kid.dx : 0) + ((e & 2) ? kid.dy : 0) + ((e & 4) ? kid.dz : 0)];
                 C w = 0;
 #pragma unroll
                 for (int e = 0; e < (1 << D); e++) {
-                    const bool in = (!(e & 1) || inx) && (!(e & 2) || iny) && (!(e & 4) || inz);
+                    const bool in = (!(e & 1) || kid.inx) && (!(e & 2) || kid.iny) && (!(e & 4) || kid.inz);
                     w += in ? ch[e] : (C)0;
                 }
                 sum[r][c] = w * (C)(D == 3 ? 0.125 : 0.25);
