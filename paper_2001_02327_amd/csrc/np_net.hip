@@ -1315,6 +1315,13 @@ void net_conv_fwd_bf16_to_f32(hipStream_t st, const uint16_t* in, int cin, const
 void net_conv_mfma(hipStream_t st, const uint16_t* in, int cin, const uint16_t* w, const float* bias, int cout, int relu,
                    int B, int Z, int Y, int X, void* out)
 {
+    // a row is one buffer, whose size and the offset that stands for "outside" (kCvOob) need
+    // 31 bits: longer rows, of 2^26 voxels and more, go to the thread-per-voxel kernels
+    if ((long)X * 16 * (long)sizeof(uint16_t) >= (long)kCvOob) {
+        if (cout == 16) net_conv_fwd_bf16(st, in, cin, w, bias, cout, relu, B, Z, Y, X, (uint16_t*)out);
+        else net_conv_fwd_bf16_to_f32(st, in, cin, w, bias, cout, relu, B, Z, Y, X, (float*)out);
+        return;
+    }
     const auto launch = [&](auto ci, auto co, auto rows, auto* o, int per_cu) {
         constexpr int R = decltype(rows)::value;
         const int ntx = cdiv(X, 16), nty = cdiv(Y, R * kCvWaves);
