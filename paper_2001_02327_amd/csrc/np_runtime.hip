@@ -299,7 +299,10 @@ struct np_solver {
     // multigrid scratch for L >= 1, shared by the levels (sized for the largest)
     double* mg_u[NP_MAX_MG] = {};
     double* mg_f[NP_MAX_MG] = {};
-    // results of the fused up legs on levels L >= 1 (use_legs)
+    // what the fused legs need beyond the per-pass kernels: results of the up legs on levels
+    // L >= 1 and in FP64 a second potential buffer (phi_alt) for a whole batch.  Without the
+    // memory for it the handle runs the per-pass kernels (legs off)
+    bool legs = true;
     double* mg_r[NP_MAX_MG] = {};
     float* mg_r32[NP_MAX_MG] = {};
     double* force_scratch = nullptr;  // FORCE_DELTA stop rule
@@ -507,11 +510,12 @@ void coarse_sweep(const np_solver* s, int l, const MGView<T>& v, int L, hipStrea
 int coarse_npost(const np_config& c) { return c.coarse_post >= 0 ? c.coarse_post : c.n_post; }
 
 // Fused legs (one launch down and one up per multigrid level, np_tile.hip, np_tile2.hip and np_stream.hip) hold one or
-// two sweeps; other counts and the sweep modes that name another form run the
-// per-pass kernels.
-bool legs_cfg(const np_config& c)
+// two sweeps; other counts, the sweep modes that name another form and a handle without
+// the memory for their buffers run the per-pass kernels.
+bool legs_cfg(const np_solver* s)
 {
-    return (c.sweep == NP_SWEEP_FULL || c.sweep == NP_SWEEP_FUSED) && level_legs_fit(c.n_pre, c.n_post) &&
+    const np_config& c = s->cfg;
+    return s->legs && (c.sweep == NP_SWEEP_FULL || c.sweep == NP_SWEEP_FUSED) && level_legs_fit(c.n_pre, c.n_post) &&
            level_legs_fit(c.n_pre, coarse_npost(c));
 }
 
@@ -523,7 +527,7 @@ bool legs_cfg(const np_config& c)
 int tail_level(const np_solver* s, int l, size_t esz)
 {
     const int nmg = s->plan.nmg[l];
-    const bool legs = legs_cfg(s->cfg);
+    const bool legs = legs_cfg(s);
     for (int L = 1; L < nmg; L++) {
         const int nlev = nmg - L;
         if (nlev <= kTailMaxLevels &&
@@ -559,7 +563,7 @@ constexpr size_t kStreamPoints32 = 1 << 23;
 int legs_level(const np_solver* s, int l)
 {
     const int nmg = s->plan.nmg[l];
-    if (!legs_cfg(s->cfg)) return nmg;
+    if (!legs_cfg(s)) return nmg;
     const bool fp64 = s->cfg.precision == NP_PREC_FP64;
     const int Lt = tail_level(s, l, fp64 ? sizeof(double) : sizeof(float));
     if (Lt == 0) return nmg;
@@ -1243,7 +1247,7 @@ int solve_batch(np_solver* s, const PatchGroup& G, const double* const* rho, dou
     MGView<double> v = mg_view<double>(s, m0, s->mg_u, s->mg_f, s->mg_r);
     for (int L = 0; L < v.nmg; L++) v.g[L] = batched(v.g[L], n, s->d_act);
     const SGrid g0 = v.g[0];
-    const bool legs = use_legs(s, m0) && s->phi_alt;
+    const bool legs = use_legs(s, m0);
     // stop-test norms of the members still iterating into their slots (with fused
     // legs the cycle has put them there), to the host
     auto norms = [&](bool first, bool launch) -> int {
@@ -1420,6 +1424,35 @@ int alloc_dev(np_solver* s, void** p, size_t bytes)
     return NP_OK;
 }
 
+// The buffers of the fused legs (mg_best: elements of each multigrid level's arrays), after
+// everything that a solve cannot do without; where they do not fit, no legs.
+void alloc_legs(np_solver* s, const size_t* mg_best)
+{
+    const bool dc = s->cfg.precision != NP_PREC_FP64;
+    int first = NP_MAX_MG;  // first level with fused legs
+    for (int gi = 0; gi < s->ngroups; gi++) first = std::min(first, legs_level(s, s->groups[gi].member[0]));
+    int rc = NP_OK;
+    for (int L = std::max(first, 1); L < NP_MAX_MG && mg_best[L] && rc == NP_OK; L++)
+        rc = dc ? alloc_dev(s, (void**)&s->mg_r32[L], mg_best[L] * sizeof(float))
+                : alloc_dev(s, (void**)&s->mg_r[L], mg_best[L] * sizeof(double));
+    if (rc == NP_OK && !dc && first == 0) {
+        size_t best = 0;  // a batch's members side by side
+        for (int gi = 0; gi < s->ngroups; gi++)
+            best = std::max(best, s->groups[gi].n * 2 * s->lg[s->groups[gi].member[0]].cs);
+        s->alt_cap = best * sizeof(double);
+        rc = alloc_dev(s, (void**)&s->phi_alt, s->alt_cap);
+    }
+    if (rc == NP_OK) return;
+    s->legs = false;
+    s->err[0] = 0;
+    for (int L = 0; L < NP_MAX_MG; L++) {
+        if (s->mg_r[L]) (void)hipFree(s->mg_r[L]);
+        if (s->mg_r32[L]) (void)hipFree(s->mg_r32[L]);
+        s->mg_r[L] = nullptr;
+        s->mg_r32[L] = nullptr;
+    }
+}
+
 }  // namespace
 
 // ------------------------------------------------------------------ C ABI
@@ -1503,10 +1536,9 @@ int nested_poisson_create(const np_config* cfg, void* hip_stream, np_solver** ou
     // multigrid scratch: per level L the largest grid over the nested levels,
     // FP64 for the plain solve, FP32 for the defect correction's inner cycles
     const bool dc = cfg->precision != NP_PREC_FP64;
-    int legs_min = NP_MAX_MG;  // first level with fused legs
-    for (int gi = 0; gi < s->ngroups; gi++) legs_min = std::min(legs_min, legs_level(s, s->groups[gi].member[0]));
+    size_t mg_best[NP_MAX_MG] = {};
     for (int L = 1; L < NP_MAX_MG && rc == NP_OK; L++) {
-        size_t best = 0;
+        size_t& best = mg_best[L];
         for (int gi = 0; gi < s->ngroups; gi++) {
             const int l = s->groups[gi].member[0];
             if (L < s->plan.nmg[l]) {
@@ -1518,11 +1550,9 @@ int nested_poisson_create(const np_config* cfg, void* hip_stream, np_solver** ou
         if (dc) {
             rc = alloc_dev(s, (void**)&s->mg_u32[L], best * sizeof(float));
             if (rc == NP_OK) rc = alloc_dev(s, (void**)&s->mg_f32[L], best * sizeof(float));
-            if (rc == NP_OK && L >= legs_min) rc = alloc_dev(s, (void**)&s->mg_r32[L], best * sizeof(float));
         } else {
             rc = alloc_dev(s, (void**)&s->mg_u[L], best * sizeof(double));
             if (rc == NP_OK) rc = alloc_dev(s, (void**)&s->mg_f[L], best * sizeof(double));
-            if (rc == NP_OK && L >= legs_min) rc = alloc_dev(s, (void**)&s->mg_r[L], best * sizeof(double));
         }
     }
     if (rc == NP_OK && cfg->buffer == NP_BUFFER_INTERP && cfg->nlevels > 1) {
@@ -1546,15 +1576,6 @@ int nested_poisson_create(const np_config* cfg, void* hip_stream, np_solver** ou
         if (rc == NP_OK) rc = alloc_dev(s, (void**)&s->r32, best * sizeof(float));
         s->alt_cap = best * sizeof(double);
         if (rc == NP_OK) rc = alloc_dev(s, (void**)&s->phi_alt, s->alt_cap);
-    }
-    if (rc == NP_OK && !dc &&
-        (legs_min == 0 || (d == 3 && cfg->sweep != NP_SWEEP_HALF && cfg->n_pre >= 1 && cfg->n_post >= 1))) {
-        // the second potential buffer of the fused legs (a batch's members side by
-        // side) and of the full sweeps
-        size_t best = 0;
-        for (int gi = 0; gi < s->ngroups; gi++) best = std::max(best, s->groups[gi].n * 2 * s->lg[s->groups[gi].member[0]].cs);
-        s->alt_cap = best * sizeof(double);
-        rc = alloc_dev(s, (void**)&s->phi_alt, s->alt_cap);
     }
     if (rc == NP_OK && cfg->guess == NP_GUESS_LEARNED) {
         size_t vox = 0;
@@ -1588,6 +1609,14 @@ int nested_poisson_create(const np_config* cfg, void* hip_stream, np_solver** ou
         (void)hipGetLastError();
         s->h_act = nullptr;
         rc = NP_ENOMEM;
+    }
+    if (rc == NP_OK) alloc_legs(s, mg_best);
+    if (rc == NP_OK && !dc && !s->phi_alt && d == 3 && cfg->sweep != NP_SWEEP_HALF && cfg->n_pre >= 1 && cfg->n_post >= 1) {
+        // the second potential buffer of the full sweeps
+        size_t best = 0;
+        for (int l = 0; l < cfg->nlevels; l++) best = std::max(best, 2 * s->lg[l].cs);
+        s->alt_cap = best * sizeof(double);
+        rc = alloc_dev(s, (void**)&s->phi_alt, s->alt_cap);
     }
     if (rc != NP_OK) {
         snprintf(g_last_error, sizeof g_last_error, "%s", s->err);
@@ -1760,7 +1789,7 @@ int nested_poisson_solve(np_solver* s, const double* const* rho, const double* p
         }
         // full sweeps write the active points of the spare buffer: the same
         const bool fs = !dc && full_sweeps(s, l);
-        const bool legs = !dc && use_legs(s, l) && s->phi_alt;
+        const bool legs = !dc && use_legs(s, l);
         bool first_done = false;  // the next cycle's first pre-smoothing sweep has run
         if (fs) launch_copy_ghosts(c.dim, s->stream, s->lg[l], s->phi[l], s->phi_alt);
         for (;;) {
