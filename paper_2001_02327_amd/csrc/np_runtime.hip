@@ -310,6 +310,7 @@ struct np_solver {
     unsigned long long* h_words = nullptr;  // pinned: two words per slot (read_slots)
     unsigned long long h_bits[kBitSlots] = {};  // the slots last read
     unsigned bits_seq = 0;                 // number of the last read queued
+    bool yields = false;                   // the device's scheduling flags, as a solve found them: wait without spinning
     int fixed[NP_MAX_LEVELS];
     bool has_fixed = false;
     bool solved = false;
@@ -781,7 +782,8 @@ constexpr long kFullSweepMinWaves = 4096;
 // Queues the read of n reduction slots from `slot` on, which zeroes them for their next
 // use, and waits for it: a kernel writes them to pinned memory with the read's number in
 // every word, and the host polls the words.  A copy and a synchronisation of the
-// stream took 20 us more per V-cycle.
+// stream took 20 us more per V-cycle.  A caller who asked the device not to keep a core busy
+// while it waits (hipDeviceScheduleYield or BlockingSync) gets the stream's own wait.
 int read_slots(np_solver* s, int slot, int n)
 {
     if (++s->bits_seq == 0) s->bits_seq = 1;  // (0: never written)
@@ -795,6 +797,10 @@ int read_slots(np_solver* s, int slot, int n)
             if ((unsigned)(__atomic_load_n(w + got, __ATOMIC_ACQUIRE) >> 32) != seq) return false;
         return true;
     };
+    if (s->yields) {
+        HIPCHK(s, hipStreamSynchronize(s->stream));
+        if (!poll()) return set_err(s, NP_EHIP, "a stop test's norm did not reach the host");
+    }
     for (unsigned spin = 1; !poll(); spin++) {
         if (spin % 4096 == 0) {
             // still running, done (the words are there, then), or failed
@@ -967,6 +973,15 @@ int vcycle_lo(np_solver* s, int l, bool red_done)
     }
     return vcycle_t<TL, float>(s, l, (TL*)s->e_lo, (const TL*)s->r_lo, 1.0, 1.0, 1.0 / (h * h), v, s->coarse_exec32,
                                red_done, red_done && dc_seed_black(s, l));
+}
+
+// Takes over the scheduling flags of the handle's device (the current one).
+int device_flags(np_solver* s)
+{
+    unsigned fl = 0;
+    HIPCHK(s, hipGetDeviceFlags(&fl));
+    s->yields = (fl & (hipDeviceScheduleYield | hipDeviceScheduleBlockingSync)) != 0;
+    return NP_OK;
 }
 
 // A norm into slot 0; norm_sync returns it (host-synchronous).
@@ -1657,6 +1672,7 @@ int nested_poisson_solve(np_solver* s, const double* const* rho, const double* p
     for (int l = 0; l < s->cfg.nlevels; l++)
         if (!rho[l]) return set_err(s, NP_EINVAL, "rho[%d] is null", l);
     HIPCHK(s, hipSetDevice(s->device));
+    if (int rc = device_flags(s)) return rc;
     const np_config& c = s->cfg;
     const int d = c.dim;
     const double fourpiG = 4.0 * M_PI * c.G;
@@ -2058,6 +2074,7 @@ int nested_poisson_guess_features(np_solver* s, int level, float* x, float* targ
         return set_err(s, NP_EINVAL, "features need a 3-D level >= 1 and an output array");
     if (!s->solved) return set_err(s, NP_ESTATE, "features requested before a successful solve");
     HIPCHK(s, hipSetDevice(s->device));
+    if (int rc = device_flags(s)) return rc;
     if (!s->feat_phi) {
         size_t best = 0;
         for (int l = 0; l < c.nlevels; l++)
