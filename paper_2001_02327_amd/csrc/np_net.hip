@@ -1253,6 +1253,45 @@ static bool aligned16(const void* a, const void* b, const void* c)
     return (((uintptr_t)a | (uintptr_t)b | (uintptr_t)c) & 15) == 0;
 }
 
+// planes per workgroup of the few-channel kernel: 8 (1.25 times the input read)
+// where that gives two workgroups per CU, else 2 for shorter chains
+static int few_planes(int B, int Z, int Y, int X)
+{
+    return (long)B * cdiv(X, kFewX) * cdiv(Y, kFewY) * cdiv(Z, 8) >= 512 ? 8 : 2;
+}
+
+static long few_workgroups(int B, int Z, int Y, int X)
+{
+    return (long)B * cdiv(X, kFewX) * cdiv(Y, kFewY) * cdiv(Z, few_planes(B, Z, Y, X));
+}
+
+// Whether a layer's forward pass is faster in blocks than with a thread per voxel (the results
+// are the same).  A block takes its time however many of its voxels lie in the volume, and a
+// chain of planes its time however few blocks there are; a thread per voxel has neither.
+// Measured, a thread per voxel / blocks: 16 -> 1 channels (0.092 ns a voxel; 22 ns a workgroup
+// of 2 planes after 12 us, 52 ns one of 8 after 24 us): 18^3 voxels 8.6 / 16.2 us, 50^3
+// 15.2 / 19.1, 58^3 23.2 / 18.8, 130^3 208 / 99, 130 x 130 x 6 14.6 / 31.6, x 16 31.7 / 33.8, x 20
+// 40.1 / 34.3; 2 -> 16: 130 x 130 x 6 10.5 / 13.6, x 14 16.2 / 14.4, x 17 18.7 / 22.0, x 26 26.6 / 22.3,
+// 66^3 18.8 / 16.5; 16 -> 16: 130 x 130 x 6 41.8 / 49.8, x 10 58.8 / 50.7, 66^3 91.5 / 53.4.
+// (The passes that round or mask as well, which a thread per voxel does in a second
+// kernel, are never slower in blocks, nor are the data gradients, but for bwd_in_blocks.)
+static bool fwd_in_blocks(int cin, int cout, int B, int Z, int Y, int X)
+{
+    const long n = (long)B * Z * Y * X, tiles = conv_tiles(B, Z, Y, X);
+    if (cout == 1) {
+        const long wgs = few_workgroups(B, Z, Y, X);
+        return few_planes(B, Z, Y, X) == 8 ? n > 200000 + 565 * wgs : n > 65000 + 200 * wgs;
+    }
+    return cin == 2 ? n + 26000 > 180 * tiles : n + 20000 > 115 * tiles;
+}
+
+// The data gradient of the 2 -> 16 layer: blocks except on long volumes of few voxels across
+// (4000 x 3 x 3: 79 us with a thread per voxel, 93 in blocks; 130 x 130 x 3: 80 and 61).
+static bool bwd_in_blocks(int B, int Z, int Y, int X)
+{
+    return (long)Y * X >= 25 || (few_planes(B, Z, Y, X) == 2 && few_workgroups(B, Z, Y, X) < 1600);
+}
+
 // input channels ci, output channels co of the pass (for the data gradient the
 // layer's output and input channels); false: not one of the layers' shapes
 template <bool BWD>
@@ -1266,17 +1305,14 @@ static bool train_conv(hipStream_t st, const float* in, int ci, const uint16_t* 
     // the small-channel kernel holds few weights: more, shorter ranges
     const long per1 = (tiles + 4 * kTrainBlocks - 1) / (4 * kTrainBlocks);
     const dim3 grid1((unsigned)((tiles + per1 - 1) / per1));
-    // planes per workgroup of the few-channel kernel: 8 (1.25 times the input read)
-    // where that gives two workgroups per CU, else 2 for shorter chains
-    const long cols = (long)B * cdiv(X, kFewX) * cdiv(Y, kFewY);
-    const int zch = cols * cdiv(Z, 8) >= 512 ? 8 : 2;
-    const long few = cols * cdiv(Z, zch);
+    const int zch = few_planes(B, Z, Y, X);
+    const long few = few_workgroups(B, Z, Y, X);
     if (ci == 16 && co == 16)
         hipLaunchKernelGGL(k_conv16_mfma_f32<BWD>, grid, dim3(256), 0, st, in, w, bias, B, Z, Y, X, P, out, per);
     else if (ci == (BWD ? 1 : 2) && co == 16)
         hipLaunchKernelGGL((k_conv_few_to16_mfma_f32<BWD ? 1 : 2, BWD>), grid1, dim3(256), 0, st, in, w, bias, B, Z, Y, X,
                            P, out, per1);
-    else if (ci == 16 && co == (BWD ? 2 : 1) && few < (1L << 31) && ((uintptr_t)w & 3) == 0)
+    else if (ci == 16 && co == (BWD ? 2 : 1) && few < (1L << 31) && ((uintptr_t)w & 3) == 0 && (!BWD || bwd_in_blocks(B, Z, Y, X)))
         hipLaunchKernelGGL((k_conv16_to_few_f32<BWD ? 2 : 1, BWD>), dim3((unsigned)few), dim3(256), 0, st, in, w, bias, B,
                            Z, Y, X, P, out, zch);
     else
@@ -1288,7 +1324,9 @@ void net_conv_fwd_f32(hipStream_t st, const float* in, int cin, const uint16_t* 
                       int B, int Z, int Y, int X, float* out)
 {
     long nv = (long)B * Z * Y * X;
-    if (train_conv<false>(st, in, cin, w, bias, cout, ConvPost{relu, 0, nullptr}, B, Z, Y, X, out)) return;
+    if (fwd_in_blocks(cin, cout, B, Z, Y, X) &&
+        train_conv<false>(st, in, cin, w, bias, cout, ConvPost{relu, 0, nullptr}, B, Z, Y, X, out))
+        return;
     if (conv_fwd_fixed(st, in, cin, w, bias, cout, relu, B, Z, Y, X, out)) return;
     hipLaunchKernelGGL((k_conv_fwd<float, float>), dim3(cdiv(nv, kNB)), dim3(kNB), 0, st, in, cin, w, bias, cout, relu, B,
                        Z, Y, X, out);
