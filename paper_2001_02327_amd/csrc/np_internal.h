@@ -216,34 +216,46 @@ struct LevelLeg {
 };
 bool level_legs_fit(int n_pre, int n_post);
 bool level_tile(int dim, const SGrid& g);
-// n_pre sweeps, then the residual's restriction into fc.  rule: a coarse level, from zero,
-// ghost values by its rule; otherwise (FP64) multigrid level 0 from u_in, ghost layer
-// in memory.  The smoothed values go to u_out: the black ones, with rule both
-// colours.  u_out must not be u_in (with rule u_in is not read)
+// Down: n_pre sweeps, then the residual's restriction into fc.  Up: u_in (as the leg down left
+// it) plus the prolonged ec, n_post sweeps, into u_out (both colours; not u_in).
+//
+// A coarse level: from zero, ghost values by the level's rule; u: both colours of the
+// smoothed values.
 template <typename T>
-void launch_level_down(hipStream_t st, const LevelLeg& a, int n_pre, bool rule, const T* u_in, const T* f, T* u_out, T* fc);
-// (streamed: kLegRule as with rule, kLegWarm as without it, FP32 as well; kLegZero as
-// kLegWarm from zero, FP32; the restricted residual times out_scale)
-constexpr int kLegRule = 0, kLegWarm = 1, kLegZero = 2;
+void launch_level_down(hipStream_t st, const LevelLeg& a, int n_pre, const T* f, T* u, T* fc);
 template <typename T>
-void launch_stream_down(hipStream_t st, const LevelLeg& a, int n_pre, int mode, const T* u_in, const T* f, T* u_out, T* fc,
-                        double out_scale);
-template <typename T>
-void launch_tile2_down(hipStream_t st, const LevelLeg& a, int n_pre, bool rule, const T* u_in, const T* f, T* u_out, T* fc);
-// u_in (as launch_level_down left it) plus the prolonged ec, n_post sweeps, into u_out
-// (both colours; not u_in).  Without rule the ghost layer is read from ring (which may
-// be u_out) and the max norm of the result's residual goes into maxbits (zeroed by
+void launch_level_up(hipStream_t st, const LevelLeg& a, int n_post, const T* u_in, const T* f, T* u_out, const T* ec);
+// Multigrid level 0 of an FP64 solve, its ghost layer in memory.  Down: from u_in, the
+// black smoothed values to u_out (not u_in).  Up: the ghost layer is read from ring
+// (which may be u_out), the max norm of the result's residual goes into maxbits (zeroed by
 // the caller; one slot per batch member)
+void launch_level0_down(hipStream_t st, const LevelLeg& a, int n_pre, const double* u_in, const double* f, double* u_out,
+                        double* fc);
+void launch_level0_up(hipStream_t st, const LevelLeg& a, int n_post, const double* u_in, const double* ring,
+                      const double* f, double* u_out, const double* ec, unsigned long long* maxbits);
+// Multigrid level 0 of a 3-D FP32 correction, streamed: the same without the norm, from zero or
+// from u_in, the restricted residual times out_scale; one post-smoothing sweep
+void launch_level0_down32(hipStream_t st, const LevelLeg& a, int n_pre, bool zero, const float* u_in, const float* f,
+                          float* u_out, float* fc, double out_scale);
+void launch_level0_up32(hipStream_t st, const LevelLeg& a, const float* u_in, const float* ring, const float* f,
+                        float* u_out, const float* ec);
+// the streamed and the 2-D form of these
 template <typename T>
-void launch_level_up(hipStream_t st, const LevelLeg& a, int n_post, bool rule, const T* u_in, const T* ring, const T* f,
-                     T* u_out, const T* ec, unsigned long long* maxbits);
-// (streamed, FP32: no norm)
+void launch_stream_down(hipStream_t st, const LevelLeg& a, int n_pre, const T* f, T* u, T* fc);
 template <typename T>
-void launch_stream_up(hipStream_t st, const LevelLeg& a, int n_post, int mode, const T* u_in, const T* ring, const T* f,
-                      T* u_out, const T* ec, unsigned long long* maxbits);
+void launch_stream_up(hipStream_t st, const LevelLeg& a, int n_post, const T* u_in, const T* f, T* u_out, const T* ec);
+void launch_stream0_down(hipStream_t st, const LevelLeg& a, int n_pre, const double* u_in, const double* f, double* u_out,
+                         double* fc);
+void launch_stream0_up(hipStream_t st, const LevelLeg& a, int n_post, const double* u_in, const double* ring,
+                       const double* f, double* u_out, const double* ec, unsigned long long* maxbits);
 template <typename T>
-void launch_tile2_up(hipStream_t st, const LevelLeg& a, int n_post, bool rule, const T* u_in, const T* ring, const T* f,
-                     T* u_out, const T* ec, unsigned long long* maxbits);
+void launch_tile2_down(hipStream_t st, const LevelLeg& a, int n_pre, const T* f, T* u, T* fc);
+template <typename T>
+void launch_tile2_up(hipStream_t st, const LevelLeg& a, int n_post, const T* u_in, const T* f, T* u_out, const T* ec);
+void launch_tile20_down(hipStream_t st, const LevelLeg& a, int n_pre, const double* u_in, const double* f, double* u_out,
+                        double* fc);
+void launch_tile20_up(hipStream_t st, const LevelLeg& a, int n_post, const double* u_in, const double* ring,
+                      const double* f, double* u_out, const double* ec, unsigned long long* maxbits);
 
 // learned initial guess network (np_net.hip); activations channel-last,
 // weights bfloat16 [27][cout][cin]

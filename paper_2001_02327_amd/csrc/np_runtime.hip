@@ -646,11 +646,10 @@ void coarse_part(const np_solver* s, int l, const MGView<T>& v, hipStream_t st)
                                     v.u[L + 1], 1, rule_of(s, l, L), seed ? v.h[L + 1] * v.h[L + 1] : 0.0);
     }
     for (int L = Lp; L < Lt; L++)
-        launch_level_down<T>(st, leg_of(s, l, v, L, 0), c.n_pre, true, v.u[L], v.f[L], v.u[L], v.f[L + 1]);
+        launch_level_down<T>(st, leg_of(s, l, v, L, 0), c.n_pre, v.f[L], v.u[L], v.f[L + 1]);
     if (Lt) tail(Lt);
     for (int L = Lt - 1; L >= Lp; L--)
-        launch_level_up<T>(st, leg_of(s, l, v, L, 0), npost, true, v.u[L], v.u[L], v.f[L], v.r[L],
-                           mg_result(s, l, v, L + 1), nullptr);
+        launch_level_up<T>(st, leg_of(s, l, v, L, 0), npost, v.u[L], v.f[L], v.r[L], mg_result(s, l, v, L + 1));
     for (int L = std::min(Lp, Lend); L > 1; L--) {
         launch_prolong_add<T, T>(d, st, v.g[L], mg_result(s, l, v, L), v.g[L - 1], v.u[L - 1], 0, rule_of(s, l, L));
         for (int it = 0; it < npost; it++) coarse_sweep(s, l, v, L - 1, st);
@@ -835,14 +834,14 @@ int vcycle_legs(np_solver* s, int l, double* u0, const double* f0, const MGView<
     hipStream_t st = s->stream;
     const bool big = full_sweep_waves(v.g[0]) >= kFullSweepMinWaves;
     prof_begin(s, big ? NP_KCLASS_FULL : NP_KCLASS_SMOOTH);
-    launch_level_down<double>(st, leg_of(s, l, v, 0, 0), c.n_pre, false, u0, f0, s->phi_alt, v.f[1]);
+    launch_level0_down(st, leg_of(s, l, v, 0, 0), c.n_pre, u0, f0, s->phi_alt, v.f[1]);
     prof_end(s);
     prof_begin(s, NP_KCLASS_COARSE);
     int rc = run_coarse(s, l, v, s->coarse_exec);
     prof_end(s);
     if (rc) return rc;
     prof_begin(s, big ? NP_KCLASS_FULL_RES : NP_KCLASS_SMOOTH);
-    launch_level_up<double>(st, leg_of(s, l, v, 0, 1), c.n_post, false, s->phi_alt, u0, f0, u0, mg_result(s, l, v, 1), bits);
+    launch_level0_up(st, leg_of(s, l, v, 0, 1), c.n_post, s->phi_alt, u0, f0, u0, mg_result(s, l, v, 1), bits);
     prof_end(s);
     return NP_OK;
 }
@@ -955,8 +954,7 @@ int vcycle_lo(np_solver* s, int l, bool red_done)
             LevelLeg a = leg_of(s, l, v, 0, 0);
             a.h2 = a.inv_h2 = 1.0;
             prof_begin(s, NP_KCLASS_SMOOTH);
-            launch_stream_down<float>(s->stream, a, s->cfg.n_pre, red_done ? kLegZero : kLegWarm, e, (const float*)s->r_lo,
-                                      mid, v.f[1], 1.0 / (h * h));
+            launch_level0_down32(s->stream, a, s->cfg.n_pre, red_done, e, (const float*)s->r_lo, mid, v.f[1], 1.0 / (h * h));
             prof_end(s);
             prof_begin(s, NP_KCLASS_COARSE);
             int rc = run_coarse(s, l, v, s->coarse_exec32);
@@ -964,8 +962,7 @@ int vcycle_lo(np_solver* s, int l, bool red_done)
             if (rc) return rc;
             a.rev = 1;
             prof_begin(s, NP_KCLASS_SMOOTH);
-            launch_stream_up<float>(s->stream, a, s->cfg.n_post, kLegWarm, mid, e, (const float*)s->r_lo, out,
-                                    mg_result(s, l, v, 1), nullptr);
+            launch_level0_up32(s->stream, a, mid, e, (const float*)s->r_lo, out, mg_result(s, l, v, 1));
             prof_end(s);
             if (red_done) std::swap(s->e_lo, s->e_nx);
             return NP_OK;

@@ -127,6 +127,8 @@ __device__ __forceinline__ void leg_store(__amdgpu_buffer_rsrc_t b, unsigned off
     else __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), b, off, 0, 0);
 }
 
+constexpr int kLegRule = 0, kLegWarm = 1, kLegZero = 2;
+
 // N sweeps, up or down.  kLegRule: a coarse level (ghost values by its rule, the down leg
 // starts from zero); otherwise multigrid level 0 with its ghost layer in memory: kLegWarm from
 // u_in, the up leg in FP64 with the max norm of the residual, kLegZero from zero.
@@ -706,43 +708,59 @@ static LegArgs<T> leg_args(const LevelLeg& a, const T* u_in, const T* ring, cons
     return A;
 }
 
-template <typename T>
-void launch_stream_down(hipStream_t st, const LevelLeg& a, int n_pre, int mode, const T* u_in, const T* f, T* u_out, T* fc,
-                        double out_scale)
+template <int MODE, typename T>
+static void stream_down(hipStream_t st, LegArgs<T> A, int n_pre, double out_scale)
 {
-    LegArgs<T> A = leg_args<T>(a, u_in, u_in, f, u_out, fc, nullptr, nullptr);
     A.scale = (T)0.125 * (T)out_scale;
-    const auto go = [&](auto m) {
-        if (n_pre == 1) leg3<T, 1, decltype(m)::value, false>(st, A);
-        else leg3<T, 2, decltype(m)::value, false>(st, A);
-    };
-    if (mode == kLegRule) return go(std::integral_constant<int, kLegRule>{});
-    if constexpr (sizeof(T) == 4) {
-        if (mode == kLegZero) return go(std::integral_constant<int, kLegZero>{});
-    }
-    go(std::integral_constant<int, kLegWarm>{});
+    if (n_pre == 1) leg3<T, 1, MODE, false>(st, A);
+    else leg3<T, 2, MODE, false>(st, A);
 }
 
 template <typename T>
-void launch_stream_up(hipStream_t st, const LevelLeg& a, int n_post, int mode, const T* u_in, const T* ring, const T* f,
-                      T* u_out, const T* ec, unsigned long long* maxbits)
+void launch_stream_down(hipStream_t st, const LevelLeg& a, int n_pre, const T* f, T* u, T* fc)
 {
-    const LegArgs<T> A = leg_args<T>(a, u_in, ring, f, u_out, nullptr, ec, maxbits);
-    const auto go = [&](auto m) {
-        if (n_post == 1) leg3<T, 1, decltype(m)::value, true>(st, A);
-        else leg3<T, 2, decltype(m)::value, true>(st, A);
-    };
-    if (mode == kLegRule) go(std::integral_constant<int, kLegRule>{});
-    else go(std::integral_constant<int, kLegWarm>{});
+    stream_down<kLegRule>(st, leg_args<T>(a, u, u, f, u, fc, nullptr, nullptr), n_pre, 1.0);
 }
 
-template void launch_stream_down<double>(hipStream_t, const LevelLeg&, int, int, const double*, const double*, double*,
-                                         double*, double);
-template void launch_stream_down<float>(hipStream_t, const LevelLeg&, int, int, const float*, const float*, float*, float*,
-                                        double);
-template void launch_stream_up<double>(hipStream_t, const LevelLeg&, int, int, const double*, const double*, const double*,
-                                       double*, const double*, unsigned long long*);
-template void launch_stream_up<float>(hipStream_t, const LevelLeg&, int, int, const float*, const float*, const float*,
-                                      float*, const float*, unsigned long long*);
+template <typename T>
+void launch_stream_up(hipStream_t st, const LevelLeg& a, int n_post, const T* u_in, const T* f, T* u_out, const T* ec)
+{
+    const LegArgs<T> A = leg_args<T>(a, u_in, u_in, f, u_out, nullptr, ec, nullptr);
+    if (n_post == 1) leg3<T, 1, kLegRule, true>(st, A);
+    else leg3<T, 2, kLegRule, true>(st, A);
+}
+
+void launch_stream0_down(hipStream_t st, const LevelLeg& a, int n_pre, const double* u_in, const double* f, double* u_out,
+                         double* fc)
+{
+    stream_down<kLegWarm>(st, leg_args<double>(a, u_in, u_in, f, u_out, fc, nullptr, nullptr), n_pre, 1.0);
+}
+
+void launch_stream0_up(hipStream_t st, const LevelLeg& a, int n_post, const double* u_in, const double* ring,
+                       const double* f, double* u_out, const double* ec, unsigned long long* maxbits)
+{
+    const LegArgs<double> A = leg_args<double>(a, u_in, ring, f, u_out, nullptr, ec, maxbits);
+    if (n_post == 1) leg3<double, 1, kLegWarm, true>(st, A);
+    else leg3<double, 2, kLegWarm, true>(st, A);
+}
+
+void launch_level0_down32(hipStream_t st, const LevelLeg& a, int n_pre, bool zero, const float* u_in, const float* f,
+                          float* u_out, float* fc, double out_scale)
+{
+    const LegArgs<float> A = leg_args<float>(a, u_in, u_in, f, u_out, fc, nullptr, nullptr);
+    if (zero) stream_down<kLegZero>(st, A, n_pre, out_scale);
+    else stream_down<kLegWarm>(st, A, n_pre, out_scale);
+}
+
+void launch_level0_up32(hipStream_t st, const LevelLeg& a, const float* u_in, const float* ring, const float* f,
+                        float* u_out, const float* ec)
+{
+    leg3<float, 1, kLegWarm, true>(st, leg_args<float>(a, u_in, ring, f, u_out, nullptr, ec, nullptr));
+}
+
+template void launch_stream_down<double>(hipStream_t, const LevelLeg&, int, const double*, double*, double*);
+template void launch_stream_down<float>(hipStream_t, const LevelLeg&, int, const float*, float*, float*);
+template void launch_stream_up<double>(hipStream_t, const LevelLeg&, int, const double*, const double*, double*, const double*);
+template void launch_stream_up<float>(hipStream_t, const LevelLeg&, int, const float*, const float*, float*, const float*);
 
 }  // namespace np

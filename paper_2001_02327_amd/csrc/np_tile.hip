@@ -646,43 +646,44 @@ static void up3(hipStream_t st, const LevelLeg& a, const T* u_in, const T* ring,
 }
 
 template <typename T>
-void launch_level_down(hipStream_t st, const LevelLeg& a, int n_pre, bool rule, const T* u_in, const T* f, T* u_out, T* fc)
+void launch_level_down(hipStream_t st, const LevelLeg& a, int n_pre, const T* f, T* u, T* fc)
 {
-    if (a.dim == 2) return launch_tile2_down<T>(st, a, n_pre, rule, u_in, f, u_out, fc);
-    if (!level_tile(3, a.g)) return launch_stream_down<T>(st, a, n_pre, rule ? kLegRule : kLegWarm, u_in, f, u_out, fc, 1.0);
-    if constexpr (sizeof(T) == 8) {
-        if (!rule) {
-            if (n_pre == 1) down3<T, 1, false>(st, a, u_in, f, u_out, fc);
-            else down3<T, 2, false>(st, a, u_in, f, u_out, fc);
-            return;
-        }
-    }
-    if (n_pre == 1) down3<T, 1, true>(st, a, u_in, f, u_out, fc);
-    else down3<T, 2, true>(st, a, u_in, f, u_out, fc);
+    if (a.dim == 2) return launch_tile2_down<T>(st, a, n_pre, f, u, fc);
+    if (!level_tile(3, a.g)) return launch_stream_down<T>(st, a, n_pre, f, u, fc);
+    if (n_pre == 1) down3<T, 1, true>(st, a, u, f, u, fc);
+    else down3<T, 2, true>(st, a, u, f, u, fc);
 }
 
 template <typename T>
-void launch_level_up(hipStream_t st, const LevelLeg& a, int n_post, bool rule, const T* u_in, const T* ring, const T* f,
-                     T* u_out, const T* ec, unsigned long long* maxbits)
+void launch_level_up(hipStream_t st, const LevelLeg& a, int n_post, const T* u_in, const T* f, T* u_out, const T* ec)
 {
-    if (a.dim == 2) return launch_tile2_up<T>(st, a, n_post, rule, u_in, ring, f, u_out, ec, maxbits);
-    if (!level_tile(3, a.g)) return launch_stream_up<T>(st, a, n_post, rule ? kLegRule : kLegWarm, u_in, ring, f, u_out, ec, maxbits);
-    if constexpr (sizeof(T) == 8) {
-        if (!rule) {
-            if (n_post == 1) up3<T, 1, false>(st, a, u_in, ring, f, u_out, ec, maxbits);
-            else up3<T, 2, false>(st, a, u_in, ring, f, u_out, ec, maxbits);
-            return;
-        }
-    }
-    if (n_post == 1) up3<T, 1, true>(st, a, u_in, ring, f, u_out, ec, maxbits);
-    else up3<T, 2, true>(st, a, u_in, ring, f, u_out, ec, maxbits);
+    if (a.dim == 2) return launch_tile2_up<T>(st, a, n_post, u_in, f, u_out, ec);
+    if (!level_tile(3, a.g)) return launch_stream_up<T>(st, a, n_post, u_in, f, u_out, ec);
+    if (n_post == 1) up3<T, 1, true>(st, a, u_in, u_in, f, u_out, ec, nullptr);
+    else up3<T, 2, true>(st, a, u_in, u_in, f, u_out, ec, nullptr);
 }
 
-template void launch_level_down<double>(hipStream_t, const LevelLeg&, int, bool, const double*, const double*, double*, double*);
-template void launch_level_down<float>(hipStream_t, const LevelLeg&, int, bool, const float*, const float*, float*, float*);
-template void launch_level_up<double>(hipStream_t, const LevelLeg&, int, bool, const double*, const double*, const double*,
-                                      double*, const double*, unsigned long long*);
-template void launch_level_up<float>(hipStream_t, const LevelLeg&, int, bool, const float*, const float*, const float*, float*,
-                                     const float*, unsigned long long*);
+void launch_level0_down(hipStream_t st, const LevelLeg& a, int n_pre, const double* u_in, const double* f, double* u_out,
+                        double* fc)
+{
+    if (a.dim == 2) return launch_tile20_down(st, a, n_pre, u_in, f, u_out, fc);
+    if (!level_tile(3, a.g)) return launch_stream0_down(st, a, n_pre, u_in, f, u_out, fc);
+    if (n_pre == 1) down3<double, 1, false>(st, a, u_in, f, u_out, fc);
+    else down3<double, 2, false>(st, a, u_in, f, u_out, fc);
+}
+
+void launch_level0_up(hipStream_t st, const LevelLeg& a, int n_post, const double* u_in, const double* ring,
+                      const double* f, double* u_out, const double* ec, unsigned long long* maxbits)
+{
+    if (a.dim == 2) return launch_tile20_up(st, a, n_post, u_in, ring, f, u_out, ec, maxbits);
+    if (!level_tile(3, a.g)) return launch_stream0_up(st, a, n_post, u_in, ring, f, u_out, ec, maxbits);
+    if (n_post == 1) up3<double, 1, false>(st, a, u_in, ring, f, u_out, ec, maxbits);
+    else up3<double, 2, false>(st, a, u_in, ring, f, u_out, ec, maxbits);
+}
+
+template void launch_level_down<double>(hipStream_t, const LevelLeg&, int, const double*, double*, double*);
+template void launch_level_down<float>(hipStream_t, const LevelLeg&, int, const float*, float*, float*);
+template void launch_level_up<double>(hipStream_t, const LevelLeg&, int, const double*, const double*, double*, const double*);
+template void launch_level_up<float>(hipStream_t, const LevelLeg&, int, const float*, const float*, float*, const float*);
 
 }  // namespace np

@@ -261,41 +261,40 @@ static T2Args<T> tile2_args(const LevelLeg& a, const T* u_in, const T* ring, con
 }
 
 template <typename T>
-void launch_tile2_down(hipStream_t st, const LevelLeg& a, int n_pre, bool rule, const T* u_in, const T* f, T* u_out, T* fc)
+void launch_tile2_down(hipStream_t st, const LevelLeg& a, int n_pre, const T* f, T* u, T* fc)
 {
-    const T2Args<T> A = tile2_args<T>(a, u_in, u_in, f, u_out, fc, nullptr, nullptr);
-    if constexpr (sizeof(T) == 8) {
-        if (!rule) {
-            if (n_pre == 1) tile2<T, 1, false, false>(st, A);
-            else tile2<T, 2, false, false>(st, A);
-            return;
-        }
-    }
+    const T2Args<T> A = tile2_args<T>(a, u, u, f, u, fc, nullptr, nullptr);
     if (n_pre == 1) tile2<T, 1, true, false>(st, A);
     else tile2<T, 2, true, false>(st, A);
 }
 
 template <typename T>
-void launch_tile2_up(hipStream_t st, const LevelLeg& a, int n_post, bool rule, const T* u_in, const T* ring, const T* f,
-                     T* u_out, const T* ec, unsigned long long* maxbits)
+void launch_tile2_up(hipStream_t st, const LevelLeg& a, int n_post, const T* u_in, const T* f, T* u_out, const T* ec)
 {
-    const T2Args<T> A = tile2_args<T>(a, u_in, ring, f, u_out, nullptr, ec, maxbits);
-    if constexpr (sizeof(T) == 8) {
-        if (!rule) {
-            if (n_post == 1) tile2<T, 1, false, true>(st, A);
-            else tile2<T, 2, false, true>(st, A);
-            return;
-        }
-    }
+    const T2Args<T> A = tile2_args<T>(a, u_in, u_in, f, u_out, nullptr, ec, nullptr);
     if (n_post == 1) tile2<T, 1, true, true>(st, A);
     else tile2<T, 2, true, true>(st, A);
 }
 
-template void launch_tile2_down<double>(hipStream_t, const LevelLeg&, int, bool, const double*, const double*, double*, double*);
-template void launch_tile2_down<float>(hipStream_t, const LevelLeg&, int, bool, const float*, const float*, float*, float*);
-template void launch_tile2_up<double>(hipStream_t, const LevelLeg&, int, bool, const double*, const double*, const double*,
-                                      double*, const double*, unsigned long long*);
-template void launch_tile2_up<float>(hipStream_t, const LevelLeg&, int, bool, const float*, const float*, const float*, float*,
-                                     const float*, unsigned long long*);
+void launch_tile20_down(hipStream_t st, const LevelLeg& a, int n_pre, const double* u_in, const double* f, double* u_out,
+                        double* fc)
+{
+    const T2Args<double> A = tile2_args<double>(a, u_in, u_in, f, u_out, fc, nullptr, nullptr);
+    if (n_pre == 1) tile2<double, 1, false, false>(st, A);
+    else tile2<double, 2, false, false>(st, A);
+}
+
+void launch_tile20_up(hipStream_t st, const LevelLeg& a, int n_post, const double* u_in, const double* ring,
+                      const double* f, double* u_out, const double* ec, unsigned long long* maxbits)
+{
+    const T2Args<double> A = tile2_args<double>(a, u_in, ring, f, u_out, nullptr, ec, maxbits);
+    if (n_post == 1) tile2<double, 1, false, true>(st, A);
+    else tile2<double, 2, false, true>(st, A);
+}
+
+template void launch_tile2_down<double>(hipStream_t, const LevelLeg&, int, const double*, double*, double*);
+template void launch_tile2_down<float>(hipStream_t, const LevelLeg&, int, const float*, float*, float*);
+template void launch_tile2_up<double>(hipStream_t, const LevelLeg&, int, const double*, const double*, double*, const double*);
+template void launch_tile2_up<float>(hipStream_t, const LevelLeg&, int, const float*, const float*, float*, const float*);
 
 }  // namespace np
