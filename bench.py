@@ -317,6 +317,28 @@ def keep_reference(solver, geom, Fs):
     return out
 
 
+def smoothing_elements(elem, n_pre, legs, cycles, outer_steps):
+    """Elements of the storage type (elem bytes) that a launch of each smoothing class has to move per grid point of
+    multigrid level 0 (both colours counted).
+
+      half sweep: read the other colour, read f of this colour, write this colour: 1.5;
+      seeded black half sweep of a defect-correction step: read the defect of both
+      colours, write black (and with one pre-smoothing sweep also the red start): 1.5 or 2;
+      full sweep (FP64, 3-D): read P's black points, f of both colours, write both
+      colours of Q: 2.5; the one that completes the stop test's residual also
+      reads P's red points: 3;
+      fused leg down: read black, f of both colours, write black and the coarse right-hand side:
+      2.125, from zero 1.625 (with FP32 storage the first cycle of every outer step);
+      fused leg up: read black, f and the coarse correction, write both colours: 2.625.
+      Legs are one class (smooth) with FP32 storage and on small grids, two (full: down,
+      full_res: up) on large ones in FP64.
+    """
+    if not legs:
+        return dict(smooth=1.5, seeded=2.0 if n_pre == 1 else 1.5, full=2.5, full_res=3.0)
+    down = 2.125 - (0.5 * outer_steps / cycles if elem == 4 and cycles else 0.0)
+    return dict(smooth=0.5 * (down + 2.625), full=down, full_res=2.625)
+
+
 def run_variant(name, wl, rho, phi_outer, Fs, steps, warmup, inner_cycles, stop_rule="residual", ref=None,
                 keep=False):
     """Warm-up, then `steps` timed steps (solve + forces on every level) with the
@@ -374,22 +396,13 @@ def run_variant(name, wl, rho, phi_outer, Fs, steps, warmup, inner_cycles, stop_
     ms_profiled = e0.elapsed_time(e1) / steps
     prof = solver.profile()
     solver.set_profiling(False)
-    # algorithmic bytes per grid point of multigrid level 0 (both colours counted),
-    # in elements e of the storage type, of each smoothing kernel class:
-    #   half sweep: read the other colour, read f of this colour, write this colour: 1.5 e;
-    #   seeded black half sweep of a defect-correction step: read the defect of both
-    #   colours, write black (and with one pre-smoothing sweep also the red start): 1.5 or 2 e;
-    #   full sweep (FP64, 3-D): read P's black points, f of both colours, write both
-    #   colours of Q: 2.5 e; the one that completes the stop test's residual also
-    #   reads P's red points: 3 e.
     elem = ELEM[v["precision"]]
     npts = math.prod(v + 2 for v in geom.ext(0))
-    #   fused legs (FP64 and FP32 storage): down: read black, f of both colours, write black and
-    #   the coarse right-hand side: 2.125 e (from zero 1.625 e); up: read black, f and the
-    #   coarse correction, write both colours: 2.625 e; FP32 and small grids: one class.
-    per_point = dict(smooth=1.5, seeded=2.0 if v.get("n_pre", 2) == 1 else 1.5, full=2.5, full_res=3.0)
-    if elem >= 4 and v.get("sweep", "full") == "full":
-        per_point.update(smooth=2.375, full=2.125, full_res=2.625)
+    # fused legs restrict and prolong within their launches (a workload's levels of one size run
+    # one form): told by what ran
+    legs = prof["restrict"][0] == 0 and prof["black_restrict"][0] == 0
+    per_point = smoothing_elements(elem, v.get("n_pre", 2), legs, sum(sum(st["cycles"]) for st in stats),
+                                   sum(sum(st["outer_steps"]) for st in stats))
     uniform = len(set(geom.ext(l) for l in range(geom.nlevels))) == 1
     sweeps = {}
     for cls, e in per_point.items():
@@ -423,7 +436,7 @@ def run_variant(name, wl, rho, phi_outer, Fs, steps, warmup, inner_cycles, stop_
                               bytes_per_launch=b, GBps=round(b / (ms_c / cnt * 1e-3) / 1e9, 1))
     # the roofline kernel: the smoothing class with the most device time
     main_cls = max((c for c in ("smooth", "full") if c in sweeps), key=lambda c: sweeps[c]["ms_per_step"])
-    smoother = dict(sweeps[main_cls], kind=main_cls, elem_bytes=elem, classes=sweeps)
+    smoother = dict(sweeps[main_cls], kind=main_cls, legs=legs, elem_bytes=elem, classes=sweeps)
     linf = linf_force_error(solver, wl, Fs)
     edge = edge_force_error(solver, wl, Fs)
     dev = None
@@ -586,8 +599,8 @@ def main():
         "roofline": None if not uniform else {
             "bound": "hbm",
             "kernel": "level-0 red-black %s of variant %s (%d-byte storage)"
-                      % ("half sweep" if sm["elem_bytes"] == 2 and sm["kind"] == "smooth" else
-                         "fused V-cycle leg" if sm["elem_bytes"] >= 4 else "full sweep (one pass, two buffers)", best,
+                      % ("fused V-cycle leg" if sm["legs"] else
+                         "half sweep" if sm["kind"] == "smooth" else "full sweep (one pass, two buffers)", best,
                          sm["elem_bytes"]),
             "achieved": sm["GBps"],
             "peak": PEAK_HBM_GBS,
