@@ -339,6 +339,16 @@ def smoothing_elements(elem, n_pre, legs, cycles, outer_steps):
     return dict(smooth=0.5 * (down + 2.625), full=down, full_res=2.625)
 
 
+def variant_line(r):
+    """What the JSON line says of a variant (everything measured of it goes to stderr): a dozen variants with
+    their kernel tables made a line of 28 KB, of which a record that keeps a few KB lost the beginning."""
+    short = lambda x: float("%.6g" % x)  # noqa: E731
+    dev = r["deviation_from_fp64"]
+    return dict(ms_per_solve=r["ms_per_solve"], cycles_per_level=r["cycles_per_level"],
+                outer_steps_per_level=r["outer_steps_per_level"], linf_force_error=short(r["linf_force_error"]),
+                deviation_from_fp64=dev and dict(phi_rel=short(dev["phi_rel"]), force_rel=short(dev["force_rel"])))
+
+
 def run_variant(name, wl, rho, phi_outer, Fs, steps, warmup, inner_cycles, stop_rule="residual", ref=None,
                 keep=False):
     """Warm-up, then `steps` timed steps (solve + forces on every level) with the
@@ -628,8 +638,9 @@ def main():
         # against plain FP64 run with the headline's own V-cycle schedule
         "speedup_vs_plain_fp64_same_schedule": (
             round(res[p]["ms_per_solve"] / b["ms_per_solve"], 3) if (p := same_schedule_fp64(best)) in res else None),
-        "variants": res,
+        "variants": {v: variant_line(r) for v, r in res.items()},
     }
+    log("variants", json.dumps(res))
     print(json.dumps(out), flush=True)
 
 
