@@ -114,7 +114,11 @@ extern "C" {
  * runs inside the restriction that follows it (Sec. 2.3 steps 2-5 in one pass;
  * needs N^0 = 2 N^1 along every axis and an odd N^1_x, elsewhere they run
  * apart).  On MI355X this pass is slower than the two kernels it replaces, so
- * it is not the default.  NP_SWEEP_HALF and NP_SWEEP_FULL_ALL run no fused legs.  The iterates are the same in all four. */
+ * it is not the default.  NP_SWEEP_HALF and NP_SWEEP_FULL_ALL run no fused legs.
+ * The legs need memory beyond the per-pass kernels' (FP64: a second potential buffer, for
+ * patches solved as a batch one of the batch's size; one more array per coarse level); a
+ * handle created without room for it runs as if its sweep counts did not fit the legs.
+ * The iterates are the same in all four. */
 #define NP_SWEEP_FULL 0
 #define NP_SWEEP_HALF 1
 #define NP_SWEEP_FUSED 2

@@ -447,7 +447,7 @@ __global__ void __launch_bounds__(kBlock) k_forces(SGrid g, double m12dx, const 
 // lanes load them.  Same arithmetic as k_forces.  DELTA: the force-change stop
 // test (Sec. 3.1): the arrays hold the previous iterate's forces, each point's
 // new value replaces the old one and max |F_new - F_old| over the points and
-// components goes to maxbits (as k_force_delta, value for value).
+// components goes to maxbits (in 2-D: k_force_delta2).
 // planes and rows per thread: (8, 4) measured best of (4, 1), (4, 2), (2, 4), (4, 4),
 // (4, 8), (2, 8) at 512^3 (1.61 -> 1.28 ms, with every x-neighbour loaded)
 constexpr int kForceChunk = 8;

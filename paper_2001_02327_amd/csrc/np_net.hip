@@ -964,8 +964,16 @@ __global__ void __launch_bounds__(256) k_conv16_to_few_f32(const float* __restri
 //             the volume enters as zero; an input that is not finite is left out
 //             of the products and its pairs are added one by one.
 // The four wavefronts' sums meet in LDS in a fixed order.  At 130^3 with the
-// second stage: 5136 -> 449, 1341 -> 108 and 1885 -> 90 us.
+// second stage: 5136 -> 450, 1341 -> 109 and 1885 -> 93 us.
+// A running sum over a workgroup's whole range would round more the larger the volume (258^3
+// voxels, gradients of either sign: 2.3e-6, 1.1e-6 and 1.5e-6 of the largest gradient from 64
+// bits in the order above; voxel rows summed by k_conv_bwd_weight_part 4.3e-7, 3.3e-7 and 4.6e-7).
+// So with few accumulators the sums of kWgStep blocks of voxels are added to a second set; the 27
+// of 16 -> 16 leave no registers for one, and where a workgroup has more than 2 kWgRun
+// blocks (130^3 voxels: 20), runs of kWgRun are added to its partial: 4.0e-7, 3.1e-7 and
+// 3.7e-7, for 2 to 5 % of the time.
 constexpr int kWgBlocks = 512;
+constexpr long kWgStep = 4, kWgRun = 10;
 
 template <int CI, int CO>
 __global__ void __launch_bounds__(256, 2) k_conv_bwd_weight_mfma(const float* __restrict__ in, const float* __restrict__ gout,
@@ -982,10 +990,10 @@ __global__ void __launch_bounds__(256, 2) k_conv_bwd_weight_mfma(const float* __
     float* const halo = lds;
     float* const blk = lds + kTNV * HC;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, q = lane >> 4, r = lane & 15;
-    v4f acc[NA];
-#pragma unroll
-    for (int a = 0; a < NA; a++) acc[a] = v4f{0.f, 0.f, 0.f, 0.f};
-    float accb = 0.0f;
+    constexpr bool TWO = NA <= 4;                             // a second set of accumulators
+    v4f acc[NA], sum[TWO ? NA : 1];
+    float accb;
+    double sumb;  // (one addition per block of voxels)
     // halo offset of the lane's row or column in each product
     int hoff[LAST || CI == 2 ? NA : 1];
     bool hlive[LAST || CI == 2 ? NA : 1];
@@ -1034,111 +1042,137 @@ __global__ void __launch_bounds__(256, 2) k_conv_bwd_weight_mfma(const float* __
 #pragma unroll
         for (int s = 0; s < 4; s++) nc[s] = inside ? src[s] : make_float4(0.f, 0.f, 0.f, 0.f);
     };
-    if (first < last) fetch(conv_tile(first, Z, Y, X));
-    for (long id = first; id < last; id++) {
-        const ConvTile T = conv_tile(id, Z, Y, X);
-        __syncthreads();  // the previous block's operands have been read
+    const auto clear = [](auto& v) {
 #pragma unroll
-        for (int j = 0; j < NR; j++) {
-            const int v = (int)threadIdx.x + 256 * j;
-            if (v >= kTNV) break;
-            if constexpr (HC == 16) {
+        for (v4f& x : v) x = v4f{0.f, 0.f, 0.f, 0.f};
+    };
+    const long len = TWO || last - first <= 2 * kWgRun ? last - first : kWgRun;
+    for (long run = first; run < last; run += len) {
+        const long end = run + len < last ? run + len : last;
+        clear(acc);
+        clear(sum);
+        accb = 0.0f;
+        sumb = 0.0;
+        fetch(conv_tile(run, Z, Y, X));
+        for (long id = run; id < end; id++) {
+            const ConvTile T = conv_tile(id, Z, Y, X);
+            __syncthreads();  // the previous block's operands have been read
 #pragma unroll
-                for (int s = 0; s < HV; s++) ((float4*)(halo + v * 16))[s] = nh[j][s];
-            } else {
-                halo[v * HC] = nh[j][0].x;
-                if (HC == 2) halo[v * HC + 1] = nh[j][0].y;
+            for (int j = 0; j < NR; j++) {
+                const int v = (int)threadIdx.x + 256 * j;
+                if (v >= kTNV) break;
+                if constexpr (HC == 16) {
+#pragma unroll
+                    for (int s = 0; s < HV; s++) ((float4*)(halo + v * 16))[s] = nh[j][s];
+                } else {
+                    halo[v * HC] = nh[j][0].x;
+                    if (HC == 2) halo[v * HC + 1] = nh[j][0].y;
+                }
             }
-        }
-        if constexpr (LAST) {
-            const int x = T.x0 + (cv & 15), y = T.y0 + (cv >> 4 & 3), z = T.z0 + (cv >> 6);
-            if (x < X && y < Y && z < Z) {
-                float* const c16 = &nc[0].x;
-                const long g = (((long)T.b * Z + z) * Y + y) * X + x;
-                const float g0 = gout[g];
-                const bool gfin = fabsf(g0) < INFINITY;
+            if constexpr (LAST) {
+                const int x = T.x0 + (cv & 15), y = T.y0 + (cv >> 4 & 3), z = T.z0 + (cv >> 6);
+                if (x < X && y < Y && z < Z) {
+                    float* const c16 = &nc[0].x;
+                    const long g = (((long)T.b * Z + z) * Y + y) * X + x;
+                    const float g0 = gout[g];
+                    const bool gfin = fabsf(g0) < INFINITY;
 #pragma unroll
-                for (int i = 0; i < 16; i++) {
-                    const float a = c16[i];
-                    const bool fin = fabsf(a) < INFINITY;
-                    if (!fin) c16[i] = 0.0f;
-                    if (fin && gfin) continue;
-                    // (inf and NaN: the order of these additions does not matter)
+                    for (int i = 0; i < 16; i++) {
+                        const float a = c16[i];
+                        const bool fin = fabsf(a) < INFINITY;
+                        if (!fin) c16[i] = 0.0f;
+                        if (fin && gfin) continue;
+                        // (inf and NaN: the order of these additions does not matter)
 #pragma unroll 1
-                    for (int t = 0; t < 27; t++) {
-                        const int dz = t / 9 - 1, dy = t / 3 % 3 - 1, dx = t % 3 - 1;
-                        const auto in_volume = [&](int zz, int yy, int xx) {
-                            return zz >= 0 && zz < Z && yy >= 0 && yy < Y && xx >= 0 && xx < X;
-                        };
-                        if (!fin && in_volume(z - dz, y - dy, x - dx))
-                            atomicAdd(&extra[t * 16 + i],
-                                      a * gout[(((long)T.b * Z + z - dz) * Y + y - dy) * X + x - dx]);
-                        if (!gfin && !in_volume(z + dz, y + dy, x + dx)) atomicAdd(&extra[t * 16 + i], g0 * 0.0f);
+                        for (int t = 0; t < 27; t++) {
+                            const int dz = t / 9 - 1, dy = t / 3 % 3 - 1, dx = t % 3 - 1;
+                            const auto in_volume = [&](int zz, int yy, int xx) {
+                                return zz >= 0 && zz < Z && yy >= 0 && yy < Y && xx >= 0 && xx < X;
+                            };
+                            if (!fin && in_volume(z - dz, y - dy, x - dx))
+                                atomicAdd(&extra[t * 16 + i],
+                                          a * gout[(((long)T.b * Z + z - dz) * Y + y - dy) * X + x - dx]);
+                            if (!gfin && !in_volume(z + dz, y + dy, x + dx)) atomicAdd(&extra[t * 16 + i], g0 * 0.0f);
+                        }
                     }
                 }
             }
-        }
 #pragma unroll
-        for (int s = 0; s < 4; s++) ((float4*)(blk + cv * 16))[s] = nc[s];
-        __syncthreads();
-        if (id + 1 < last) fetch(conv_tile(id + 1, Z, Y, X));
-        // a voxel past the row's end: gout is zero there, and so is what it multiplies
+            for (int s = 0; s < 4; s++) ((float4*)(blk + cv * 16))[s] = nc[s];
+            __syncthreads();
+            if (id + 1 < end) fetch(conv_tile(id + 1, Z, Y, X));
+            // a voxel past the row's end: gout is zero there, and so is what it multiplies
 #pragma unroll 1
-        for (int p = 0; p < 4; p++) {
-            if (T.z0 + wave >= Z || T.y0 + p >= Y) break;
-            const float* h0 = halo + ((wave * kTSY + p) * kTSX + q) * HC;
-            const float* c0 = blk + ((wave * 4 + p) * 16 + q) * BC + r;
+            for (int p = 0; p < 4; p++) {
+                if (T.z0 + wave >= Z || T.y0 + p >= Y) break;
+                const float* h0 = halo + ((wave * kTSY + p) * kTSX + q) * HC;
+                const float* c0 = blk + ((wave * 4 + p) * 16 + q) * BC + r;
 #pragma unroll KU
-            for (int k4 = 0; k4 < 4; k4++, h0 += 4 * HC, c0 += 4 * BC) {
-                const float g = *c0;
-                const bool vox = T.x0 + 4 * k4 + q < X;
-                if constexpr (!LAST) accb += g;
+                for (int k4 = 0; k4 < 4; k4++, h0 += 4 * HC, c0 += 4 * BC) {
+                    const float g = *c0;
+                    const bool vox = T.x0 + 4 * k4 + q < X;
+                    if constexpr (!LAST) accb += g;
 #pragma unroll
-                for (int a = 0; a < NA; a++) {
-                    if constexpr (LAST) {
-                        const float h = hlive[a] && vox ? h0[hoff[a]] : 0.0f;
-                        acc[a] = __builtin_amdgcn_mfma_f32_16x16x4f32(h, g, acc[a], 0, 0, 0);
-                        if (a == 0 && r == 13) accb += h;  // the centre tap's row: gout of the voxel itself
-                    } else if constexpr (CI == 2) {
-                        const float h = hlive[a] && vox ? h0[hoff[a]] : 0.0f;
-                        acc[a] = __builtin_amdgcn_mfma_f32_16x16x4f32(g, h, acc[a], 0, 0, 0);
-                    } else {
-                        const float h = h0[((a / 9 * kTSY + a / 3 % 3) * kTSX + a % 3) * 16 + r];
-                        acc[a] = __builtin_amdgcn_mfma_f32_16x16x4f32(g, vox ? h : 0.0f, acc[a], 0, 0, 0);
+                    for (int a = 0; a < NA; a++) {
+                        if constexpr (LAST) {
+                            const float h = hlive[a] && vox ? h0[hoff[a]] : 0.0f;
+                            acc[a] = __builtin_amdgcn_mfma_f32_16x16x4f32(h, g, acc[a], 0, 0, 0);
+                            if (a == 0 && r == 13) accb += h;  // the centre tap's row: gout of the voxel itself
+                        } else if constexpr (CI == 2) {
+                            const float h = hlive[a] && vox ? h0[hoff[a]] : 0.0f;
+                            acc[a] = __builtin_amdgcn_mfma_f32_16x16x4f32(g, h, acc[a], 0, 0, 0);
+                        } else {
+                            const float h = h0[((a / 9 * kTSY + a / 3 % 3) * kTSX + a % 3) * 16 + r];
+                            acc[a] = __builtin_amdgcn_mfma_f32_16x16x4f32(g, vox ? h : 0.0f, acc[a], 0, 0, 0);
+                        }
                     }
                 }
             }
-        }
-    }
-    // bias: the four voxel lanes of a channel, then the wavefronts with the weights
-    accb += __shfl_xor(accb, 16, 64);
-    accb += __shfl_xor(accb, 32, 64);
-    for (int wv = 0; wv < 4; wv++) {
-        __syncthreads();
-        if (wave != wv) continue;
+            sumb += (double)accb;
+            accb = 0.0f;
+            if (TWO && ((id - run) % kWgStep == kWgStep - 1 || id + 1 == end)) {
 #pragma unroll
-        for (int a = 0; a < NA; a++)
-#pragma unroll
-            for (int e = 0; e < 4; e++) {
-                const int m = 4 * q + e;  // row
-                int at;
-                if constexpr (LAST) at = 16 * a + m < 27 ? (16 * a + m) * 16 + r : -1;
-                else if constexpr (CI == 2) at = 16 * a + r < 54 ? ((16 * a + r) / 2 * 16 + m) * 2 + (r & 1) : -1;
-                else at = (a * 16 + m) * 16 + r;
-                if (at >= 0) lds[at] = wv == 0 ? acc[a][e] : lds[at] + acc[a][e];
+                for (int a = 0; a < (TWO ? NA : 0); a++) sum[a] += acc[a];
+                clear(acc);
             }
-        const bool mine = LAST ? lane == 13 : lane < 16;
-        if (mine) {
-            const int at = 27 * CI * CO + (LAST ? 0 : lane);
-            lds[at] = wv == 0 ? accb : lds[at] + accb;
         }
-    }
-    __syncthreads();
-    for (int e = threadIdx.x; e < NE; e += 256) {
-        float v = lds[e];
-        if constexpr (LAST)
-            if (e < 27 * 16) v += extra[e];
-        part[(long)blockIdx.x * NE + e] = v;
+        // the wavefronts' sums into the workgroup's partial; bias: the four voxel lanes of a
+        // channel first
+        sumb += __shfl_xor(sumb, 16, 64);
+        sumb += __shfl_xor(sumb, 32, 64);
+        v4f(&tot)[NA] = [&]() -> v4f(&)[NA] {
+            if constexpr (TWO) return sum;
+            else return acc;
+        }();
+        for (int wv = 0; wv < 4; wv++) {
+            __syncthreads();
+            if (wave != wv) continue;
+#pragma unroll
+            for (int a = 0; a < NA; a++)
+#pragma unroll
+                for (int e = 0; e < 4; e++) {
+                    const int m = 4 * q + e;  // row
+                    int at;
+                    if constexpr (LAST) at = 16 * a + m < 27 ? (16 * a + m) * 16 + r : -1;
+                    else if constexpr (CI == 2) at = 16 * a + r < 54 ? ((16 * a + r) / 2 * 16 + m) * 2 + (r & 1) : -1;
+                    else at = (a * 16 + m) * 16 + r;
+                    if (at >= 0) lds[at] = wv == 0 ? tot[a][e] : lds[at] + tot[a][e];
+                }
+            const bool mine = LAST ? lane == 13 : lane < 16;
+            if (mine) {
+                const int at = 27 * CI * CO + (LAST ? 0 : lane);
+                lds[at] = wv == 0 ? (float)sumb : lds[at] + (float)sumb;
+            }
+        }
+        __syncthreads();
+        for (int e = threadIdx.x; e < NE; e += 256) {
+            float v = lds[e];
+            float* const p = part + (long)blockIdx.x * NE + e;
+            if (run != first) v += *p;
+            if constexpr (LAST)
+                if (end == last && e < 27 * 16) v += extra[e];
+            *p = v;
+        }
     }
 }
 

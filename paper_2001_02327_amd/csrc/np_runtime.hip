@@ -557,8 +557,12 @@ bool dc_seed_black(const np_solver* s, int l)
 // the mixed precisions, from the first one on if that has 2^23 points, or from the
 // first one on that the block form serves: FP32 streamed / per pass 257^3 points V(2,1)
 // 127 / 184 us, V(1,1) 113 / 141, V(1,2) 162 / 181; 129^3 47.5 / 45.5, 36.5 / 34.6, 59 / 47;
-// together the larger one decides.  (FP16 storage is as fast or faster per pass: 514^3 points
-// V(1,1) 567 us, streamed 790.)
+// together the larger one decides.  In whole solves of 300^3 to 512^3 cells (first coarse
+// levels of 3.4 to 17 million points, both sides of the line) streaming them is between 4 %
+// slower (mostly two post-smoothing sweeps) and 9 % faster, 2 % faster in the mean.  (FP16
+// storage is as fast or faster per pass: 514^3 points V(1,1) 567 us, streamed 790.)  FP32 level 0
+// wants an even row length: on odd ones the outer pass stores the start of the next
+// correction, red points relaxed, and the legs have no form that takes over from there.
 constexpr size_t kStreamPoints32 = 1 << 23;
 
 int legs_level(const np_solver* s, int l)
@@ -773,9 +777,11 @@ int vcycle_t(np_solver* s, int l, T0* u0, const T0* f0, double h2_0, double inv_
 // 3 x 128^3 stack took 15.2 ms per solve with full sweeps and 8.6 ms with half
 // sweeps, eight 64^3 patches one after another 46.7 and 27.3 ms, a 512 x 512 x
 // 64 slab (1080 waves) 150 us per full sweep against two half sweeps of 48 us;
-// 2 x 256^3 (952 waves) alike, 512^3 (7128 waves) faster with full sweeps.  The
-// profile counts the fused legs of such levels with the full sweeps, those of
-// smaller ones with the half sweeps.
+// 2 x 256^3 (952 waves) alike, 512^3 (7128 waves) faster with full sweeps.  They run
+// with three or more sweeps (one or two: fused legs) or by NP_SWEEP_FULL_ALL.  The
+// profile's classes keep that line: the fused legs of such levels are booked as full
+// sweeps, those of smaller ones as half sweeps; a level that runs legs has no launch
+// in the classes of the restriction and the prolongation.
 constexpr long kFullSweepMinWaves = 4096;
 
 // Queues the read of n reduction slots from `slot` on, which zeroes them for their next
@@ -879,7 +885,7 @@ void full_sweep(np_solver* s, int l, int mode)
 
 // Plain FP64 V-cycle (Sec. 2.3 steps 2-13) with full sweeps on multigrid level
 // 0.  The last post-smoothing sweep takes the residual norm of its black points
-// into slot 0 (zeroed here); full_sweep_norm_sync completes it.  With
+// into slot 0 (zeroed by its last read); full_sweep_norm_sync completes it.  With
 // first_done the first pre-smoothing sweep has already run (by
 // full_sweep_norm_sync, its result in the spare buffer).
 int vcycle_full(np_solver* s, int l, bool first_done)

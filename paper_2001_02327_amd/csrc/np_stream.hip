@@ -31,8 +31,9 @@
 // What bounds it: a step is some 200 instructions per wavefront, 25 LDS accesses and a
 // barrier, with the registers of two wavefronts per SIMD in FP64: 1.2 to 1.4 us, and the
 // columns along the boundary, whose steps are the longest, decide; at 514^3 points the
-// memory system as much: 2.9 and 3.5 GB a leg, a third of the reads the halo's that the L2 did
-// not keep, at 4.0 and 4.2 TB/s (non-temporal stores do not help: 758 and 871 us).
+// memory system as much: 2.9 and 3.5 GB moved a leg, a third of the reads the halo's that the
+// L2 did not keep, at 4.0 and 4.2 TB/s (2.3 and 2.85 GB that a leg cannot do without: 3.2
+// and 3.5 TB/s; non-temporal stores do not help: 758 and 871 us).
 // Measured, V(2,1) in FP64, down + up: 514^3 729 + 816 us against 2.79 ms in full sweeps,
 // restriction and prolongation; 258^3 107 + 114 us against 419; 130^3 32 + 26 against 87; coarse 129^3 35 + 22 against 80.
 // FP32, two workgroups per CU: coarse 257^3 67 + 60 us against 184.

@@ -1,7 +1,7 @@
 // Fused V-cycle legs of a 2-D multigrid level (gfx950).
 //
-// The 2-D levels are bound by launch latency at every size that the solver is used
-// at: a kernel takes 3-5 us whether it sweeps 66^2 or 514^2 points, and a V(2,1)
+// The 2-D levels are bound by launch latency up to about 1000^2 points: a kernel takes
+// 3-5 us whether it sweeps 66^2 or 514^2 points, and a V(2,1)
 // cycle runs eight of them per level.  As on the small 3-D levels (np_tile.hip) a
 // whole leg of the cycle is one launch here:
 //   down: the pre-smoothing sweeps, the residual and its restriction;
@@ -16,7 +16,11 @@
 //
 // What bounds it: the chain of a load, N half sweeps of an LDS round trip and a
 // barrier, and a store: 4 to 5 us a leg up to 514^2 points, with the halo's work 15 us
-// at 1026^2; per pass 26 to 30 us a level and cycle, 52 at 1026^2.
+// at 1026^2; per pass 26 to 30 us a level and cycle, 52 at 1026^2.  On larger levels the points
+// decide, and the legs stay ahead of the per-pass kernels: six cycles of a single level, per pass
+// and legs, FP64 V(2,1) 2048^2 1.98 / 1.09 ms, 4096^2 4.32 / 3.11, 8192^2 15.0 / 11.2, 16384^2
+// (the largest there is) 60.3 / 43.3; V(2,2) 4096^2 5.08 / 3.88; FP32's coarse levels 4096^2
+// 3.30 / 2.85, 8192^2 11.5 / 11.4, 16384^2 46 / 45.
 #include <type_traits>
 
 #include "np_device.h"
