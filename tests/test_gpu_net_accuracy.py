@@ -22,10 +22,11 @@ def _reference(x, g):
     n, ci, co = x.shape[1], x.shape[-1], g.shape[-1]
     xp = torch.zeros((n + 2,) * 3 + (ci,), dtype=torch.float64, device="cuda")
     xp[1:-1, 1:-1, 1:-1] = x[0].double()
-    gt = g.double().reshape(-1, co).t().contiguous()
+    gt = g[0].double().reshape(n, n * n, co).transpose(1, 2).contiguous()  # plane by plane
     taps = [(t // 9, t // 3 % 3, t % 3) for t in range(27)]
-    w = torch.stack([gt @ xp[a:a + n, b:b + n, c:c + n].reshape(-1, ci).contiguous() for a, b, c in taps])
-    return w.reshape(-1), gt.sum(1)
+    w = torch.stack([torch.bmm(gt, xp[a:a + n, b:b + n, c:c + n].reshape(n, n * n, ci).contiguous()).sum(0)
+                     for a, b, c in taps])
+    return w.reshape(-1), gt.sum((0, 2))
 
 
 def _gradients(x, g, off):
